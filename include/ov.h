@@ -358,7 +358,8 @@ ov_status ov_tune_ms(ov_ctx *ctx, int prec, int nrhs, int block, int sites_per_t
  * completion of the preceding work to the kernel's completion, so it includes
  * the dispatch gap), the number of sampled launches, their summed algorithmic
  * HBM bytes (3 spinor fields per site and pass: two read, one written; two
- * passes per iteration), and the summed kernel-only span max(end) - min(start)
+ * passes per iteration; the resident kernel, which keeps r and t on the chip, the one
+ * field per site and iteration that it writes), and the summed kernel-only span max(end) - min(start)
  * over the workgroups (ms; what a kernel trace reports) with its launch count.
  * Any output pointer may be NULL.  reset != 0 clears the sums.  The stamp buffer
  * (2 x 8 bytes per workgroup and sampled launch) is allocated with hipMalloc

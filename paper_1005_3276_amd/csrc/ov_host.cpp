@@ -137,4 +137,57 @@ void free_spectrum(const ov_params* p, double& smin, double& smax) {
         }
 }
 
+// Modelled time of one pass of k_ms_res (us), fitted to a sweep of blocks on MI355X (FP64,
+// 4^4 to 16^3x32, 1 to 256 workgroups of 48 to 864 sites: within 12%): the sites of a
+// workgroup, the exchange among G of them, the faces, and short rows of x.
+static double res_us(const ResGeom& r, int esize) {
+  double us = 0.9 + r.S * (esize == 16 ? 0.0021 : 0.0013) + 0.3 / r.b[0];
+  if (r.G > 1) us += 0.95 + 0.0045 * r.G + (double)r.FT * esize * r.G / 5.5e6;
+  return us;
+}
+
+ResGeom res_geom(const int dims[4], int esize, int ncu, int maxK) {
+  ResGeom best;
+  double cost = 1e300;
+  int b[4];
+  for (b[0] = 1; b[0] <= dims[0]; ++b[0]) {
+    if (dims[0] % b[0]) continue;
+    for (b[1] = 1; b[1] <= dims[1]; ++b[1]) {
+      if (dims[1] % b[1]) continue;
+      for (b[2] = 1; b[2] <= dims[2]; ++b[2]) {
+        if (dims[2] % b[2]) continue;
+        for (b[3] = 1; b[3] <= dims[3]; ++b[3]) {
+          if (dims[3] % b[3]) continue;
+          if (b[0] > 255 || b[1] > 255 || b[2] > 255 || b[3] > 255) continue;
+          const long long S = (long long)b[0] * b[1] * b[2] * b[3];
+          if (S > (long long)RES_MAX_THREADS * maxK || S * 4 * esize > RES_MAX_LDS) continue;
+          ResGeom r;
+          long long G = 1;
+          r.S = (int)S;
+          for (int mu = 0; mu < 4; ++mu) {
+            r.b[mu] = b[mu];
+            r.nb[mu] = dims[mu] / b[mu];
+            G *= r.nb[mu];
+            if (r.nb[mu] > 1) r.FT += 4 * (r.S / b[mu]);
+          }
+          bool thin = false;  // a cut axis needs two sites in the block
+          for (int mu = 0; mu < 4; ++mu) thin |= r.nb[mu] > 1 && b[mu] < 2;
+          if (G > ncu || thin) continue;
+          r.G = (int)G;
+          r.K = (r.S + RES_MAX_THREADS - 1) / RES_MAX_THREADS;
+          r.threads = (r.S + 64 * r.K - 1) / (64 * r.K) * 64;
+          r.us = res_us(r, esize);
+          // two sources per system is the solver's launch: half the CUs each
+          const double c = r.us * (1 + (2 * r.G + ncu - 1) / ncu);
+          if (c < cost) {
+            cost = c;
+            best = r;
+          }
+        }
+      }
+    }
+  }
+  return best;
+}
+
 }  // namespace ov

@@ -27,6 +27,7 @@
 
 namespace ov {
 
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int MAXP = 32;      // max poles
 constexpr int NTHREADS = 256; // default workgroup size (4 waves)
 
@@ -798,103 +799,636 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
   if (mp_.tstamp) stamp_block(mp_.tstamp, t0, sites);
 }
 
-// ------------------------------------------------ multi-shift: persistent form
-// All iterations of one multi-shift solve in a single cooperative launch: the
-// t and r passes are separated by grid barriers instead of kernel boundaries.
-// Every spin is bounded: a barrier that does not complete within the limit
-// raises `abort` and every workgroup leaves, so the launch always drains.
-struct GridBar {
-  unsigned int count;  // arrivals in the current barrier
-  unsigned int gen;    // barrier generation
-  int abort;           // set by a workgroup whose wait timed out
-  int pad;
+// ------------------------------------------------ multi-shift: resident form
+// Every iteration of a multi-shift solve in one launch, for lattices whose r_n and t_n fit
+// the chip's registers: one workgroup per CU owns a block of bx by bz bt sites of one
+// entry; its compute waves keep r and t of their sites in registers (K sites per thread)
+// and the field the stencil reads in LDS, one more wave (the service wave) handles the
+// exchange with the other workgroups and the CG scalars.  Per pass
+//   1. the compute waves publish the field: their sites to LDS, and the projected half
+//      spinors (1 -+ g_mu) psi (two of four components: the hop needs no more) of the
+//      block's faces to the neighbouring workgroups by device-scope (sc1) stores;
+//   2. while these travel they apply the hops inside the block out of LDS, then read the
+//      neighbours' faces (device-scope loads) once their words say that they are out;
+//      meanwhile the service wave sends the block's partial norm and collects everybody's:
+//      words that carry the pass's epoch, so one exchange is the reduction and the barrier;
+//   3. with the sum they update t or r, while the service wave advances the recurrences.
+// Nothing else crosses workgroups, so no cache is written back or invalidated, and t_n goes
+// to the basis with streaming stores that nothing waits for.  Bound by latency: of the
+// 9100 cycles of an FP64 pass at 16^4 (one source, 128 workgroups of 512 sites, 3.9 us; 10 us
+// plus the launch gap per pass kernel) 2400 update and publish, 2600 are hops out of LDS,
+// and 3800 wait for faces and the sum; 8^4 takes 2.4 us (4.5 us), 4^4, one workgroup and no
+// exchange, 1.5 us (3.3 us).
+struct ResRun {          // consecutive entries on one lattice
+  int e0, ne;            // table entries
+  int wg0;               // first workgroup of the launch
+  int G;                 // workgroups per entry
+  int b[4], nb[4];       // block extents, blocks per axis
+  int FT;                // complex values of one workgroup's faces (one field)
+  long long face0;       // first byte of this run's faces
+};
+constexpr int RES_RUNS = 8;
+constexpr int RES_WGS = 256;      // workgroups of a launch at most
+// Compute waves of a workgroup at most: with the service wave four per SIMD, 128 registers
+// each (FP64 one site per thread, FP32 two).  The same block on half the waves with twice
+// the sites each takes a fifth longer (12^4, 216 sites: 2.84 -> 3.41 us per pass).
+constexpr int RES_WAVES = 15;
+constexpr int RES_THREADS = 64 * (RES_WAVES + 1);
+// Device words of the exchange, zero at first: epochs only grow, so nothing is cleared
+// between launches.
+struct ResShared {
+  unsigned epoch, abort;                    // epoch base of the next launch; a wait ran out
+  unsigned pad[62];
+  // per workgroup one 64-byte line each: words of one line written by several workgroups
+  // cost the exchange a quarter more (128 workgroups: 2.37 us, 1.73 us apart)
+  struct {
+    u32x4 word, pad[3];
+  } part[2][RES_WGS];                       // tagged partial sums by the epoch's parity
+  unsigned face[RES_WGS][16];               // [0]: epoch the workgroup's faces are out for
+};
+struct ResArgs {
+  int nrun, L;                     // runs; iterations at most
+  unsigned eoff;                   // epoch offset of this launch
+  ResShared* sh;
+  int* abort_host;                 // pinned host word, set with sh->abort
+  char* face;
+  long long spin;                  // wall-clock ticks a wait may take
+  ResRun run[RES_RUNS];
+};
+// What k_ms_coef, which follows every resident multi-shift, does to the epochs.
+struct ResEpoch {
+  ResShared* sh = nullptr;         // null: no resident launch
+  unsigned bump = 0;               // epochs the launches used
 };
 
-constexpr long long kSpinLimit = 1LL << 20;
+constexpr unsigned RES_OOB = 0x80000000u;  // beyond every buffer: loads 0, stores nothing
+constexpr int RES_SC1 = 16;                // device-scope cache policy of a buffer access
+constexpr int RES_VOLATILE = (int)0x80000000;
 
-// Grid barrier.  Each wave first waits for its own stores to complete, the
-// workgroup meets, then one thread per workgroup publishes the workgroup's
-// writes device-wide (agent-scope release: L2 write-back), arrives with a
-// relaxed atomic, polls the generation with relaxed atomic loads (no cache
-// invalidation per poll) and finally acquires once (agent-scope invalidate).
-__device__ __forceinline__ bool grid_sync(GridBar* gb, unsigned int nblocks) {
-  __shared__ int sh_ok;
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+template <class R>
+struct Half {
+  c2<R> a, b;
+};
+
+// Two components of a face site at byte offset o: FP64 one 16-byte access per component
+// (components Fb bytes apart), FP32 both in one access.
+__device__ __forceinline__ Half<double> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
+                                                double) {
+  const u32x4 p = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, RES_SC1);
+  const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, o + Fb, 0, RES_SC1);
+  return Half<double>{__builtin_bit_cast(double2, p), __builtin_bit_cast(double2, q)};
+}
+__device__ __forceinline__ Half<float> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned,
+                                               float) {
+  return __builtin_bit_cast(Half<float>, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, RES_SC1));
+}
+__device__ __forceinline__ void face_st(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
+                                        const Half<double>& h) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.a), rs, o, 0, RES_SC1);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.b), rs, o + Fb, 0,
+                                         RES_SC1);
+}
+__device__ __forceinline__ void face_st(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned,
+                                        const Half<float>& h) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), rs, o, 0, RES_SC1);
+}
+
+// Sum over the wave in lane 63, on the vector ALU alone (a shuffle tree through LDS takes
+// three times as long, on the critical path of every pass): rows of 16 by row_shr 1, 2, 4,
+// 8, then row_bcast 15 and 31.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_term(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v += dpp_term<0x111, 0xf>(v);
+  v += dpp_term<0x112, 0xf>(v);
+  v += dpp_term<0x114, 0xf>(v);
+  v += dpp_term<0x118, 0xf>(v);
+  v += dpp_term<0x142, 0xa>(v);
+  v += dpp_term<0x143, 0xc>(v);
+  return v;
+}
+
+// Upper two components of (1 + s g_mu) psi: s = -1 the hop from x + mu, s = 1 from x - mu.
+// With g_mu = [[0, B], [B^dag, 0]] they are u + s B l, and the lower two s B^dag of them.
+template <class R, int MU>
+__device__ __forceinline__ Half<R> hop_project(const c2<R> v[4], R s) {
+  using C = c2<R>;
+  C p, q;  // B l
+  if (MU == 0) { p = cmul_i(v[3]); q = cmul_i(v[2]); }
+  if (MU == 1) { p = v[3]; q = C{-v[2].x, -v[2].y}; }
+  if (MU == 2) { p = cmul_i(v[2]); q = C{v[3].y, -v[3].x}; }
+  if (MU == 3) { p = v[2]; q = v[3]; }
+  return Half<R>{C{v[0].x + s * p.x, v[0].y + s * p.y}, C{v[1].x + s * q.x, v[1].y + s * q.y}};
+}
+
+// acc += f (h, s B^dag h), with fs = f s.
+template <class R, int MU>
+__device__ __forceinline__ void hop_add(const Half<R>& h, R f, R fs, c2<R> acc[4]) {
+  using C = c2<R>;
+  C p, q;  // B^dag h
+  if (MU == 0) { p = C{h.b.y, -h.b.x}; q = C{h.a.y, -h.a.x}; }
+  if (MU == 1) { p = C{-h.b.x, -h.b.y}; q = h.a; }
+  if (MU == 2) { p = C{h.a.y, -h.a.x}; q = cmul_i(h.b); }
+  if (MU == 3) { p = h.a; q = h.b; }
+  acc[0] = C{acc[0].x + f * h.a.x, acc[0].y + f * h.a.y};
+  acc[1] = C{acc[1].x + f * h.b.x, acc[1].y + f * h.b.y};
+  acc[2] = C{acc[2].x + fs * p.x, acc[2].y + fs * p.y};
+  acc[3] = C{acc[3].x + fs * q.x, acc[3].y + fs * q.y};
+}
+
+// One site of a block as its thread sees it, set up once.  An axis that is cut (split over
+// workgroups) has at least two sites in the block, so a site lies on at most one of the two
+// faces: one half spinor per axis goes out and one comes in.
+struct ResSite {
+  int j, gi;        // index in the block and on the lattice
+  unsigned fl;      // bits 2 mu, 2 mu + 1: the hop from above / below comes from another
+                    // workgroup; 8, 9: the time hop above / below takes the phase -1
+  unsigned nb[4];   // LDS indices of the neighbours: above | below << 16
+  unsigned st[4];   // byte offset of the half spinor the site sends, RES_OOB for none
+  unsigned ld[4];   // byte offset of the one it receives
+};
+
+// Site index jj (of the block's S = prod b, or beyond: a thread without a site gets the last
+// one's fields and no faces) of workgroup w of its entry.
+template <class R>
+__host__ __device__ inline ResSite res_site(const ResRun& U, const Geo& g, int w, int jj) {
+  const int S = U.b[0] * U.b[1] * U.b[2] * U.b[3];
+  const bool have = jj < S;
+  const int j = have ? jj : S - 1;
+  int c[4], wc[4], q = j, r = w;
+  for (int mu = 0; mu < 4; ++mu) {
+    c[mu] = q % U.b[mu];
+    q /= U.b[mu];
+    wc[mu] = r % U.nb[mu];
+    r /= U.nb[mu];
+  }
+  ResSite s;
+  s.j = jj;
+  s.gi = wc[0] * U.b[0] + c[0] +
+         g.X * (wc[1] * U.b[1] + c[1] +
+                g.Y * (wc[2] * U.b[2] + c[2] + g.Z * (wc[3] * U.b[3] + c[3])));
+  s.fl = 0;
+  int ss = 1, ws = 1;  // strides of the axis in the block and among the workgroups
+  unsigned o = 0;      // first face value of the axis
+  for (int mu = 0; mu < 4; ++mu) {
+    const int b = U.b[mu], n = U.nb[mu];
+    const bool top = c[mu] == b - 1, bot = c[mu] == 0, cut = n > 1;
+    const unsigned F = (unsigned)(S / b);
+    s.nb[mu] = (unsigned)(top ? j - ss * (b - 1) : j + ss) |
+               (unsigned)(bot ? j + ss * (b - 1) : j - ss) << 16;
+    s.st[mu] = s.ld[mu] = RES_OOB;
+    if (cut && top) s.fl |= 1u << 2 * mu;
+    if (cut && bot) s.fl |= 2u << 2 * mu;
+    if (cut && have && (top || bot)) {
+      const unsigned f = (unsigned)(j % ss + ss * (j / (ss * b)));  // site of the face
+      // own face: the lower one, or 2 F values on, the upper; the neighbour's is the other
+      const int wn = top ? w + (wc[mu] + 1 < n ? ws : ws - n * ws)
+                         : w - (wc[mu] > 0 ? ws : ws - n * ws);
+      const unsigned own = (unsigned)(w * U.FT) + o + (top ? 2 * F : 0u);
+      const unsigned oth = (unsigned)(wn * U.FT) + o + (top ? 0u : 2 * F);
+      const unsigned e = sizeof(R) == sizeof(double) ? f : 2 * f;  // FP32: interleaved
+      s.st[mu] = (own + e) * (unsigned)sizeof(c2<R>);
+      s.ld[mu] = (oth + e) * (unsigned)sizeof(c2<R>);
+    }
+    if (mu == 3 && g.bc < 0) {
+      if (top && wc[3] == n - 1) s.fl |= 256u;
+      if (bot && wc[3] == 0) s.fl |= 512u;
+    }
+    if (cut) o += 4 * F;
+    ss *= b;
+    ws *= n;
+  }
+  return s;
+}
+
+template <class R>
+struct ResHalo {
+  Half<R> h[4];     // per axis (0 where nothing is received)
+};
+
+// The field's uniform data of a compute wave.
+template <class R>
+struct ResBlock {
+  int S;                     // sites of the block
+  unsigned Fb[4];            // bytes between the two components of a face site (FP64)
+  c2<R>* sh;                 // LDS, [4][S]
+  __amdgpu_buffer_rsrc_t rs;
+
+  // Keeps what follows from a value (addresses of eight neighbours per site) from being
+  // hoisted out of the iteration loop, where it would spill.
+  __device__ __forceinline__ static unsigned opaque(unsigned c) {
+    asm volatile("" : "+v"(c));
+    return c;
+  }
+  // the forward hop of the block below, (1 - g) psi, or the backward hop of the one above
+  template <int MU>
+  __device__ __forceinline__ void put(const c2<R> v[4], const ResSite& s, unsigned fl,
+                                      unsigned fld) const {
+    face_st(rs, opaque(s.st[MU]) + fld, Fb[MU], hop_project<R, MU>(v, fl & (1u << 2 * MU) ? R(1) : R(-1)));
+  }
+  // The site holds v: to the faces and to LDS.
+  __device__ __forceinline__ void publish(const c2<R> v[4], const ResSite& s, unsigned fld) const {
+    const unsigned fl = opaque(s.fl);
+    put<0>(v, s, fl, fld);
+    put<1>(v, s, fl, fld);
+    put<2>(v, s, fl, fld);
+    put<3>(v, s, fl, fld);
+    if (s.j < S) {
+      const int j = (int)opaque((unsigned)s.j);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sh[q * S + j] = v[q];
+    }
+  }
+  __device__ __forceinline__ void halo(ResHalo<R>& h, const ResSite& s, unsigned fld) const {
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) h.h[mu] = face_ld(rs, opaque(s.ld[mu]) + fld, Fb[mu], R());
+  }
+
+  // hops of an axis from inside the block (0 where the neighbour is another workgroup's)
+  template <int MU>
+  __device__ __forceinline__ void hop_in(unsigned nb, unsigned fl, c2<R> acc[4]) const {
+    const unsigned jf = nb & 0xffffu, jb = nb >> 16;
+    R ff = R(1), fb = R(1);
+    if (MU == 3) {
+      ff = fl & 256u ? R(-1) : R(1);
+      fb = fl & 512u ? R(-1) : R(1);
+    }
+    ff = fl & (1u << 2 * MU) ? R(0) : ff;
+    fb = fl & (2u << 2 * MU) ? R(0) : fb;
+    c2<R> n[4], m[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) n[q] = sh[q * S + jf];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = sh[q * S + jb];
+    hop_add<R, MU>(hop_project<R, MU>(n, R(-1)), ff, -ff, acc);
+    hop_add<R, MU>(hop_project<R, MU>(m, R(1)), fb, fb, acc);
+  }
+  // acc = sum of the hops from inside the block (the field in LDS)
+  __device__ __forceinline__ void inside(const ResSite& s, c2<R> acc[4]) const {
+    const unsigned fl = opaque(s.fl);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = c2<R>{R(0), R(0)};
+    // two axes at a time: more LDS reads in flight would spill
+    hop_in<0>(opaque(s.nb[0]), fl, acc);
+    hop_in<1>(opaque(s.nb[1]), fl, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    hop_in<2>(opaque(s.nb[2]), fl, acc);
+    hop_in<3>(opaque(s.nb[3]), fl, acc);
+    // computed here, before the barrier that follows: the compiler would sink the
+    // arithmetic to its use behind it and keep every LDS operand alive
+#pragma unroll
+    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(acc[q].x), "+v"(acc[q].y));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  template <int MU>
+  __device__ __forceinline__ void hop_out(const ResHalo<R>& h, unsigned fl, c2<R> acc[4]) const {
+    R f = R(1);
+    const bool top = fl & (1u << 2 * MU);
+    if (MU == 3) f = fl & (top ? 256u : 512u) ? R(-1) : R(1);
+    hop_add<R, MU>(h.h[MU], f, top ? -f : f, acc);
+  }
+  // acc += the hops from other workgroups' sites
+  __device__ __forceinline__ void outside(const ResHalo<R>& h, const ResSite& s,
+                                          c2<R> acc[4]) const {
+    const unsigned fl = opaque(s.fl);
+    hop_out<0>(h, fl, acc);
+    hop_out<1>(h, fl, acc);
+    hop_out<2>(h, fl, acc);
+    hop_out<3>(h, fl, acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(acc[q].x), "+v"(acc[q].y));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // out = H_W f at a site: g5 (diag v - 1/2 sum of the hops), v its own value.
+  __device__ __forceinline__ static void finish(R diag, const c2<R> v[4], const c2<R> acc[4],
+                                                c2<R> out[4]) {
+    const R hh = R(0.5);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const c2<R> d = c2<R>{diag * v[q].x - hh * acc[q].x, diag * v[q].y - hh * acc[q].y};
+      out[q] = q < 2 ? c2<R>{-d.x, -d.y} : d;
+    }
+  }
+};
+
+// What the service wave and the compute waves tell each other.
+struct ResLds {
+  double red[RES_WAVES];  // wave sums of the field just published
+  double total;           // the entry's sum
+  int stop;               // leave after the field is out (converged, broke down)
+  int gone;               // a wait ran out
+  unsigned drained;       // compute waves whose faces have arrived, over all passes
+  unsigned faces;         // epoch the neighbours' faces are out for
+};
+
+// The service wave's exchange: send the workgroup's partial s and wait for the G partials
+// of the entry; their sum (lane 63) in a fixed order, the same bits in every workgroup.
+// Each half of a 16-byte word carries the epoch, so that it need not arrive whole.
+// Partials alternate between two slots: a workgroup writes epoch e + 2 only after every
+// workgroup has sent e + 1, that is, has read e.  On the way it tells the compute waves
+// when the neighbours' faces are out (facew: this lane's face word, null for none); a face
+// word may already hold a later epoch: its writer went on, and the faces alternate between
+// t and r.  The wait is bounded: when `spin` ticks pass, or another workgroup has given up,
+// the abort words are raised, false is returned and every workgroup leaves.
+__device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int slot0, int w, int G,
+                                             unsigned epoch, double s, const unsigned* facew,
+                                             double* total) {
+  const int lane = threadIdx.x & 63;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      A.sh->part[epoch & 1] + slot0, 0, G * (int)sizeof(A.sh->part[0][0]), 0x00020000);
+  if (lane == 0) {
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(s);
+    const u32x4 x = {(unsigned)bits, epoch, (unsigned)(bits >> 32), epoch};
+    __builtin_amdgcn_raw_buffer_store_b128(x, rs, w * 64, 0, RES_SC1);
+  }
+  long long t0 = 0;
+  bool faces = false;
+  for (int n = 0;; ++n) {
+    bool ready = true, fready = true;
+    unsigned f = epoch;
+    if (facew && !faces)
+      f = __hip_atomic_load(facew, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    double p = 0.0;
+    for (int j = lane; j < G; j += 64) {
+      const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, j * 64, 0, RES_SC1 | RES_VOLATILE);
+      ready &= x.y == epoch && x.w == epoch;
+      p += __longlong_as_double((long long)(((unsigned long long)x.z << 32) | x.x));
+    }
+    if (!faces) {
+      fready = (int)(f - epoch) >= 0;
+      if (__all(fready)) {
+        faces = true;
+        if (lane == 0)
+          __hip_atomic_store(&X.faces, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    if (faces && __all(ready)) {
+      *total = wave_sum_last(p);
+      return true;
+    }
+    if ((n & 15) == 0) {
+      const long long now = (long long)wall_clock64();
+      if (n == 0) t0 = now;
+      if (now - t0 >= A.spin ||
+          __hip_atomic_load(&A.sh->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        if (lane == 0) {
+          __hip_atomic_store(&A.sh->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(A.abort_host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          X.gone = 1;
+          __hip_atomic_store(&X.faces, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        return false;
+      }
+    }
+  }
+}
+
+template <class R, int K>
+__global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict__ tab,
+                                                        const ResArgs A, const MsParams mp) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  __shared__ ResLds X;
+  int ir = 0;
+  for (int k = 1; k < A.nrun; ++k)
+    if (A.run[k].wg0 <= (int)blockIdx.x) ir = k;
+  const ResRun& U = A.run[ir];
+  const int lw = (int)blockIdx.x - U.wg0;
+  const int G = U.G;
+  const SysDev& S = tab[U.e0 + lw / G];
+  const int w = lw % G;
+  const int slot0 = (int)blockIdx.x - w;
+  if (S.active && *S.active == 0) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nwc = (int)(blockDim.x >> 6) - 1;  // compute waves; the last wave serves
   if (threadIdx.x == 0) {
-    int ok = 1;
-    const unsigned int g0 = __hip_atomic_load(&gb->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    const unsigned int arrived =
-        __hip_atomic_fetch_add(&gb->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (arrived == nblocks - 1) {
-      __hip_atomic_store(&gb->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      __hip_atomic_fetch_add(&gb->gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      long long spins = 0;
-      while (__hip_atomic_load(&gb->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g0) {
-        __builtin_amdgcn_s_sleep(1);
-        if (++spins > kSpinLimit ||
-            __hip_atomic_load(&gb->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-          ok = 0;
-          break;
+    X.stop = X.gone = 0;
+    X.drained = X.faces = 0;
+  }
+  unsigned ep = A.sh->epoch + A.eoff;
+
+  if (wave == nwc) {
+    // ---------------------------------------------------------- service wave
+    // face word this lane watches: neighbour lane (axis lane / 2, side lane % 2)
+    const unsigned* face_nbr = nullptr;
+    if (lane < 8) {
+      const int mu = lane >> 1;
+      int ws = 1;
+      for (int m = 0; m < mu; ++m) ws *= U.nb[m];
+      const int n = U.nb[mu], c = (w / ws) % n;
+      const int nw = lane & 1 ? w + (c + 1 < n ? ws : ws - n * ws)
+                              : w - (c > 0 ? ws : ws - n * ws);
+      if (n > 1) face_nbr = A.sh->face[slot0 + nw];
+    }
+    const int np = mp.np;
+    const double sigma = lane < np ? mp.sigma[lane] : 0.0;
+    const bool keep = w == 0;  // records the history
+    double* const h_zeta = S.h_zeta;
+    double* const h_rho = S.h_rho;
+    double* const h_alpha = S.h_alpha;
+    unsigned* const h_active = S.h_active;
+    // scalar history of lane = shift, as in the per-pass kernels
+    double zk1 = 1.0, zk2 = 1.0, a1 = 1.0, a2 = 1.0, rho_m1 = 1.0, rho_m2 = 1.0, thr = 0.0;
+    unsigned act_prev = 0xffffffffu;
+    int n_stop = 0, status = 0, done = 0;
+    auto exchange = [&](double* tot) -> bool {
+      double s = 0.0;
+      for (int k = 0; k < nwc; ++k) s += X.red[k];
+      ++ep;
+      bool ok = true;
+      if (G > 1)
+        ok = res_exchange(A, X, slot0, w, G, ep, s, face_nbr, &s);
+      if (lane == 63) X.total = s;
+      *tot = __longlong_as_double(
+          ((long long)__builtin_amdgcn_readlane((int)(__double_as_longlong(s) >> 32), 63) << 32) |
+          (unsigned)__builtin_amdgcn_readlane((int)__double_as_longlong(s), 63));
+      return ok;
+    };
+    bool ok = true;
+    for (int n = 0; n < A.L; ++n) {
+      __syncthreads();  // r_n is out
+      if (done) break;  // the previous r pass broke down
+      double rho, gam;
+      ok = exchange(&rho);
+      __syncthreads();  // total is in
+      if (!ok) break;
+      const double srho = sqrt(rho);
+      if (n == 0) thr = mp.tol * srho;
+      bool act = false;
+      double zn = 1.0;
+      if (n == 0) {
+        act = lane < np && srho > thr;
+      } else if (lane < np) {
+        zn = zk1;
+        if (act_prev & (1u << lane)) {
+          const double b2 = n >= 2 ? rho_m1 / rho_m2 : 0.0;
+          const double den = a2 * zk2 * (1.0 + a1 * sigma) + a1 * b2 * (zk2 - zk1);
+          zn = zk1 * zk2 * a2 / den;
+          act = fabs(zn) * srho > thr;
         }
       }
-      if (!ok) __hip_atomic_store(&gb->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned amask = (unsigned)__ballot(act);
+      if (n > 0 && (!(rho >= 0.0) || !isfinite(rho))) status = 1;
+      bool stop = amask == 0 || status != 0;
+      if (!stop && n >= mp.cap) {
+        stop = true;
+        status = 2;
+      }
+      if (keep) {
+        if (lane < np) h_zeta[(size_t)n * MAXP + lane] = zn;
+        if (lane == 0) {
+          h_rho[n] = rho;
+          h_active[n] = amask;
+        }
+      }
+      if (stop) {
+        n_stop = n;
+        done = n + 1;
+        if (lane == 0) X.stop = 1;
+      }
+      __syncthreads();  // t_n is out
+      if (stop) break;
+      ok = exchange(&gam);
+      __syncthreads();  // total is in
+      if (!ok) break;
+      const double alpha = rho / gam;
+      if (keep && lane == 0) h_alpha[n] = alpha;
+      if (!(gam > 0.0) || !isfinite(alpha)) {
+        status = 1;
+        n_stop = n;
+        done = n + 1;
+        if (lane == 0) X.stop = 1;
+      }
+      zk2 = zk1;
+      zk1 = zn;
+      a2 = a1;
+      a1 = alpha;
+      rho_m2 = rho_m1;
+      rho_m1 = rho;
+      act_prev = amask;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    sh_ok = ok;
-  }
-  __syncthreads();
-  return sh_ok != 0;
-}
-
-// True when every participating system finished at an iteration <= n.  A
-// system that finishes at n' writes n' + 1 in one word, so a workgroup that
-// runs ahead into iteration n + 1 can never change this answer for iteration n.
-__device__ __forceinline__ bool all_done(const SysDev* __restrict__ sys, int nsys, int n) {
-  for (int s = 0; s < nsys; ++s) {
-    const SysDev& S = sys[s];
-    if (S.active && *S.active == 0) continue;
-    const int d = __hip_atomic_load(&S.h_ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (d == 0 || d - 1 > n) return false;
-  }
-  return true;
-}
-
-// Launch with exactly `grid` co-resident workgroups (cooperative launch).
-// Workgroup b handles logical blocks j, j + grid, ... with j its XCD-contiguous
-// index.  Every workgroup runs the same barriers and leaves at the same
-// iteration (after L iterations, or once all_done holds after a barrier).
-template <class R>
-__global__ void __launch_bounds__(256) k_ms_persistent(const SysDev* __restrict__ sys, int nsys,
-                                                       const int* __restrict__ bmap, int nb_total,
-                                                       int L, const MsParams mp_, GridBar* gb) {
-  __shared__ double lds[17];
-  const int grid = gridDim.x;
-  const int j0 = xcd_logical_block(grid);
-  for (int n = 0; n < L; ++n) {
-    for (int Lb = j0; Lb < nb_total; Lb += grid) {
-      const SysDev& S = sys[bmap[Lb]];
-      ms_t_block<R, 0, false>(S, Lb - S.blk0, n, &mp_, lds, (c2<R>*)nullptr);
-      __syncthreads();
+    if (keep && lane == 0 && ok) {
+      if (done) {
+        S.h_ctl[1] = n_stop;
+        S.h_ctl[2] = status;
+      }
+      S.h_ctl[0] = done;  // 0: not finished within L
     }
-    if (!grid_sync(gb, grid)) return;
-    for (int Lb = j0; Lb < nb_total; Lb += grid) {
-      const SysDev& S = sys[bmap[Lb]];
-      ms_r_block<R, 0, false>(S, Lb - S.blk0, n, &mp_, lds, (c2<R>*)nullptr);
-      __syncthreads();
-    }
-    if (!grid_sync(gb, grid)) return;
-    if (all_done(sys, nsys, n)) return;
+    return;
   }
-}
 
-__global__ void k_bar_reset(GridBar* gb) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    gb->count = 0;
-    gb->abort = 0;
+  // ------------------------------------------------------------ compute waves
+  const Geo g = S.g;
+  ResBlock<R> B;
+  B.S = U.b[0] * U.b[1] * U.b[2] * U.b[3];
+  B.sh = (c2<R>*)dyn_lds;
+  const unsigned fb = (unsigned)(G * U.FT * sizeof(c2<R>));  // bytes of one field's faces
+  B.rs = __builtin_amdgcn_make_buffer_rsrc(A.face + U.face0 + (size_t)(lw / G) * 2 * fb, 0,
+                                           (int)(2 * fb), 0x00020000);
+  const R diag = (R)mp.diag;
+  ResSite site[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) site[k] = res_site<R>(U, g, w, (int)threadIdx.x + k * 64 * nwc);
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu)
+    B.Fb[mu] = (unsigned)(B.S / U.b[mu]) * (unsigned)sizeof(c2<R>);
+  unsigned* const face_own = &A.sh->face[slot0 + w][0];
+  unsigned sent = 0;  // fields sent, times the compute waves
+  c2<R>* basis = (c2<R>*)S.basis;
+  const size_t slot = (size_t)4 * g.V;
+
+  c2<R> r[K][4], t[K][4], hops[K][4];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    load_sp<R>((const c2<R>*)S.src, g.V, site[k].gi, r[k]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[k][q] = c2<R>{R(0), R(0)};
+  }
+  // The field v of the next pass goes out, its hops inside the block follow; false: leave.
+  auto send = [&](c2<R>(&v)[K][4], unsigned fo) -> bool {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      B.publish(v[k], site[k], fo);
+      acc += site[k].j < B.S ? norm2_sp(v[k]) : 0.0;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    acc = wave_sum_last(acc);
+    if (lane == 63) X.red[wave] = acc;
+    ++ep;
+    __syncthreads();
+    return X.stop == 0;
+  };
+  // hops = sum of the hops of the field just sent, its faces in the half at fo
+  auto gather = [&](unsigned fo) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) B.inside(site[k], hops[k]);
+    if (G == 1) return;
+    // the service wave says when; it also ends the wait when it gives up
+    while (__hip_atomic_load(&X.faces, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != ep)
+      __builtin_amdgcn_s_sleep(1);
+    ResHalo<R> h[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) B.halo(h[k], site[k], fo);
+#pragma unroll
+    for (int k = 0; k < K; ++k) B.outside(h[k], site[k], hops[k]);
+  };
+  // this wave's faces have arrived; the last wave's word tells the neighbours
+  auto faces_out = [&]() {
+    sent += nwc;
+    if (G == 1) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0 && __hip_atomic_fetch_add(&X.drained, 1u, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WORKGROUP) + 1 == sent)
+      __hip_atomic_store(face_own, ep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  double rho_m1 = 1.0;
+  bool on = send(r, 0);
+  for (int n = 0; n < A.L && on; ++n) {
+    // ---- t pass: t_n = H r_n + beta_{n-1} t_{n-1}
+    faces_out();
+    gather(0);
+    __syncthreads();
+    const double rho = X.total;
+    if (X.gone) return;
+    const R beta = (R)(n > 0 ? rho / rho_m1 : 0.0);
+    rho_m1 = rho;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      c2<R> o[4];
+      B.finish(diag, r[k], hops[k], o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        t[k][q] = c2<R>{o[q].x + beta * t[k][q].x, o[q].y + beta * t[k][q].y};
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!send(t, fb)) return;  // converged at n
+    // ---- r pass: alpha_n = rho_n / |t_n|^2, r_{n+1} = r_n - alpha_n H t_n
+    faces_out();
+    c2<R>* tn = basis + (size_t)n * slot;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (site[k].j < B.S)
+        store_sp_nt<R>(tn, g.V, (int)B.opaque((unsigned)site[k].gi), t[k]);
+    gather(fb);
+    __syncthreads();
+    const R alpha = (R)(rho / X.total);
+    if (X.gone) return;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      c2<R> o[4];
+      B.finish(diag, t[k], hops[k], o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        r[k][q] = c2<R>{r[k][q].x - alpha * o[q].x, r[k][q].y - alpha * o[q].y};
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (n + 1 < A.L) on = send(r, 0);
   }
 }
 
@@ -996,10 +1530,23 @@ __device__ __forceinline__ void coef_second(const SysDev& S, const MsParams* mp,
 }
 
 __global__ void __launch_bounds__(256) k_ms_coef(const SysDev* __restrict__ sys, int nsys,
-                                                 int launched, const MsParams mp_) {
+                                                 int launched, const MsParams mp_,
+                                                 const ResEpoch re) {
   __shared__ CoefLds L;
   const int s = blockIdx.x;
   if (s >= nsys) return;
+  if (s == 0 && re.sh) {  // the next resident launch's epochs
+    const unsigned e = re.sh->epoch;
+    __syncthreads();
+    if (e > 0x70000000u) {  // start over: no word may hold an epoch that returns
+      unsigned* q = (unsigned*)re.sh->part;
+      constexpr int n = (sizeof(ResShared) - offsetof(ResShared, part)) / sizeof(unsigned);
+      for (int k = threadIdx.x; k < n; k += blockDim.x) q[k] = 0u;
+      if (threadIdx.x == 0) re.sh->epoch = 0u;
+    } else if (threadIdx.x == 0) {
+      re.sh->epoch = e + re.bump;
+    }
+  }
   const SysDev& S = sys[s];
   if (S.active && *S.active == 0) return;
   const MsParams* mp = &mp_;

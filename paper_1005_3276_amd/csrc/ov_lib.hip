@@ -33,9 +33,17 @@ struct ov_ctx {
   bool use_graphs = false;
   bool fft_fixed = true;          // fixed-length transforms for z = P r (OV_FFT_FIXED=0 at
                                   // context creation: the generic passes)
-  int persistent = 0;            // cooperative persistent multi-shift kernel (0: per-pass kernels)
+  // resident multi-shift kernel (k_ms_res): see ResGeom
+  int res_cus = 0;               // compute units: workgroups of a resident launch
+  bool resident = true;          // OV_PERSISTENT=0 at context creation: per-pass kernels only
+  ResGeom rg[2];                 // block decomposition of this lattice, FP64 / FP32
+  ResShared* res_sh = nullptr;   // device words of the exchange
+  int* res_abort = nullptr;      // pinned: raised by a resident launch whose wait ran out
+  long long res_spin = 0;        // wall-clock ticks a resident wait may take
+  int res_aborts = 0;
+  hipEvent_t ev_res = nullptr;   // marks this context's work for another context's launch
+  bool capturing = false;        // inside a graph capture of the private stream
   std::map<long long, int> n_est;  // (precision, tolerance) -> iterations the last multi-shift needed
-  int coop_cap[2] = {0, 0};      // co-resident workgroups of k_ms_persistent<double/float>
   int device = 0;
   std::string err;
   double a[MAXP], b[MAXP], delta = 0;
@@ -366,6 +374,19 @@ int pick_xc(int X, int T) {
   return best;
 }
 
+// The resident launches of one multi-shift solve over a table: entries in order, as many per
+// launch as there are CUs for.
+struct ResLaunch {
+  ResRun run[RES_RUNS];
+  int nrun = 0, grid = 0, threads = 64, K = 1;
+  size_t lds = 0;
+};
+struct ResPlan {
+  std::vector<ResLaunch> launches;
+  size_t face_bytes = 0;  // the largest launch's faces
+  bool use = false;
+};
+
 // Lattices the momentum-space kernels handle (LDS tiles of <= 1024 complex values).
 // A batch of systems sharing poles, tolerances and precision.
 struct Engine {
@@ -382,7 +403,6 @@ struct Engine {
   int* bmap = nullptr;              // device: logical workgroup -> system
   std::vector<int> hbmap;
   std::vector<void*> hptrs;         // host staging of ptrs (outlives the async copy)
-  GridBar* gbar = nullptr;          // device: grid barrier of the persistent kernel
   double* cg_all = nullptr;         // device: nsys * CG_NSLOT scalars (one copy to the host)
   long long* stat_all = nullptr;    // device: 3 nsys * 4 multi-shift counters (entries A, B, B')
   double* dstat_all = nullptr;      // device: 3 nsys * 2 shift residuals
@@ -410,9 +430,96 @@ struct Engine {
   SysDev* trgwtab = nullptr;        // device: 2 nsys entries of the FP64 true residual (same map)
   std::vector<SysDev> htrgw;        // host copy
 
+  ResPlan res[2][2];                // resident launches: [FP64, FP32][copies of the systems - 1]
+  bool no_res = false;              // per-pass kernels only (tuning, a tight workspace)
+  char* face = nullptr;             // device: faces of the largest resident launch
+
+  template <class R>
+  const ResPlan* resident(int copies) const {
+    const ResPlan& p = res[sizeof(R) == sizeof(float)][copies - 1];
+    return p.use ? &p : nullptr;
+  }
+  bool resident_any() const {
+    return res[0][0].use || res[0][1].use || res[1][0].use || res[1][1].use;
+  }
+
+  // Resident launches for `copies` entries per system in a precision, and whether they beat
+  // the per-pass kernels: those cost two launches and three field passes per iteration at
+  // about 7 us + bytes / 4.6 TB/s each (16^4, two FP64 sources: 12.5 us), a resident pass
+  // what res_geom models for it, once per launch.
+  void plan_resident(int fp32, int copies) {
+    ResPlan& P = res[fp32][copies - 1];
+    P = ResPlan{};
+    if (no_res || !lead->resident) return;
+    const int esize = fp32 ? 8 : 16;
+    double t_res = 0.0, t_pass = 7.0;
+    double us = 0.0;  // slowest block of the open launch
+    size_t faces = 0;
+    auto close = [&]() {
+      t_res += us;
+      us = 0.0;
+      P.face_bytes = std::max(P.face_bytes, faces);
+      faces = 0;
+    };
+    for (int e = 0; e < copies * nsys; ++e) {
+      const ov_ctx* c = ctxs[e % nsys];
+      const ResGeom& q = c->rg[fp32];
+      if (q.G == 0) return;
+      t_pass += 12.0 * esize * q.S * q.G / 4.6e6;
+      const size_t fb = (size_t)2 * q.G * q.FT * esize;
+      ResLaunch* l = P.launches.empty() ? nullptr : &P.launches.back();
+      const ov_ctx* prev = e > 0 ? ctxs[(e - 1) % nsys] : nullptr;
+      const bool same = l && std::equal(c->p.dims, c->p.dims + 4, prev->p.dims);
+      if (!l || l->grid + q.G > lead->res_cus || (!same && l->nrun == RES_RUNS)) {
+        close();
+        P.launches.emplace_back();
+        l = &P.launches.back();
+      }
+      if (l->nrun > 0 && same) {
+        ++l->run[l->nrun - 1].ne;
+      } else {
+        ResRun& r = l->run[l->nrun++];
+        r.e0 = e;
+        r.ne = 1;
+        r.wg0 = l->grid;
+        r.G = q.G;
+        r.FT = q.FT;
+        std::copy(q.b, q.b + 4, r.b);
+        std::copy(q.nb, q.nb + 4, r.nb);
+        r.face0 = (long long)faces;
+      }
+      l->grid += q.G;
+      l->threads = std::max(l->threads, q.threads);
+      l->K = std::max(l->K, q.K);
+      l->lds = std::max(l->lds, (size_t)q.S * 4 * esize);
+      faces += fb;
+      us = std::max(us, q.us);
+    }
+    close();
+    P.use = t_res < t_pass;
+    if (!P.use) P = ResPlan{};
+  }
+
+  // The plans of the tables this engine runs: sign / apply and M, M^dag forms one entry per
+  // system, the Ginsparg-Wilson forms two.
+  size_t plan_residents() {
+    for (auto& row : res)
+      for (ResPlan& p : row) p = ResPlan{};
+    if (!pl.fft && pl.cap64 > 0) {
+      plan_resident(0, 1);
+      if (pl.gwx || (pl.gw && !pl.mixed)) plan_resident(0, 2);
+      if (pl.solve && pl.mixed) plan_resident(1, pl.gw ? 2 : 1);
+    }
+    size_t fb = 0;
+    for (const auto& row : res)
+      for (const ResPlan& p : row) fb = std::max(fb, p.face_bytes);
+    return fb;
+  }
+
   size_t layout(void* base, size_t cap, bool dry) {
     Bump bp(base, cap, dry);
-    gbar = (GridBar*)bp.take(sizeof(GridBar));
+    const size_t fb = plan_residents();
+    face = fb ? (char*)bp.take(fb) : nullptr;
     // the CG scalars and, right after them, the counters of entries A, B (inner) and
     // B (true residual) -- read back with one copy -- then the entries' shift residuals
     // and control words: everything from stat_all on is cleared by one fill kernel
@@ -597,6 +704,76 @@ MsParams make_mp(const ov_ctx* c, double tol, int cap) {
 }
 
 // Build the engine for `ctxs` (one entry per system) and carve the workspace.
+// Two resident launches that share the chip wait for each other's workgroups: launches of
+// one stream follow one another, and a launch on another context's stream (of this process)
+// is ordered after the work enqueued on the last one that launched.
+struct ResGate {
+  std::mutex mu;
+  ov_ctx* last = nullptr;
+};
+ResGate g_res_gate[kMaxDevices];
+
+void res_gate(ov_ctx* c) {
+  if (c->device < 0 || c->device >= kMaxDevices) return;
+  ResGate& g = g_res_gate[c->device];
+  std::lock_guard<std::mutex> lock(g.mu);
+  if (g.last && g.last != c) {
+    if (hipEventRecord(g.last->ev_res, g.last->priv) == hipSuccess)
+      (void)hipStreamWaitEvent(c->priv, g.last->ev_res, 0);
+  }
+  g.last = c;
+}
+
+template <class R>
+const void* res_kernel(int K) {
+  if constexpr (sizeof(R) == sizeof(float))  // FP64 with two sites per thread would spill
+    if (K > 1) return (const void*)k_ms_res<R, 2>;
+  return (const void*)k_ms_res<R, 1>;
+}
+
+// Set-up of the resident multi-shift kernel: the lattice's decompositions, the epoch word,
+// abort word and slots, and the wait limit (OV_RES_WAIT_US at context creation; half a
+// second is far beyond any pass and short enough for a caller that lost the race with
+// another process for the chip).
+ov_status res_setup(ov_ctx* c) {
+  const char* ep = std::getenv("OV_PERSISTENT");
+  c->resident = !(ep && *ep == '0');
+  int cus = 0, khz = 0;
+  HIPCHK(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+  HIPCHK(c, hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device));
+  c->res_cus = std::min(cus, RES_WGS);
+  const char* ew = std::getenv("OV_RES_WAIT_US");
+  const double us = ew ? std::atof(ew) : 5e5;
+  c->res_spin = (long long)(us * khz * 1e-3);
+  c->rg[0] = res_geom(c->p.dims, 16, c->res_cus, 1);
+  c->rg[1] = res_geom(c->p.dims, 8, c->res_cus, 2);
+  const void* kern[] = {res_kernel<double>(1), res_kernel<float>(1), res_kernel<float>(2)};
+  for (const void* k : kern)
+    HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RES_MAX_LDS));
+  HIPCHK(c, hipMalloc((void**)&c->res_sh, sizeof(ResShared)));
+  HIPCHK(c, hipMemsetAsync(c->res_sh, 0, sizeof(ResShared), c->priv));
+  HIPCHK(c, hipHostMalloc((void**)&c->res_abort, 64));
+  *c->res_abort = 0;
+  HIPCHK(c, hipEventCreateWithFlags(&c->ev_res, hipEventDisableTiming));
+  return OV_OK;
+}
+
+// Run a call; when a resident launch gave up waiting (another process held part of the
+// chip), run it again with the per-pass kernels.  Inputs are untouched until then.
+template <class F>
+ov_status res_retry(ov_ctx* c, F&& call) {
+  const ov_status rc = call();
+  if (!c || !c->res_abort || !*c->res_abort) return rc;
+  HIPCHK(c, hipStreamSynchronize(c->priv));
+  *c->res_abort = 0;
+  k_zero32<<<1, 64, 0, c->priv>>>(&c->res_sh->abort, 1);
+  const bool was = c->resident;
+  c->resident = false;
+  const ov_status again = call();
+  c->resident = was && ++c->res_aborts < 3;
+  return again;
+}
+
 // The plan of a call (buffers, basis capacities, multi-shift parameters) for `ctxs`
 // (one entry per system).  Host only: engine_init carves it, the workspace queries size it.
 void plan_engine(Engine& E, const std::vector<ov_ctx*>& ctxs, bool solve, bool mixed,
@@ -646,11 +823,17 @@ ov_status engine_init(Engine& E, const std::vector<ov_ctx*>& ctxs, bool solve, b
   for (int& k : E.lead->ev_call_count) k = 0;
   HIPCHK(E.lead, hipEventRecord(E.lead->ev_in, E.lead->stream));
   HIPCHK(E.lead, hipStreamWaitEvent(E.st, E.lead->ev_in, 0));
-  const size_t need = E.layout(nullptr, 0, true);
+  size_t need = E.layout(nullptr, 0, true);
+  const size_t limit = E.lead->noalloc   ? (size_t)OV_NOALLOC_SCRATCH_BYTES
+                       : E.lead->user_ws ? E.lead->user_ws_bytes
+                                         : (size_t)-1;
+  if (need > limit && E.resident_any()) {  // no room for the faces: the per-pass kernels
+    E.no_res = true;
+    need = E.layout(nullptr, 0, true);
+  }
   void* base = nullptr;
   TRY(ensure_ws(E.lead, need, &base));
   E.layout(base, need, false);
-  k_zero32<<<1, 64, 0, E.st>>>((unsigned int*)E.gbar, sizeof(GridBar) / sizeof(unsigned int));
   TRY(ensure_pinned(E.lead, E.nsys));
   return OV_OK;
 }
@@ -781,24 +964,34 @@ void collect_samples(ov_ctx* c) {
   for (int& k : c->ev_call_count) k = 0;
 }
 
-// Co-resident workgroups of k_ms_persistent<R> on this device (0: no cooperative launch).
 template <class R>
-int coop_capacity(ov_ctx* c) {
-  int& cap = c->coop_cap[sizeof(R) == sizeof(float) ? 1 : 0];
-  if (cap == 0) {
-    int coop = 0, cus = 0, per = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device) != hipSuccess ||
-        !coop ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)k_ms_persistent<R>, c->block,
-                                                     0) != hipSuccess ||
-        per < 1) {
-      cap = -1;
-    } else {
-      cap = per * cus;
-    }
+void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double bytes,
+                     const MsParams& mp, int L) {
+  ov_ctx* c = E.lead;
+  if (!c->capturing) res_gate(c);
+  const unsigned range = 2 * (unsigned)L + 4;  // epochs of one launch
+  unsigned eoff = 0;
+  int nent = 0;
+  for (const ResLaunch& l : P.launches) {
+    ResArgs a{};
+    a.nrun = l.nrun;
+    a.L = L;
+    a.eoff = eoff;
+    a.sh = c->res_sh;
+    a.abort_host = c->res_abort;
+    a.face = E.face;
+    a.spin = c->res_spin;
+    std::copy(l.run, l.run + l.nrun, a.run);
+    MsParams m = mp;
+    const SysDev* Tp = T;
+    void* args[] = {(void*)&Tp, (void*)&a, (void*)&m};
+    // written per iteration: t_n of the launch's entries
+    Sample smp(c, 2, bytes / 3.0 / P.launches.size(), E.sb[0].h_ctl + 1);
+    (void)hipLaunchKernel(res_kernel<R>(l.K), dim3(l.grid), dim3(l.threads + 64), args, l.lds, E.st);
+    eoff += range;
+    for (int k = 0; k < l.nrun; ++k) nent += l.run[k].ne;
   }
-  return cap > 0 ? cap : 0;
+  k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
 }
 
 template <class R>
@@ -811,31 +1004,9 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
   for (const auto& b : E.sb) vol += (double)b.V * copies;
   const double bytes = 3.0 * 4.0 * sizeof(c2<R>) * vol;  // per pass
   ov_ctx* c = E.lead;
-  const int cap = (c->persistent && copies == 1) ? coop_capacity<R>(c) : 0;
-  if (cap > 0) {
-    int grid = std::min(E.nb_total, cap);
-    k_bar_reset<<<1, 64, 0, E.st>>>(E.gbar);
-    const SysDev* Tp = T;
-    int nsys = E.nsys;
-    const int* bmap = E.bmap;
-    int nbt = E.nb_total;
-    int Lp = L;
-    MsParams mpc = mp;
-    GridBar* gb = E.gbar;
-    void* args[] = {(void*)&Tp, (void*)&nsys, (void*)&bmap, (void*)&nbt, (void*)&Lp, (void*)&mpc,
-                    (void*)&gb};
-    hipError_t e;
-    {
-      Sample smp(c, 2, 2.0 * bytes, E.sb[0].h_ctl + 1);
-      e = hipLaunchCooperativeKernel((const void*)k_ms_persistent<R>, dim3(grid),
-                                     dim3(c->block), args, 0, E.st);
-    }
-    if (e == hipSuccess) {
-      k_ms_coef<<<E.nsys, 256, 0, E.st>>>(T, E.nsys, L, mp);
-      return;
-    }
-    (void)hipGetLastError();
-    c->persistent = 0;  // cooperative launch refused: per-pass kernels from now on
+  if (const ResPlan* pl = E.resident<R>(copies)) {
+    launch_resident<R>(E, T, *pl, bytes, mp, L);
+    return;
   }
   // z-marching passes when every system's workgroup owns whole xy planes of one
   // time slice (X Y == threads per workgroup, sites per thread zc >= 2 dividing Z);
@@ -911,7 +1082,7 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
         k_ms_r<R, 0, false><<<nbt_, c->block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
     }
   }
-  k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp);
+  k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp, ResEpoch{});
 }
 
 template <class R>
@@ -1084,13 +1255,9 @@ ov_status sync(Engine& E) {
   TRY(check_launch(E.lead));
   HIPCHK(E.lead, hipStreamSynchronize(E.st));
   if (!E.lead->ev_use.empty()) collect_samples(E.lead);
-  if (E.gbar && E.lead->persistent) {  // only the persistent kernel uses the grid barrier
-    GridBar gb;
-    HIPCHK(E.lead, hipMemcpy(&gb, E.gbar, sizeof(gb), hipMemcpyDeviceToHost));
-    if (gb.abort) {
-      E.lead->err = "persistent multi-shift: a grid barrier timed out";
-      return OV_ERR_DEVICE;
-    }
+  if (*E.lead->res_abort) {  // the caller runs again with the per-pass kernels (res_retry)
+    E.lead->err = "resident multi-shift: a wait ran out";
+    return OV_ERR_DEVICE;
   }
   return OV_OK;
 }
@@ -1693,7 +1860,8 @@ long long n_est_key(size_t rsize, double tol) {
 template <class F>
 ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
   ov_ctx* c = E.lead;
-  if (!c->use_graphs || c->sample_max > 0 || c->persistent) {
+  if (E.resident_any()) res_gate(c);
+  if (!c->use_graphs || c->sample_max > 0) {
     enqueue();
     return check_launch(c);
   }
@@ -1705,7 +1873,9 @@ ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
   if (it == c->graphs.end()) {
     if (c->graphs.size() >= 64) clear_graphs(c);
     HIPCHK(c, hipStreamBeginCapture(E.st, hipStreamCaptureModeThreadLocal));
+    c->capturing = true;
     enqueue();
+    c->capturing = false;
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(E.st, &g);
     TRY(check_launch(c));
@@ -1845,11 +2015,13 @@ ov_status reliable_update(Engine& E, double tol, int scalar_op) {
   // the last count at this tolerance plus max(4, n/8): a true residual cut short is
   // repeated in full, so this margin stays wider than the inner solves' one (max(3, n/16)
   // saved 0.13 ms per 16^4 solve but repeated four true residuals per uneven-batch solve,
-  // +4%: a batch's count is the maximum over its systems, which moves between calls)
+  // +4%: a batch's count is the maximum over its systems, which moves between calls);
+  // a resident launch stops by itself
   int L = Lfull;
   {
     auto it = c->n_est.find(key);
-    if (it != c->n_est.end()) L = std::min(Lfull, it->second + std::max(4, it->second / 8));
+    if (it != c->n_est.end() && !E.resident<double>(E.pl.gwx ? 2 : 1))
+      L = std::min(Lfull, it->second + std::max(4, it->second / 8));
   }
   clear_ctl(E);
   TRY(reliable_update_L<R>(E, tol, scalar_op, L));
@@ -2017,11 +2189,11 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
     // launch past convergence is an empty pass of ~5 us; a multi-shift cut one iteration
     // short ends a fraction above its relaxed tolerance, which the relaxation bound
     // absorbs, and widens the estimate for the next one: 16^4 15.3 -> 15.1 ms, same
-    // outer iterations, against a margin of two)
+    // outer iterations, against a margin of two); a resident launch stops by itself
     const long long nkey = n_est_key(sizeof(R), tol_it);
     {
       auto it = c->n_est.find(nkey);
-      if (it != c->n_est.end()) LR = std::min(LR, it->second + 1);
+      if (it != c->n_est.end() && !E.resident<R>(E.pl.gw ? 2 : 1)) LR = std::min(LR, it->second + 1);
     }
     char ikey[96];
     std::snprintf(ikey, sizeof ikey, "in|%zu|%.6e|%d|%d|%d|%d", sizeof(R), tol_it, LR, (int)pc,
@@ -2235,6 +2407,7 @@ ov_status tune_run(ov_ctx* c, int nrhs, int iters, float* us) {
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
   const bool fp32 = sizeof(R) == sizeof(float);
+  E.no_res = true;  // the launch shape is the per-pass kernels'
   TRY(engine_init(E, v, true, fp32, solve_tol64(c), fp32 ? c->p.mixed_inner_tol : c->p.inner_tol));
   E.htab.assign((size_t)T_NT * nrhs, SysDev{});
   for (int s = 0; s < nrhs; ++s) {
@@ -2381,11 +2554,11 @@ ov_status ov_ctx_create(const ov_params* p, void* hip_stream, ov_ctx** out) {
   c->use_graphs = (eg && *eg == '1');
   const char* ef = std::getenv("OV_FFT_FIXED");
   c->fft_fixed = !(ef && *ef == '0');
-  // The persistent cooperative multi-shift kernel is opt-in: its grid barriers
-  // (one L2 write-back and invalidate per workgroup) cost more than a kernel
-  // boundary at these sizes.
-  const char* ep = std::getenv("OV_PERSISTENT");
-  c->persistent = (ep && *ep == '1') ? 1 : 0;
+  if (res_setup(c) != OV_OK) {
+    g_err = c->err;
+    (void)ov_ctx_destroy(c);
+    return OV_ERR_DEVICE;
+  }
   *out = c;
   return OV_OK;
 }
@@ -2393,7 +2566,14 @@ ov_status ov_ctx_create(const ov_params* p, void* hip_stream, ov_ctx** out) {
 ov_status ov_ctx_destroy(ov_ctx* c) {
   if (!c) return OV_ERR_INVALID_ARG;
   if (c->priv) (void)hipStreamSynchronize(c->priv);
+  if (c->device >= 0 && c->device < kMaxDevices) {
+    std::lock_guard<std::mutex> lock(g_res_gate[c->device].mu);
+    if (g_res_gate[c->device].last == c) g_res_gate[c->device].last = nullptr;
+  }
   clear_graphs(c);
+  if (c->ev_res) (void)hipEventDestroy(c->ev_res);
+  if (c->res_sh) (void)hipFree(c->res_sh);
+  if (c->res_abort) (void)hipHostFree(c->res_abort);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->ev_in) (void)hipEventDestroy(c->ev_in);
   if (c->priv) (void)hipStreamDestroy(c->priv);
@@ -2533,7 +2713,7 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
 
 ov_status ov_sign(ov_ctx* c, void* out, const void* in, int nrhs, ov_stats* st) {
   Range range("ov_sign");
-  return apply_impl(c, -1, out, in, nullptr, nrhs, st);
+  return res_retry(c, [&] { return apply_impl(c, -1, out, in, nullptr, nrhs, st); });
 }
 
 ov_status ov_apply(ov_ctx* c, ov_op op, void* out, const void* in, const void* phi, int nrhs,
@@ -2542,7 +2722,7 @@ ov_status ov_apply(ov_ctx* c, ov_op op, void* out, const void* in, const void* p
   if ((int)op < 0 || (int)op > OV_OP_M0INV_DAG) return OV_ERR_INVALID_ARG;
   if (c && (op == OV_OP_M0INV || op == OV_OP_M0INV_DAG) && !fft_ok(&c->p, c->err))
     return OV_ERR_INVALID_ARG;
-  return apply_impl(c, (int)op, out, in, phi, nrhs, st);
+  return res_retry(c, [&] { return apply_impl(c, (int)op, out, in, phi, nrhs, st); });
 }
 
 ov_status ov_apply_noalloc(ov_ctx* c, ov_op op, void* out, const void* in, const void* phi,
@@ -2687,7 +2867,7 @@ ov_status ov_solve(ov_ctx* c, void* x, const void* b, const void* phi, int nrhs,
     bv[r] = (const char*)b + r * vb;
     xv[r] = (char*)x + r * vb;
   }
-  return solve_systems(sc, bv, xv, ph, st);
+  return res_retry(sc[0], [&] { return solve_systems(sc, bv, xv, ph, st); });
 }
 
 ov_status ov_solve_batch(int n, ov_ctx* const* ctx, void* const* x, const void* const* b,
@@ -2712,12 +2892,11 @@ ov_status ov_solve_batch(int n, ov_ctx* const* ctx, void* const* x, const void* 
       ph.push_back(phi[i]);
     }
   }
-  return solve_systems(sc, bv, xv, ph, st);
+  return res_retry(sc[0], [&] { return solve_systems(sc, bv, xv, ph, st); });
 }
 
-ov_status ov_force(ov_ctx* c, void* grad_phi, double* S_host, const void* xi, const void* phi,
+static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const void* xi, const void* phi,
                    int nrhs, ov_stats* st) {
-  Range range("ov_force");
   if (!c || !grad_phi || !S_host || !xi || !phi || nrhs < 1) return OV_ERR_INVALID_ARG;
   const double t0 = now_s();
   const size_t V = (size_t)c->p.dims[0] * c->p.dims[1] * c->p.dims[2] * c->p.dims[3];
@@ -2818,6 +2997,14 @@ ov_status ov_force(ov_ctx* c, void* grad_phi, double* S_host, const void* xi, co
   if (st && fell_back)
     for (int r = 0; r < nrhs; ++r) st[r].fp64_fallback = 1;
   return OV_OK;
+}
+
+ov_status ov_force(ov_ctx* c, void* grad_phi, double* S_host, const void* xi, const void* phi,
+                   int nrhs, ov_stats* st) {
+  Range range("ov_force");
+  return res_retry(c, [&] {
+    return force_impl(c, grad_phi, S_host, xi, phi, nrhs, st);
+  });
 }
 
 // ------------------------------------------------ rational layers (Sec. 7.3)
@@ -2934,7 +3121,7 @@ static ov_status rational_core(ov_ctx* c, Engine& E, double a0, int n, const dou
       int bits = 0;
       for (int s = 0; s < ns; ++s) bits |= live[s] ? sticky_bits(E, s) : 0;
       TRY(sticky_status(c, bits, "multi-shift CG on MdagM, product MdagM p"));
-      Lrun = std::min(L, nobs + 4);
+      if (!E.resident<double>(E.pl.gwx ? 2 : 1)) Lrun = std::min(L, nobs + 4);
     }
     k_cg_misc<double><<<nb, bl, 0, E.st>>>(tab(E, T_CG), E.bmap, nb, 5);  // r -= alpha w
     k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 2);                // rho, beta
@@ -3061,9 +3248,8 @@ static ov_status shifted_solve_acc(ov_ctx* c, double sigma, double alpha,
   return OV_ERR_NOT_CONVERGED;
 }
 
-ov_status ov_rational(ov_ctx* c, double a0, int n, const double* alpha, const double* beta,
+static ov_status rational_impl(ov_ctx* c, double a0, int n, const double* alpha, const double* beta,
                       void* out, const void* in, const void* phi, int nrhs, ov_stats* st) {
-  Range range("ov_rational");
   if (!c || !alpha || !beta || !out || !in || !phi || nrhs < 1 || n < 1 || n > MAXP)
     return OV_ERR_INVALID_ARG;
   for (int k = 0; k < n; ++k)
@@ -3133,10 +3319,17 @@ ov_status ov_rational(ov_ctx* c, double a0, int n, const double* alpha, const do
   return OV_OK;
 }
 
-ov_status ov_rational_force(ov_ctx* c, double a0, int n, const double* alpha,
+ov_status ov_rational(ov_ctx* c, double a0, int n, const double* alpha, const double* beta,
+                      void* out, const void* in, const void* phi, int nrhs, ov_stats* st) {
+  Range range("ov_rational");
+  return res_retry(c, [&] {
+    return rational_impl(c, a0, n, alpha, beta, out, in, phi, nrhs, st);
+  });
+}
+
+static ov_status rational_force_impl(ov_ctx* c, double a0, int n, const double* alpha,
                             const double* beta, void* grad_phi, double* S_host, const void* xi,
                             const void* phi, int nrhs, ov_stats* st) {
-  Range range("ov_rational_force");
   if (!c || !alpha || !beta || !grad_phi || !S_host || !xi || !phi || nrhs < 1 || n < 1 ||
       n > MAXP)
     return OV_ERR_INVALID_ARG;
@@ -3224,6 +3417,15 @@ ov_status ov_rational_force(ov_ctx* c, double a0, int n, const double* alpha,
   so.conv.assign(nrhs, 1);
   fill_stats(st, nrhs, &E, &so, now_s() - t0, 16);
   return OV_OK;
+}
+
+ov_status ov_rational_force(ov_ctx* c, double a0, int n, const double* alpha,
+                            const double* beta, void* grad_phi, double* S_host, const void* xi,
+                            const void* phi, int nrhs, ov_stats* st) {
+  Range range("ov_rational_force");
+  return res_retry(c, [&] {
+    return rational_force_impl(c, a0, n, alpha, beta, grad_phi, S_host, xi, phi, nrhs, st);
+  });
 }
 
 // ------------------------------------------------------------ RHMC (Sec. 7.3)
@@ -3338,8 +3540,7 @@ ov_status ov_rhmc_trajectory(ov_ctx* c, void* phi, const void* pi0, const void* 
   return OV_OK;
 }
 
-ov_status ov_locality(ov_ctx* c, int spin, double* f, int nr, ov_stats* st) {
-  Range range("ov_locality");
+static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats* st) {
   if (!c || !f || spin < 0 || spin > 3) return OV_ERR_INVALID_ARG;
   const int* d = c->p.dims;
   const int rmax = d[0] / 2 + d[1] / 2 + d[2] / 2 + d[3] / 2;
@@ -3385,6 +3586,13 @@ ov_status ov_locality(ov_ctx* c, int spin, double* f, int nr, ov_stats* st) {
     return OV_ERR_NOT_CONVERGED;
   }
   return OV_OK;
+}
+
+ov_status ov_locality(ov_ctx* c, int spin, double* f, int nr, ov_stats* st) {
+  Range range("ov_locality");
+  return res_retry(c, [&] {
+    return locality_impl(c, spin, f, nr, st);
+  });
 }
 
 ov_status ov_pack(ov_ctx* c, int prec, void* dst, const void* src, int nrhs) {

@@ -88,7 +88,7 @@ class Lattice:
 
     def kernel_times(self, kernel, reset=True):
         """(event_ms, count, bytes) of the sampled multi-shift kernel (0 t pass, 1 r pass,
-        2 persistent); see kernel_spans for the device-stamped kernel-only spans."""
+        2 resident); see kernel_spans for the device-stamped kernel-only spans."""
         return self._kernel_times(kernel, reset)[:3]
 
     def kernel_spans(self, kernel, reset=True):
