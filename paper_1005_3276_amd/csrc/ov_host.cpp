@@ -160,7 +160,7 @@ ResGeom res_geom(const int dims[4], int esize, int ncu, int maxK) {
           if (dims[3] % b[3]) continue;
           if (b[0] > 255 || b[1] > 255 || b[2] > 255 || b[3] > 255) continue;
           const long long S = (long long)b[0] * b[1] * b[2] * b[3];
-          if (S > (long long)RES_MAX_THREADS * maxK || S * 4 * esize > RES_MAX_LDS) continue;
+          if (S > (long long)RES_MAX_THREADS * maxK || (S + 1) * (4 * esize + 16) > RES_MAX_LDS) continue;
           ResGeom r;
           long long G = 1;
           r.S = (int)S;

@@ -28,6 +28,7 @@
 namespace ov {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int MAXP = 32;      // max poles
 constexpr int NTHREADS = 256; // default workgroup size (4 waves)
 
@@ -814,11 +815,11 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
 //      words that carry the pass's epoch, so one exchange is the reduction and the barrier;
 //   3. with the sum they update t or r, while the service wave advances the recurrences.
 // Nothing else crosses workgroups, so no cache is written back or invalidated, and t_n goes
-// to the basis with streaming stores that nothing waits for.  Bound by latency: of the
-// 9100 cycles of an FP64 pass at 16^4 (one source, 128 workgroups of 512 sites, 3.9 us; 10 us
-// plus the launch gap per pass kernel) 2400 update and publish, 2600 are hops out of LDS,
-// and 3800 wait for faces and the sum; 8^4 takes 2.4 us (4.5 us), 4^4, one workgroup and no
-// exchange, 1.5 us (3.3 us).
+// to the basis with streaming stores that nothing waits for.  Bound by latency: an FP64 pass
+// at 16^4 (one source, 128 workgroups of 512 sites) takes 3.7 us, a quarter of it update and
+// publish, a quarter the hops out of LDS, the rest waits for faces and the sum (the per-pass
+// kernels: 10 us and the launch gap); 8^4 takes 2.4 us (4.5 us), 4^4, one workgroup and no
+// exchange, 1.4 us (3.3 us).
 struct ResRun {          // consecutive entries on one lattice
   int e0, ne;            // table entries
   int wg0;               // first workgroup of the launch
@@ -870,27 +871,62 @@ struct Half {
   c2<R> a, b;
 };
 
-// Two components of a face site at byte offset o: FP64 one 16-byte access per component
-// (components Fb bytes apart), FP32 both in one access.
-__device__ __forceinline__ Half<double> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
-                                                double) {
-  const u32x4 p = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, RES_SC1);
-  const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, o + Fb, 0, RES_SC1);
+// Two components of a face site at byte offset o of the field that starts at byte so: FP64
+// one 16-byte access per component (components Fb bytes apart), FP32 both in one access.
+__device__ __forceinline__ Half<double> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned so,
+                                                unsigned Fb, double) {
+  const u32x4 p = __builtin_amdgcn_raw_buffer_load_b128(rs, o, so, RES_SC1);
+  const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, o, so + Fb, RES_SC1);
   return Half<double>{__builtin_bit_cast(double2, p), __builtin_bit_cast(double2, q)};
 }
-__device__ __forceinline__ Half<float> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned,
-                                               float) {
-  return __builtin_bit_cast(Half<float>, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, RES_SC1));
+__device__ __forceinline__ Half<float> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned so,
+                                               unsigned, float) {
+  return __builtin_bit_cast(Half<float>,
+                            __builtin_amdgcn_raw_buffer_load_b128(rs, o, so, RES_SC1));
 }
+// Stores add the field's byte to the vector offset: behind a 16-byte store with an offset in
+// a scalar register the compiler leaves no wait state before it reuses the data registers,
+// and the store then took the new values here.
 __device__ __forceinline__ void face_st(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
                                         const Half<double>& h) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.a), rs, o, 0, RES_SC1);
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.b), rs, o + Fb, 0,
-                                         RES_SC1);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.b), rs, o + Fb, 0, RES_SC1);
 }
 __device__ __forceinline__ void face_st(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned,
                                         const Half<float>& h) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), rs, o, 0, RES_SC1);
+}
+
+// The field in LDS: a site's four components side by side, 16 bytes of padding behind them
+// (FP64 80, FP32 48 bytes a site: 16 lanes of consecutive sites fall on different banks, and
+// one address serves every component).  Site S, the last, stays zero: a neighbour that is
+// another workgroup's.
+template <class R>
+constexpr int RES_SITE = 4 * (int)sizeof(c2<R>) + 16;
+__device__ __forceinline__ void lds_get(const unsigned char* sh, unsigned j, double2 v[4]) {
+  const u32x4* p = (const u32x4*)(sh + j * RES_SITE<double>);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = __builtin_bit_cast(double2, p[q]);
+}
+__device__ __forceinline__ void lds_get(const unsigned char* sh, unsigned j, float2 v[4]) {
+  const f32x4* p = (const f32x4*)(sh + j * RES_SITE<float>);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const f32x4 x = p[q];
+    v[2 * q] = float2{x.x, x.y};
+    v[2 * q + 1] = float2{x.z, x.w};
+  }
+}
+__device__ __forceinline__ void lds_put(unsigned char* sh, unsigned j, const double2 v[4]) {
+  u32x4* p = (u32x4*)(sh + j * RES_SITE<double>);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) p[q] = __builtin_bit_cast(u32x4, v[q]);
+}
+__device__ __forceinline__ void lds_put(unsigned char* sh, unsigned j, const float2 v[4]) {
+  f32x4* p = (f32x4*)(sh + j * RES_SITE<float>);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    p[q] = f32x4{v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y};
 }
 
 // Sum over the wave in lane 63, on the vector ALU alone (a shuffle tree through LDS takes
@@ -948,7 +984,7 @@ struct ResSite {
   int j, gi;        // index in the block and on the lattice
   unsigned fl;      // bits 2 mu, 2 mu + 1: the hop from above / below comes from another
                     // workgroup; 8, 9: the time hop above / below takes the phase -1
-  unsigned nb[4];   // LDS indices of the neighbours: above | below << 16
+  unsigned nb[4];   // LDS sites of the neighbours: above | below << 16 (S: another's)
   unsigned st[4];   // byte offset of the half spinor the site sends, RES_OOB for none
   unsigned ld[4];   // byte offset of the one it receives
 };
@@ -979,8 +1015,8 @@ __host__ __device__ inline ResSite res_site(const ResRun& U, const Geo& g, int w
     const int b = U.b[mu], n = U.nb[mu];
     const bool top = c[mu] == b - 1, bot = c[mu] == 0, cut = n > 1;
     const unsigned F = (unsigned)(S / b);
-    s.nb[mu] = (unsigned)(top ? j - ss * (b - 1) : j + ss) |
-               (unsigned)(bot ? j + ss * (b - 1) : j - ss) << 16;
+    s.nb[mu] = (unsigned)(!top ? j + ss : cut ? S : j - ss * (b - 1)) |
+               (unsigned)(!bot ? j - ss : cut ? S : j + ss * (b - 1)) << 16;
     s.st[mu] = s.ld[mu] = RES_OOB;
     if (cut && top) s.fl |= 1u << 2 * mu;
     if (cut && bot) s.fl |= 2u << 2 * mu;
@@ -1016,7 +1052,7 @@ template <class R>
 struct ResBlock {
   int S;                     // sites of the block
   unsigned Fb[4];            // bytes between the two components of a face site (FP64)
-  c2<R>* sh;                 // LDS, [4][S]
+  unsigned char* sh;         // LDS
   __amdgpu_buffer_rsrc_t rs;
 
   // Keeps what follows from a value (addresses of eight neighbours per site) from being
@@ -1038,33 +1074,24 @@ struct ResBlock {
     put<1>(v, s, fl, fld);
     put<2>(v, s, fl, fld);
     put<3>(v, s, fl, fld);
-    if (s.j < S) {
-      const int j = (int)opaque((unsigned)s.j);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sh[q * S + j] = v[q];
-    }
+    if (s.j < S) lds_put(sh, (unsigned)s.j, v);
   }
   __device__ __forceinline__ void halo(ResHalo<R>& h, const ResSite& s, unsigned fld) const {
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) h.h[mu] = face_ld(rs, opaque(s.ld[mu]) + fld, Fb[mu], R());
+    for (int mu = 0; mu < 4; ++mu) h.h[mu] = face_ld(rs, s.ld[mu], fld, Fb[mu], R());
   }
 
-  // hops of an axis from inside the block (0 where the neighbour is another workgroup's)
+  // hops of an axis from inside the block
   template <int MU>
   __device__ __forceinline__ void hop_in(unsigned nb, unsigned fl, c2<R> acc[4]) const {
-    const unsigned jf = nb & 0xffffu, jb = nb >> 16;
     R ff = R(1), fb = R(1);
     if (MU == 3) {
       ff = fl & 256u ? R(-1) : R(1);
       fb = fl & 512u ? R(-1) : R(1);
     }
-    ff = fl & (1u << 2 * MU) ? R(0) : ff;
-    fb = fl & (2u << 2 * MU) ? R(0) : fb;
     c2<R> n[4], m[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) n[q] = sh[q * S + jf];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) m[q] = sh[q * S + jb];
+    lds_get(sh, nb & 0xffffu, n);
+    lds_get(sh, nb >> 16, m);
     hop_add<R, MU>(hop_project<R, MU>(n, R(-1)), ff, -ff, acc);
     hop_add<R, MU>(hop_project<R, MU>(m, R(1)), fb, fb, acc);
   }
@@ -1146,6 +1173,9 @@ __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int sl
     const u32x4 x = {(unsigned)bits, epoch, (unsigned)(bits >> 32), epoch};
     __builtin_amdgcn_raw_buffer_store_b128(x, rs, w * 64, 0, RES_SC1);
   }
+  // nothing arrives sooner; polls in the meantime slow the stores that are on their way
+  // (16^4 3.98 -> 3.78 us per pass, 8^4 2.54 -> 2.50; 44 instead of 30: 4.10 and 2.88)
+  __builtin_amdgcn_s_sleep(30);
   long long t0 = 0;
   bool faces = false;
   for (int n = 0;; ++n) {
@@ -1326,7 +1356,9 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
   const Geo g = S.g;
   ResBlock<R> B;
   B.S = U.b[0] * U.b[1] * U.b[2] * U.b[3];
-  B.sh = (c2<R>*)dyn_lds;
+  B.sh = dyn_lds;
+  if (threadIdx.x < RES_SITE<R> / 4)  // the zero site
+    ((unsigned*)(dyn_lds + B.S * RES_SITE<R>))[threadIdx.x] = 0u;
   const unsigned fb = (unsigned)(G * U.FT * sizeof(c2<R>));  // bytes of one field's faces
   B.rs = __builtin_amdgcn_make_buffer_rsrc(A.face + U.face0 + (size_t)(lw / G) * 2 * fb, 0,
                                            (int)(2 * fb), 0x00020000);

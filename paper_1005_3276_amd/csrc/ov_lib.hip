@@ -491,7 +491,7 @@ struct Engine {
       l->grid += q.G;
       l->threads = std::max(l->threads, q.threads);
       l->K = std::max(l->K, q.K);
-      l->lds = std::max(l->lds, (size_t)q.S * 4 * esize);
+      l->lds = std::max(l->lds, (size_t)(q.S + 1) * (4 * esize + 16));
       faces += fb;
       us = std::max(us, q.us);
     }

@@ -28,7 +28,7 @@ static void check(const int* d, int ncu, bool fits) {
   CHECK((q.G > 0) == fits, d);
   if (q.G == 0) return;
   CHECK(q.G <= ncu && q.K <= maxK && q.threads % 64 == 0 && q.threads <= RES_MAX_THREADS, d);
-  CHECK(q.threads * q.K >= q.S && q.S * 4 * (int)sizeof(c2<R>) <= RES_MAX_LDS, d);
+  CHECK(q.threads * q.K >= q.S && (q.S + 1) * RES_SITE<R> <= RES_MAX_LDS, d);
   const int V = d[0] * d[1] * d[2] * d[3];
   CHECK(q.G * q.S == V, d);
   ResRun U{};
@@ -73,6 +73,7 @@ static void check(const int* d, int ncu, bool fits) {
         const ResSite& n = at[side ? dn : up];
         const bool cut = s.fl & ((side ? 2u : 1u) << 2 * m);
         if (cut) {
+          CHECK((side ? s.nb[m] >> 16 : s.nb[m] & 0xffffu) == (unsigned)q.S, d);  // zero site
           CHECK(s.ld[m] == n.st[m] && n.st[m] != RES_OOB, d);
           // the sender's face is the one that looks at the receiver
           CHECK(n.fl & ((side ? 1u : 2u) << 2 * m), d);
