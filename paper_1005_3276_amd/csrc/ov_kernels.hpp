@@ -85,6 +85,12 @@ struct SysDev {
   int off_xy, off_z, off_t; // first workgroup of this system in each transform pass
   int xc;                   // x values per workgroup in the t pass (divides X, xc T <= 64)
   double* pcs;              // [V] preconditioner scale per momentum (k_pcg_table), or null
+  // the caller's fields (complex128, spin innermost) and their planar twins of a call:
+  // k_pack io_in -> io_pin, k_unpack io_pout -> io_out
+  const double2* io_in;
+  void* io_pin;
+  void* io_pout;
+  double2* io_out;
 };
 
 // CG scalar slots
@@ -111,39 +117,36 @@ __device__ __forceinline__ int find_sys(const SysDev* __restrict__ sys, int nsys
 }
 
 // ------------------------------------------------------------------ pack
-// ABI complex128 (V,4) AoS (optionally times g5, times scale) <-> spin-planar R.
+// The caller's complex128 (V, 4) <-> spin-planar R.
 template <class R>
-__global__ void k_pack(const SysDev* __restrict__ sys, const int* __restrict__ bmap, int nb_total,
-                       const double2* const* __restrict__ src, void* const* __restrict__ dst,
-                       double scale) {
+__global__ void k_pack(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
+                       int nb_total) {
   const int L = xcd_logical_block(nb_total);
-  const int s = bmap[L];
-  const SysDev& S = sys[s];
+  const SysDev& S = sys[bmap[L]];
   const int V = S.g.V;
   const int lb = L - S.blk0;
-  const double2* in = src[s];
-  c2<R>* out = (c2<R>*)dst[s];
+  const double2* in = S.io_in;
+  c2<R>* out = (c2<R>*)S.io_pin;
   const int i0 = lb * S.spb;
   const int i1 = min(V, i0 + S.spb);
   for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const double2 v = in[(size_t)i * 4 + k];
-      out[(size_t)k * V + i] = c2<R>{(R)(scale * v.x), (R)(scale * v.y)};
+      out[(size_t)k * V + i] = c2<R>{(R)v.x, (R)v.y};
     }
   }
 }
 
 template <class R>
-__global__ void k_unpack(const SysDev* __restrict__ sys, const int* __restrict__ bmap, int nb_total,
-                         void* const* __restrict__ src, double2* const* __restrict__ dst) {
+__global__ void k_unpack(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
+                         int nb_total) {
   const int L = xcd_logical_block(nb_total);
-  const int s = bmap[L];
-  const SysDev& S = sys[s];
+  const SysDev& S = sys[bmap[L]];
   const int V = S.g.V;
   const int lb = L - S.blk0;
-  const c2<R>* in = (const c2<R>*)src[s];
-  double2* out = dst[s];
+  const c2<R>* in = (const c2<R>*)S.io_pout;
+  double2* out = S.io_out;
   const int i0 = lb * S.spb;
   const int i1 = min(V, i0 + S.spb);
   for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
@@ -165,17 +168,15 @@ __global__ void k_scale_copy(double2* __restrict__ out, const double2* __restric
   }
 }
 
-// dst += a * src: planar FP64 src (spin-planar) added into the ABI's complex128 AoS dst.
+// io_out += a io_pout: planar FP64 added into the caller's field.
 __global__ void k_unpack_axpy(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
-                              int nb_total, void* const* __restrict__ src,
-                              double2* const* __restrict__ dst, double a) {
+                              int nb_total, double a) {
   const int L = xcd_logical_block(nb_total);
-  const int s = bmap[L];
-  const SysDev& S = sys[s];
+  const SysDev& S = sys[bmap[L]];
   const int V = S.g.V;
   const int lb = L - S.blk0;
-  const double2* in = (const double2*)src[s];
-  double2* out = dst[s];
+  const double2* in = (const double2*)S.io_pout;
+  double2* out = S.io_out;
   const int i0 = lb * S.spb;
   const int i1 = min(V, i0 + S.spb);
   for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
@@ -3045,7 +3046,8 @@ __global__ void __launch_bounds__(256) k_md_axpy(double2* __restrict__ y, double
 //   3 / 7: reliable update (true |r|^2 replaces the recursive one; 7 restarts);
 //   4: |b|^2;  5: true |r|^2 only;
 //   preconditioned (PCG, z = P r):  9: beta, rho = <r, z>, |r|^2;  10: start;
-//   11 / 12: reliable update from the true residual (|r|^2 set by op 5; 12 restarts).
+//   11 / 12: reliable update from the true residual (|r|^2 set by op 5; 12 restarts);
+//   13: the part_b sum alone -> RTRUE.
 __global__ void k_cg_scalar(const SysDev* __restrict__ sys, int nsys, int op) {
   __shared__ double lds[17];
   const int s = blockIdx.x;
@@ -3098,6 +3100,8 @@ __global__ void k_cg_scalar(const SysDev* __restrict__ sys, int nsys, int op) {
       c[CG_BETA] = (op == 12 || rt > 4.0 * rec) ? 0.0 : rz / c[CG_RR_OLD];
     } else if (op == 4) {  // norm of b
       c[CG_BB] = v;
+    } else if (op == 13) {
+      c[CG_RTRUE] = rz;
     }
   }
 }

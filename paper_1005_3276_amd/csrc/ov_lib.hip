@@ -55,10 +55,14 @@ struct ov_ctx {
   size_t user_ws_bytes = 0;
   void* own_ws = nullptr;
   size_t own_ws_bytes = 0;
+  char* host_block = nullptr;    // pinned: what a context starts with (the four below)
   double* pinned = nullptr;      // host staging of per-system scalars
   int pinned_n = 0;
   bool noalloc = false;          // inside ov_apply_noalloc: scratch array, no allocation
   int* pinned_flags = nullptr;
+  char* stage = nullptr;         // pinned: a call's tables on their way to the device
+  size_t stage_cap = 0;
+  bool stage_busy = false;       // a copy from it may still run
   // kernel-duration sampling (see ov_kernel_sampling)
   int sample_max = 0;
   std::vector<hipEvent_t> ev_pool;             // pairs
@@ -95,6 +99,9 @@ void* g_scratch_dev[kMaxDevices] = {};  // device address of `scratch` per devic
 // Host staging (pinned scalars) allocated at context creation, so that the
 // no-allocation entry point never allocates it: systems it serves per call.
 constexpr int kNoAllocSystems = 16;
+// ... and bytes of tables: two per system, and a workgroup map that the scratch array bounds
+// (each workgroup's sites hold basis fields in it).
+constexpr size_t kNoAllocStage = 64 << 10;
 
 thread_local std::string g_err;
 
@@ -397,12 +404,18 @@ struct Engine {
   hipStream_t st;
   Plan pl;
   int nsys = 0, nb_total = 0;
-  SysDev* tables = nullptr;         // device: T_NT * nsys
+  SysDev* tables = nullptr;         // device: ntab * nsys
   std::vector<SysDev> htab;         // host copy
-  void** ptrs = nullptr;            // device pointer arrays for pack/unpack (2 * nsys)
+  size_t up_bytes = 0;              // bytes from `tables` to the end of the uploaded region
+  int ntab = T_NT;                  // tables this engine has: the first two, or all (solves)
   int* bmap = nullptr;              // device: logical workgroup -> system
-  std::vector<int> hbmap;
-  std::vector<void*> hptrs;         // host staging of ptrs (outlives the async copy)
+  // the caller's fields and their planar twins per system (SysDev io_*), copied into the
+  // T_APPLY entries
+  struct Io {
+    const void* in = nullptr;
+    void *pin = nullptr, *pout = nullptr, *out = nullptr;
+  };
+  std::vector<Io> io;
   double* cg_all = nullptr;         // device: nsys * CG_NSLOT scalars (one copy to the host)
   long long* stat_all = nullptr;    // device: 3 nsys * 4 multi-shift counters (entries A, B, B')
   double* dstat_all = nullptr;      // device: 3 nsys * 2 shift residuals
@@ -417,6 +430,7 @@ struct Engine {
   int L64 = 0, LR = 0;              // multi-shift launch counts
   bool no_relax = false;            // fixed inner tolerance (the FP64 fallback solver)
   double shift = 0.0;               // solve (MdagM + shift) x = b (rational layers)
+  bool guess = false;               // solve: pack the caller's guesses (io) into x64 first
   int max_outer = 0;                // > 0: outer iteration cap instead of max_outer (the
                                     // fallback solver gets what the mixed one left)
   bool force_fallback = false;      // hand every system to the FP64 solver at its first
@@ -425,7 +439,6 @@ struct Engine {
   SysDev* ftab = nullptr;           // device: (system, shift) table of the rational force
   SysDev* gwtab = nullptr;          // device: 2 nsys multi-shift entries of the GW inner operator
   int* gwbmap = nullptr;            // device: 2 nb_total workgroups -> entry
-  std::vector<int> hgwbmap;
   std::vector<SysDev> hgwtab;       // host copy of gwtab
   SysDev* trgwtab = nullptr;        // device: 2 nsys entries of the FP64 true residual (same map)
   std::vector<SysDev> htrgw;        // host copy
@@ -577,30 +590,22 @@ struct Engine {
     geo_key.clear();
     for (int s = 0; s < nsys; ++s) {
       const ov_params& p = ctxs[s]->p;
+      if (!lead->use_graphs) break;
       char g[96];
       std::snprintf(g, sizeof g, "%dx%dx%dx%d/%d/%d/%d;", p.dims[0], p.dims[1], p.dims[2],
                     p.dims[3], p.bc_t, sb[s].spb, sb[s].xc);
       geo_key += g;
     }
-    tables = (SysDev*)bp.take(sizeof(SysDev) * T_NT * nsys);
     ftab = pl.nshift > 0 ? (SysDev*)bp.take(sizeof(SysDev) * nsys * pl.nshift) : nullptr;
-    gwtab = pl.gw ? (SysDev*)bp.take(sizeof(SysDev) * 2 * nsys) : nullptr;
-    gwbmap = (pl.gw || pl.gwx) ? (int*)bp.take(sizeof(int) * 2 * (size_t)nb_total) : nullptr;
-    trgwtab = pl.gwx ? (SysDev*)bp.take(sizeof(SysDev) * 2 * nsys) : nullptr;
-    hgwbmap.clear();
-    if (pl.gw || pl.gwx) {
-      hgwbmap.assign(2 * (size_t)nb_total, 0);
-      for (int s = 0; s < nsys; ++s)
-        for (int b = 0; b < sb[s].nblk; ++b) {
-          hgwbmap[sb[s].blk0 + b] = s;
-          hgwbmap[nb_total + sb[s].blk0 + b] = nsys + s;
-        }
-    }
-    ptrs = (void**)bp.take(sizeof(void*) * 2 * nsys);
+    // one region, uploaded with one copy (upload_tables)
+    ntab = pl.solve ? T_NT : 2;
+    tables = (SysDev*)bp.take(sizeof(SysDev) * ntab * nsys);
+    const size_t up0 = bp.off - sizeof(SysDev) * ntab * nsys;
     bmap = (int*)bp.take(sizeof(int) * (size_t)nb_total);
-    hbmap.assign(nb_total, 0);
-    for (int s = 0; s < nsys; ++s)
-      for (int b = 0; b < sb[s].nblk; ++b) hbmap[sb[s].blk0 + b] = s;
+    gwtab = pl.gw ? (SysDev*)bp.take(sizeof(SysDev) * 2 * nsys) : nullptr;
+    trgwtab = pl.gwx ? (SysDev*)bp.take(sizeof(SysDev) * 2 * nsys) : nullptr;
+    gwbmap = (pl.gw || pl.gwx) ? (int*)bp.take(sizeof(int) * 2 * (size_t)nb_total) : nullptr;
+    up_bytes = bp.off - up0;
     return bp.off + 256;
   }
 };
@@ -651,6 +656,31 @@ ov_status ensure_ws(ov_ctx* c, size_t need, void** base) {
   return OV_OK;
 }
 
+// Pinned memory a context starts with, one allocation: scalars and flags of kNoAllocSystems
+// systems, the staging, and the abort word of the resident launches.
+constexpr size_t kHostScalars = sizeof(double) * (CG_NSLOT + 24) * kNoAllocSystems;
+constexpr size_t kHostFlags = 256;  // two ints per system
+static_assert(2 * kNoAllocSystems * sizeof(int) <= kHostFlags, "flags");
+static_assert(2 * kNoAllocSystems * sizeof(SysDev) + 16384 <= kNoAllocStage, "tables");
+constexpr size_t kHostBlock = kHostScalars + kHostFlags + kNoAllocStage + 64;
+ov_status host_setup(ov_ctx* c) {
+  HIPCHK(c, hipHostMalloc((void**)&c->host_block, kHostBlock));
+  c->pinned = (double*)c->host_block;
+  c->pinned_flags = (int*)(c->host_block + kHostScalars);
+  c->pinned_n = kNoAllocSystems;
+  c->stage = c->host_block + kHostScalars + kHostFlags;
+  c->stage_cap = kNoAllocStage;
+  c->res_abort = (int*)(c->stage + kNoAllocStage);
+  *c->res_abort = 0;
+  return OV_OK;
+}
+
+// Frees pinned memory a context has grown (not its first block).
+void host_free(ov_ctx* c, void* p) {
+  if (p && !((char*)p >= c->host_block && (char*)p < c->host_block + kHostBlock))
+    (void)hipHostFree(p);
+}
+
 ov_status ensure_pinned(ov_ctx* c, int nsys) {
   if (c->pinned_n >= nsys) return OV_OK;
   if (c->noalloc) {
@@ -660,8 +690,8 @@ ov_status ensure_pinned(ov_ctx* c, int nsys) {
     c->err = buf;
     return OV_ERR_WORKSPACE;
   }
-  if (c->pinned) (void)hipHostFree(c->pinned);
-  if (c->pinned_flags) (void)hipHostFree(c->pinned_flags);
+  host_free(c, c->pinned);
+  host_free(c, c->pinned_flags);
   c->pinned = nullptr;
   c->pinned_flags = nullptr;
   HIPCHK(c, hipHostMalloc((void**)&c->pinned, sizeof(double) * (CG_NSLOT + 24) * nsys));
@@ -752,8 +782,6 @@ ov_status res_setup(ov_ctx* c) {
     HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RES_MAX_LDS));
   HIPCHK(c, hipMalloc((void**)&c->res_sh, sizeof(ResShared)));
   HIPCHK(c, hipMemsetAsync(c->res_sh, 0, sizeof(ResShared), c->priv));
-  HIPCHK(c, hipHostMalloc((void**)&c->res_abort, 64));
-  *c->res_abort = 0;
   HIPCHK(c, hipEventCreateWithFlags(&c->ev_res, hipEventDisableTiming));
   return OV_OK;
 }
@@ -763,7 +791,7 @@ ov_status res_setup(ov_ctx* c) {
 template <class F>
 ov_status res_retry(ov_ctx* c, F&& call) {
   const ov_status rc = call();
-  if (!c || !c->res_abort || !*c->res_abort) return rc;
+  if (!c || !*c->res_abort) return rc;
   HIPCHK(c, hipStreamSynchronize(c->priv));
   *c->res_abort = 0;
   k_zero32<<<1, 64, 0, c->priv>>>(&c->res_sh->abort, 1);
@@ -877,24 +905,52 @@ SysDev base_dev(const SysBuf& b) {
   return d;
 }
 
-// Host tables are pageable; synchronise after the copy so that htab can be
-// rebuilt safely (tables change a few times per call, never per iteration).
-ov_status upload_tables(Engine& E) {
-  HIPCHK(E.lead, hipMemcpyAsync(E.tables, E.htab.data(), sizeof(SysDev) * E.htab.size(),
-                                hipMemcpyHostToDevice, E.st));
-  HIPCHK(E.lead, hipMemcpyAsync(E.bmap, E.hbmap.data(), sizeof(int) * E.hbmap.size(),
-                                hipMemcpyHostToDevice, E.st));
-  if (E.pl.gw && E.hgwtab.size() == 2 * (size_t)E.nsys)
-    HIPCHK(E.lead, hipMemcpyAsync(E.gwtab, E.hgwtab.data(), sizeof(SysDev) * E.hgwtab.size(),
-                                  hipMemcpyHostToDevice, E.st));
-  if (E.pl.gwx && E.htrgw.size() == 2 * (size_t)E.nsys)
-    HIPCHK(E.lead, hipMemcpyAsync(E.trgwtab, E.htrgw.data(), sizeof(SysDev) * E.htrgw.size(),
-                                  hipMemcpyHostToDevice, E.st));
-  if ((E.pl.gw || E.pl.gwx) && E.hgwbmap.size() == 2 * (size_t)E.nb_total) {
-    HIPCHK(E.lead, hipMemcpyAsync(E.gwbmap, E.hgwbmap.data(), sizeof(int) * E.hgwbmap.size(),
-                                  hipMemcpyHostToDevice, E.st));
+// Pinned staging of at least `bytes`, free to be written.
+ov_status ensure_stage(ov_ctx* c, size_t bytes) {
+  if (c->stage_busy) HIPCHK(c, hipStreamSynchronize(c->priv));
+  c->stage_busy = false;
+  if (c->stage_cap >= bytes) return OV_OK;
+  if (c->noalloc) {
+    c->err = "no-allocation call: the host staging is too small";
+    return OV_ERR_WORKSPACE;
   }
-  HIPCHK(E.lead, hipStreamSynchronize(E.st));
+  host_free(c, c->stage);
+  c->stage = nullptr;
+  c->stage_cap = 0;
+  HIPCHK(c, hipHostMalloc((void**)&c->stage, bytes));
+  c->stage_cap = bytes;
+  return OV_OK;
+}
+
+// The engine's host tables to the device: one asynchronous copy from pinned memory (a copy
+// per table, each waited for, took 20 us of a call that runs 60 us of kernels).
+ov_status upload_tables(Engine& E) {
+  ov_ctx* c = E.lead;
+  TRY(ensure_stage(c, E.up_bytes));
+  auto at = [&](const void* dev) { return c->stage + ((const char*)dev - (const char*)E.tables); };
+  std::memcpy(c->stage, E.htab.data(), sizeof(SysDev) * (size_t)E.ntab * E.nsys);
+  if (!E.io.empty())
+    for (int s = 0; s < E.nsys; ++s) {
+      SysDev& d = ((SysDev*)c->stage)[(size_t)T_APPLY * E.nsys + s];
+      d.io_in = (const double2*)E.io[s].in;
+      d.io_pin = E.io[s].pin;
+      d.io_pout = E.io[s].pout;
+      d.io_out = (double2*)E.io[s].out;
+    }
+  int* m = (int*)at(E.bmap);
+  for (int s = 0; s < E.nsys; ++s)
+    for (int b = 0; b < E.sb[s].nblk; ++b) *m++ = s;
+  if (E.pl.gw && E.hgwtab.size() == 2 * (size_t)E.nsys)
+    std::memcpy(at(E.gwtab), E.hgwtab.data(), sizeof(SysDev) * E.hgwtab.size());
+  if (E.pl.gwx && E.htrgw.size() == 2 * (size_t)E.nsys)
+    std::memcpy(at(E.trgwtab), E.htrgw.data(), sizeof(SysDev) * E.htrgw.size());
+  if (E.gwbmap) {
+    m = (int*)at(E.gwbmap);
+    for (int s = 0; s < 2 * E.nsys; ++s)
+      for (int b = 0; b < E.sb[s % E.nsys].nblk; ++b) *m++ = s;
+  }
+  HIPCHK(c, hipMemcpyAsync(E.tables, c->stage, E.up_bytes, hipMemcpyHostToDevice, E.st));
+  c->stage_busy = true;
   return OV_OK;
 }
 
@@ -1254,6 +1310,7 @@ ov_status check_launch(ov_ctx* c) {
 ov_status sync(Engine& E) {
   TRY(check_launch(E.lead));
   HIPCHK(E.lead, hipStreamSynchronize(E.st));
+  E.lead->stage_busy = false;
   if (!E.lead->ev_use.empty()) collect_samples(E.lead);
   if (*E.lead->res_abort) {  // the caller runs again with the per-pass kernels (res_retry)
     E.lead->err = "resident multi-shift: a wait ran out";
@@ -1262,36 +1319,46 @@ ov_status sync(Engine& E) {
   return OV_OK;
 }
 
-ov_status read_ctl(Engine& E, std::vector<int>& ctl3, std::vector<long long>& stat0,
-                   std::vector<double>& dstat0) {
-  ctl3.resize(E.nsys);
-  stat0.resize(E.nsys);
-  dstat0.resize(E.nsys);
-  std::vector<long long> statb(E.nsys, 0), statt(E.nsys, 0);
-  std::vector<int> ctlb(E.nsys, 0);
-  for (int s = 0; s < E.nsys; ++s) {
-    HIPCHK(E.lead, hipMemcpyAsync(&ctl3[s], E.sb[s].h_ctl + 3, sizeof(int),
-                                  hipMemcpyDeviceToHost, E.st));
-    HIPCHK(E.lead, hipMemcpyAsync(&stat0[s], E.sb[s].stat, sizeof(long long),
-                                  hipMemcpyDeviceToHost, E.st));
-    HIPCHK(E.lead, hipMemcpyAsync(&dstat0[s], E.sb[s].dstat, sizeof(double),
-                                  hipMemcpyDeviceToHost, E.st));
-    if (E.sb[s].ms_b_stat) {  // second multi-shift entry of the GW inner operator
-      HIPCHK(E.lead, hipMemcpyAsync(&statb[s], E.sb[s].ms_b_stat, sizeof(long long),
-                                    hipMemcpyDeviceToHost, E.st));
-      HIPCHK(E.lead, hipMemcpyAsync(&ctlb[s], E.sb[s].ms_b_h_ctl + 3, sizeof(int),
-                                    hipMemcpyDeviceToHost, E.st));
-    }
-    if (E.sb[s].tb_stat)  // entry B of the true residuals (iteration counts only)
-      HIPCHK(E.lead, hipMemcpyAsync(&statt[s], E.sb[s].tb_stat, sizeof(long long),
-                                    hipMemcpyDeviceToHost, E.st));
+// CG scalars, multi-shift counters, shift residuals and control words of every entry
+// (the engine's contiguous scalar block) to the pinned host copy, then synchronise.
+ov_status read_scalars(Engine& E) {
+  static_assert(sizeof(long long) == sizeof(double), "counters share the scalar block");
+  HIPCHK(E.lead, hipMemcpyAsync(E.lead->pinned, E.cg_all,
+                                sizeof(double) * CG_NSLOT * E.nsys + sizeof(int) * E.ctl_words,
+                                hipMemcpyDeviceToHost, E.st));
+  return sync(E);
+}
+
+// Sticky multi-shift error bits (h_ctl[3]: bit 1 breakdown, bit 2 not converged within
+// the launched iterations or the basis) of system s's entries, from the last
+// read_scalars.
+int sticky_bits(const Engine& E, int s) {
+  const int* ctl = (const int*)((const double*)E.lead->pinned + (size_t)CG_NSLOT * E.nsys +
+                                (size_t)18 * E.nsys);
+  int b = 0;
+  for (int e = 0; e < 3; ++e) b |= ctl[(size_t)(e * E.nsys + s) * 4 + 3];
+  return b;
+}
+
+// Error bits, multi-shift iterations (every entry) and shift residual of system s, from the
+// last read_scalars.
+struct SysCtl {
+  int bits;
+  long long inner;
+  double shift_res;
+};
+SysCtl sys_ctl(const Engine& E, int s) {
+  const size_t ns = E.nsys;
+  const long long* st = (const long long*)(E.lead->pinned + CG_NSLOT * ns);
+  const double* ds = E.lead->pinned + (CG_NSLOT + 12) * ns;
+  const int* ctl = (const int*)(E.lead->pinned + (CG_NSLOT + 18) * ns);
+  SysCtl c{ctl[4 * s + 3], st[4 * s], ds[2 * s]};
+  if (E.sb[s].ms_b_stat) {  // second multi-shift entry of the inner operator
+    c.bits |= ctl[4 * (ns + s) + 3];
+    c.inner += st[4 * (ns + s)];
   }
-  HIPCHK(E.lead, hipStreamSynchronize(E.st));
-  for (int s = 0; s < E.nsys; ++s) {
-    stat0[s] += statb[s] + statt[s];
-    ctl3[s] |= ctlb[s];
-  }
-  return OV_OK;
+  if (E.sb[s].tb_stat) c.inner += st[4 * (2 * ns + s)];  // and of the true residuals
+  return c;
 }
 
 // Counters, shift residuals and control words of every entry: one fill kernel.
@@ -1309,45 +1376,25 @@ void zero_dev(const Engine& E, void* p, size_t bytes) {
   k_zero32<<<nb, 256, 0, E.st>>>((unsigned int*)p, n);
 }
 
-// ABI field pointers -> pack into the planar FP64 buffer chosen by `dst_of`.
-ov_status pack64(Engine& E, const std::vector<const void*>& src, std::vector<void*> dst) {
-  TRY(sync(E));  // the staging vector may still be read by an earlier copy
-  std::vector<void*>& h = E.hptrs;
-  h.assign(2 * E.nsys, nullptr);
-  for (int s = 0; s < E.nsys; ++s) {
-    h[s] = (void*)src[s];
-    h[E.nsys + s] = dst[s];
-  }
-  HIPCHK(E.lead, hipMemcpyAsync(E.ptrs, h.data(), sizeof(void*) * h.size(),
-                                hipMemcpyHostToDevice, E.st));
-  k_pack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(
-      tab(E, T_APPLY), E.bmap, E.nb_total, (const double2* const*)E.ptrs, E.ptrs + E.nsys, 1.0);
+// The caller's fields to their planar twins and back (E.io, in the uploaded tables).
+ov_status pack64(Engine& E) {
+  k_pack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return check_launch(E.lead);
 }
 
-ov_status unpack64(Engine& E, const std::vector<void*>& src, const std::vector<void*>& dst) {
-  TRY(sync(E));
-  std::vector<void*>& h = E.hptrs;
-  h.assign(2 * E.nsys, nullptr);
-  for (int s = 0; s < E.nsys; ++s) {
-    h[s] = src[s];
-    h[E.nsys + s] = dst[s];
-  }
-  HIPCHK(E.lead, hipMemcpyAsync(E.ptrs, h.data(), sizeof(void*) * h.size(),
-                                hipMemcpyHostToDevice, E.st));
-  k_unpack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(
-      tab(E, T_APPLY), E.bmap, E.nb_total, E.ptrs, (double2* const*)(E.ptrs + E.nsys));
+ov_status unpack64(Engine& E) {
+  k_unpack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return check_launch(E.lead);
 }
 
 // --------------------------------------------------------- apply / sign
-// Inputs were packed into x64 (planar FP64); result goes to r64 (planar FP64).
-ov_status run_apply(Engine& E, int op) {
-  E.htab.assign((size_t)T_NT * E.nsys, SysDev{});
+// Tables of an operator on x64 (planar FP64) with the result in r64.
+ov_status run_apply(Engine& E, int op, const void* phi) {
+  E.htab.assign((size_t)E.ntab * E.nsys, SysDev{});
   for (int s = 0; s < E.nsys; ++s) {
     SysBuf& b = E.sb[s];
     SysDev d = base_dev(b);
-    d.phi = (const double2*)nullptr;
+    d.phi = (const double2*)phi;
     d.basis = b.basis64;
     d.r = b.r64ms;
     SysDev d1 = d, d2 = d;
@@ -1355,7 +1402,7 @@ ov_status run_apply(Engine& E, int op) {
     d1.e_in = b.x64;
     d1.src = (op == OV_OP_DOV_DAG || op == OV_OP_M_DAG) ? (const void*)b.src64b
                                                         : (const void*)b.x64;
-    d1.e_out = (op == OV_OP_MDAGM) ? (void*)b.u64 : (void*)b.r64;
+    d1.e_out = (op == OV_OP_MDAGM) ? (void*)b.u64 : (void*)b.r64;  // H_W: x64 -> r64 too
     d1.e_out2 = (op == OV_OP_MDAGM) ? (void*)b.src64b : nullptr;
     d1.fft_tmp = b.src64b;  // momentum-space ops: transform scratch
     d2.fft_tmp = b.src64b;
@@ -1366,12 +1413,6 @@ ov_status run_apply(Engine& E, int op) {
     E.htab[(size_t)T_APPLY * E.nsys + s] = d1;
     E.htab[(size_t)T_APPLY2 * E.nsys + s] = d2;
   }
-  return upload_tables(E);
-}
-
-ov_status set_phi(Engine& E, const std::vector<const void*>& phi) {
-  for (int t = 0; t < T_NT; ++t)
-    for (int s = 0; s < E.nsys; ++s) E.htab[(size_t)t * E.nsys + s].phi = (const double2*)phi[s];
   return upload_tables(E);
 }
 
@@ -1562,7 +1603,7 @@ ov_status pc_masses(Engine& E, const std::vector<const void*>& phi, std::vector<
   ov_ctx* c = E.lead;
   const int ns = E.nsys;
   pcm.assign(ns, double2{0.0, 0.0});
-  E.htab.assign((size_t)T_NT * ns, SysDev{});
+  E.htab.assign((size_t)E.ntab * ns, SysDev{});
   for (int s = 0; s < ns; ++s) {
     SysDev d = base_dev(E.sb[s]);
     d.phi = (const double2*)phi[s];
@@ -1571,14 +1612,11 @@ ov_status pc_masses(Engine& E, const std::vector<const void*>& phi, std::vector<
   TRY(upload_tables(E));
   k_c_norm<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   TRY(check_launch(c));
+  k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_APPLY), ns, 4);
+  TRY(read_scalars(E));
   for (int s = 0; s < ns; ++s) {
     const SysBuf& b = E.sb[s];
-    std::vector<double> tmp(b.nblk);
-    HIPCHK(c, hipMemcpyAsync(tmp.data(), b.part_c, sizeof(double) * tmp.size(),
-                             hipMemcpyDeviceToHost, E.st));
-    TRY(sync(E));
-    double acc = 0.0;
-    for (double v : tmp) acc += v;
+    const double acc = c->pinned[(size_t)s * CG_NSLOT + CG_BB];
     const ov_params& p = b.ctx->p;
     const double rms = std::sqrt(acc / b.V);
     const double am = std::hypot(p.m_re, p.m_im);
@@ -1593,7 +1631,7 @@ ov_status build_solve_tables(Engine& E, const std::vector<const void*>& bvec,
   std::vector<double2> pcm;
   const bool rms_pc = E.pl.pc && E.lead->p.pc_mass == 1;
   if (rms_pc) TRY(pc_masses(E, phi, pcm));
-  E.htab.assign((size_t)T_NT * E.nsys, SysDev{});
+  E.htab.assign((size_t)E.ntab * E.nsys, SysDev{});
   E.hgwtab.assign(E.pl.gw ? 2 * (size_t)E.nsys : 0, SysDev{});
   E.htrgw.assign(E.pl.gwx ? 2 * (size_t)E.nsys : 0, SysDev{});
   for (int s = 0; s < E.nsys; ++s) {
@@ -1790,27 +1828,6 @@ ov_status set_flags(Engine& E, const std::vector<int>& cg, const std::vector<int
   HIPCHK(E.lead, hipMemcpyAsync(E.act_all, h, sizeof(int) * f.size(), hipMemcpyHostToDevice, E.st));
   E.last_flags = f;
   return OV_OK;
-}
-
-// CG scalars, multi-shift counters, shift residuals and control words of every entry
-// (the engine's contiguous scalar block) to the pinned host copy, then synchronise.
-ov_status read_scalars(Engine& E) {
-  static_assert(sizeof(long long) == sizeof(double), "counters share the scalar block");
-  HIPCHK(E.lead, hipMemcpyAsync(E.lead->pinned, E.cg_all,
-                                sizeof(double) * CG_NSLOT * E.nsys + sizeof(int) * E.ctl_words,
-                                hipMemcpyDeviceToHost, E.st));
-  return sync(E);
-}
-
-// Sticky multi-shift error bits (h_ctl[3]: bit 1 breakdown, bit 2 not converged within
-// the launched iterations or the basis) of system s's entries, from the last
-// read_scalars.
-int sticky_bits(const Engine& E, int s) {
-  const int* ctl = (const int*)((const double*)E.lead->pinned + (size_t)CG_NSLOT * E.nsys +
-                                (size_t)18 * E.nsys);
-  int b = 0;
-  for (int e = 0; e < 3; ++e) b |= ctl[(size_t)(e * E.nsys + s) * 4 + 3];
-  return b;
 }
 
 // Clear every entry's control words before multi-shift solves that are checked on their own.
@@ -2073,6 +2090,7 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
   const int max_outer = E.max_outer > 0 ? E.max_outer : P.max_outer;
   Range range(sizeof(R) == sizeof(double) ? "ov solve engine FP64" : "ov solve engine mixed");
   TRY((build_solve_tables<R>(E, bvec, phi)));
+  if (E.guess) TRY(pack64(E));
   pcg_table(E);
   TRY(reset_stats(E));
   std::vector<int> fcg(ns, 1), fru(ns, 1);
@@ -2091,17 +2109,10 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
   }
   // |x0|^2 -> part_b via prep on x64 (src = x64 in T_CG)
   k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 0);
-  std::vector<double> x0n(ns);
-  for (int s = 0; s < ns; ++s) {
-    std::vector<double> tmp(E.sb[s].nblk);
-    HIPCHK(c, hipMemcpyAsync(tmp.data(), E.sb[s].part_b, sizeof(double) * tmp.size(),
-                             hipMemcpyDeviceToHost, E.st));
-    TRY(sync(E));
-    double acc = 0;
-    for (double v : tmp) acc += v;
-    x0n[s] = acc;
-  }
+  k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 13);
   TRY(read_scalars(E));
+  std::vector<double> x0n(ns);
+  for (int s = 0; s < ns; ++s) x0n[s] = c->pinned[(size_t)s * CG_NSLOT + CG_RTRUE];
   // rmax: residual norm at the last restart (the recursion's |r| is slot CG_R2,
   // with or without the preconditioner).
   std::vector<double> bn(ns), rmax(ns);
@@ -2373,21 +2384,19 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
 }
 
 
+// Statistics from the last read_scalars.
 void fill_stats(ov_stats* st, int n, Engine* E, const SolveOut* so, double secs, int prec_bytes) {
   if (!st) return;
-  std::vector<int> ctl;
-  std::vector<long long> st0;
-  std::vector<double> ds;
-  if (E) read_ctl(*E, ctl, st0, ds);
   for (int s = 0; s < n; ++s) {
     ov_stats& o = st[s];
     std::memset(&o, 0, sizeof(o));
     if (E) {
-      o.inner_iters = st0[s];
-      o.stencil_apps = 2 * st0[s];
-      o.max_shift_res = ds[s];
+      const SysCtl k = sys_ctl(*E, s);
+      o.inner_iters = k.inner;
+      o.stencil_apps = 2 * k.inner;
+      o.max_shift_res = k.shift_res;
       const double V = E->sb[s].V;
-      o.model_bytes = 7.0 * (double)st0[s] * 4.0 * V * prec_bytes;
+      o.model_bytes = 7.0 * (double)k.inner * 4.0 * V * prec_bytes;
     }
     if (so) {
       o.outer_iters = so->outer[s];
@@ -2409,7 +2418,7 @@ ov_status tune_run(ov_ctx* c, int nrhs, int iters, float* us) {
   const bool fp32 = sizeof(R) == sizeof(float);
   E.no_res = true;  // the launch shape is the per-pass kernels'
   TRY(engine_init(E, v, true, fp32, solve_tol64(c), fp32 ? c->p.mixed_inner_tol : c->p.inner_tol));
-  E.htab.assign((size_t)T_NT * nrhs, SysDev{});
+  E.htab.assign((size_t)E.ntab * nrhs, SysDev{});
   for (int s = 0; s < nrhs; ++s) {
     SysBuf& b = E.sb[s];
     SysDev d = base_dev(b);
@@ -2541,12 +2550,11 @@ ov_status ov_ctx_create(const ov_params* p, void* hip_stream, ov_ctx** out) {
   }
   // set-up of the no-allocation entry point: the scratch array's device address and
   // host staging for kNoAllocSystems systems
-  if (noalloc_scratch_setup(c) != OV_OK || ensure_pinned(c, kNoAllocSystems) != OV_OK) {
+  if (noalloc_scratch_setup(c) != OV_OK || host_setup(c) != OV_OK) {
     g_err = c->err;
     (void)hipEventDestroy(c->ev_in);
     (void)hipStreamDestroy(c->priv);
-    if (c->pinned) (void)hipHostFree(c->pinned);
-    if (c->pinned_flags) (void)hipHostFree(c->pinned_flags);
+    if (c->host_block) (void)hipHostFree(c->host_block);
     delete c;
     return OV_ERR_DEVICE;
   }
@@ -2573,14 +2581,15 @@ ov_status ov_ctx_destroy(ov_ctx* c) {
   clear_graphs(c);
   if (c->ev_res) (void)hipEventDestroy(c->ev_res);
   if (c->res_sh) (void)hipFree(c->res_sh);
-  if (c->res_abort) (void)hipHostFree(c->res_abort);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->ev_in) (void)hipEventDestroy(c->ev_in);
   if (c->priv) (void)hipStreamDestroy(c->priv);
   if (c->own_ws) (void)hipFree(c->own_ws);
   if (c->ts_dev) (void)hipFree(c->ts_dev);
-  if (c->pinned) (void)hipHostFree(c->pinned);
-  if (c->pinned_flags) (void)hipHostFree(c->pinned_flags);
+  host_free(c, c->pinned);
+  host_free(c, c->pinned_flags);
+  host_free(c, c->stage);
+  if (c->host_block) (void)hipHostFree(c->host_block);
   delete c;
   return OV_OK;
 }
@@ -2673,37 +2682,20 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
   TRY(reset_stats(E));
-  const int V = E.sb[0].V;
-  std::vector<const void*> src(nrhs), ph(nrhs, phi);
-  std::vector<void*> dst(nrhs), res(nrhs), outs(nrhs);
-  for (int r = 0; r < nrhs; ++r) {
-    src[r] = (const char*)in + (size_t)r * V * 4 * sizeof(double2);
-    outs[r] = (char*)out + (size_t)r * V * 4 * sizeof(double2);
-    dst[r] = E.sb[r].x64;
-    res[r] = E.sb[r].r64;
-  }
-  TRY(run_apply(E, op));
-  TRY(set_phi(E, ph));
-  TRY(pack64(E, src, dst));
-  if (op == OV_OP_HW) {
-    // plain stencil: e_in = x64, e_out = r64
-    for (int s = 0; s < nrhs; ++s) {
-      E.htab[(size_t)T_APPLY * nrhs + s].e_in = E.sb[s].x64;
-      E.htab[(size_t)T_APPLY * nrhs + s].e_out = E.sb[s].r64;
-    }
-    TRY(upload_tables(E));
-  }
+  const size_t vb = (size_t)E.sb[0].V * 4 * sizeof(double2);
+  E.io.resize(nrhs);
+  for (int r = 0; r < nrhs; ++r)
+    E.io[r] = {(const char*)in + r * vb, E.sb[r].x64, E.sb[r].r64, (char*)out + r * vb};
+  TRY(run_apply(E, op, phi));
+  TRY(pack64(E));
   TRY(apply_sequence(E, op));
-  TRY(unpack64(E, res, outs));
-  TRY(sync(E));
-  std::vector<int> ctl;
-  std::vector<long long> st0;
-  std::vector<double> ds;
-  TRY(read_ctl(E, ctl, st0, ds));
+  TRY(unpack64(E));
+  TRY(read_scalars(E));
   ov_status rc = OV_OK;
   for (int s = 0; s < nrhs; ++s) {
-    if (ctl[s] & (1 << 1)) rc = OV_ERR_BREAKDOWN;
-    else if ((ctl[s] & (1 << 2)) && rc == OV_OK) rc = OV_ERR_NOT_CONVERGED;
+    const int bits = sys_ctl(E, s).bits;
+    if (bits & (1 << 1)) rc = OV_ERR_BREAKDOWN;
+    else if ((bits & (1 << 2)) && rc == OV_OK) rc = OV_ERR_NOT_CONVERGED;
   }
   if (rc == OV_ERR_BREAKDOWN) c->err = "multi-shift breakdown (non-finite input?)";
   if (rc == OV_ERR_NOT_CONVERGED) c->err = "multi-shift did not converge within its basis";
@@ -2767,26 +2759,16 @@ static ov_status solve_systems(std::vector<ov_ctx*>& sysctx, std::vector<const v
   TRY(engine_init(E, sysctx, true, mixed, solve_tol64(c), tolR));
   const int ns = E.nsys;
   E.force_fallback = mixed && force_fallback_env();
-  // pack the guesses into x64 (needs a geometry table)
-  E.htab.assign((size_t)T_NT * ns, SysDev{});
-  for (int s = 0; s < ns; ++s) E.htab[(size_t)T_APPLY * ns + s] = base_dev(E.sb[s]);
-  TRY(upload_tables(E));
-  std::vector<void*> x64(ns);
-  std::vector<const void*> xin(ns);
-  for (int s = 0; s < ns; ++s) {
-    x64[s] = E.sb[s].x64;
-    xin[s] = xv[s];
-  }
-  TRY(pack64(E, xin, x64));
+  E.io.resize(ns);
+  for (int s = 0; s < ns; ++s) E.io[s] = {xv[s], E.sb[s].x64, E.sb[s].x64, xv[s]};
+  E.guess = true;
   SolveOut so;
   const double delta = c->p.reliable_delta;
   ov_status rc = mixed ? solve_engine<float>(E, bv, phv, tolR, delta, so)
                        : solve_engine<double>(E, bv, phv, tolR, delta, so);
   if (rc != OV_OK && rc != OV_ERR_NOT_CONVERGED) return rc;
-  std::vector<void*> x64v(ns);
-  for (int s = 0; s < ns; ++s) x64v[s] = E.sb[s].x64;
-  TRY(unpack64(E, x64v, xv));
-  TRY(sync(E));
+  TRY(unpack64(E));
+  TRY(read_scalars(E));
   fill_stats(st, ns, &E, &so, now_s() - t0, mixed ? 8 : 16);
   if (rc != OV_OK) return rc;  // x holds the best iterate; err says why
   // Systems whose mixed-precision cycles stagnated: the FP64 solver (fixed inner
@@ -2801,30 +2783,26 @@ static ov_status solve_systems(std::vector<ov_ctx*>& sysctx, std::vector<const v
   if (!fb.empty() && used < c->p.max_outer) {
     if (ov_log()) std::fprintf(stderr, "[ov] %zu system(s) handed to the FP64 solver\n", fb.size());
     std::vector<ov_ctx*> c2;
-    std::vector<const void*> b2, p2, x2in;
+    std::vector<const void*> b2, p2;
     std::vector<void*> x2;
     for (int s : fb) {
       c2.push_back(sysctx[s]);
       b2.push_back(bv[s]);
       p2.push_back(phv[s]);
       x2.push_back(xv[s]);
-      x2in.push_back(xv[s]);
     }
     Engine F;
     TRY(engine_init(F, c2, true, false, solve_tol64(c), c->p.inner_tol));
     F.no_relax = true;
     F.max_outer = c->p.max_outer - used;
-    F.htab.assign((size_t)T_NT * F.nsys, SysDev{});
-    for (int k = 0; k < F.nsys; ++k) F.htab[(size_t)T_APPLY * F.nsys + k] = base_dev(F.sb[k]);
-    TRY(upload_tables(F));
-    std::vector<void*> fx(F.nsys);
-    for (int k = 0; k < F.nsys; ++k) fx[k] = F.sb[k].x64;
-    TRY(pack64(F, x2in, fx));
+    F.io.resize(F.nsys);
+    for (int k = 0; k < F.nsys; ++k) F.io[k] = {x2[k], F.sb[k].x64, F.sb[k].x64, x2[k]};
+    F.guess = true;
     SolveOut so2;
     rc = solve_engine<double>(F, b2, p2, c->p.inner_tol, delta, so2);
     if (rc != OV_OK && rc != OV_ERR_NOT_CONVERGED) return rc;
-    TRY(unpack64(F, fx, x2));
-    TRY(sync(F));
+    TRY(unpack64(F));
+    TRY(read_scalars(F));
     std::vector<ov_stats> st2(F.nsys);
     fill_stats(st2.data(), F.nsys, &F, &so2, now_s() - t0, 16);
     for (int k = 0; k < F.nsys; ++k) {
@@ -2948,7 +2926,7 @@ static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const voi
       return OV_ERR_NOT_CONVERGED;
     }
   // Y = M X (FP64, recomputed: no shifted vector was kept)
-  E.htab.assign((size_t)T_NT * nrhs, SysDev{});
+  E.htab.assign((size_t)E.ntab * nrhs, SysDev{});
   for (int s = 0; s < nrhs; ++s) {
     SysBuf& b = E.sb[s];
     SysDev d = base_dev(b);
@@ -2979,20 +2957,14 @@ static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const voi
   // G summed over right-hand sides in order (one launch over the sites)
   k_force<<<E.sb[0].nblk, c->block, 0, E.st>>>(tab(E, T_APPLY), nrhs, E.sb[0].nblk,
                                                (double2*)grad_phi);
+  k_cg_scalar<<<nrhs, 256, 0, E.st>>>(tab(E, T_APPLY), nrhs, 4);  // S_r -> BB
   TRY(read_scalars(E));
   if (!E.pl.fft) {
     int bits = 0;
     for (int s = 0; s < nrhs; ++s) bits |= sticky_bits(E, s);
     TRY(sticky_status(c, bits, "ov_force, Y = M X"));
   }
-  for (int s = 0; s < nrhs; ++s) {
-    std::vector<double> tmp(E.sb[s].nblk);
-    HIPCHK(c, hipMemcpy(tmp.data(), E.sb[s].part_c, sizeof(double) * tmp.size(),
-                        hipMemcpyDeviceToHost));
-    double acc = 0;
-    for (double v : tmp) acc += v;
-    S_host[s] = acc;
-  }
+  for (int s = 0; s < nrhs; ++s) S_host[s] = c->pinned[(size_t)s * CG_NSLOT + CG_BB];
   fill_stats(st, nrhs, &E, &so, now_s() - t0, (mixed && !fell_back) ? 8 : 16);
   if (st && fell_back)
     for (int r = 0; r < nrhs; ++r) st[r].fp64_fallback = 1;
@@ -3208,21 +3180,20 @@ static ov_status shifted_solve_acc(ov_ctx* c, double sigma, double alpha,
     Engine F;
     TRY(engine_init(F, sc, true, m, solve_tol64(c), tolR));
     F.shift = sigma;
+    F.io.resize(ns);
+    for (int r = 0; r < ns; ++r) F.io[r] = {nullptr, nullptr, F.sb[r].x64, outs[r]};
     F.no_relax = attempt == 1;
     for (int r = 0; r < ns; ++r) zero_dev(F, F.sb[r].x64, vb);
     SolveOut so;
     ov_status rc = m ? solve_engine<float>(F, bv, ph, tolR, c->p.reliable_delta, so)
                      : solve_engine<double>(F, bv, ph, tolR, c->p.reliable_delta, so);
     if (rc != OV_OK) return rc;
-    std::vector<int> ctl;
-    std::vector<long long> st0;
-    std::vector<double> ds;
-    TRY(read_ctl(F, ctl, st0, ds));
+    TRY(read_scalars(F));
     bool fell_back = false;
     for (int r = 0; r < ns; ++r) {
       outer[r] += so.outer[r];
       ru[r] += so.ru[r];
-      inner[r] += st0[r];
+      inner[r] += sys_ctl(F, r).inner;
       fell_back |= so.fallback[r] != 0;
     }
     if (fell_back && m) continue;
@@ -3231,17 +3202,7 @@ static ov_status shifted_solve_acc(ov_ctx* c, double sigma, double alpha,
         c->err = "shifted solve of the rational layer did not converge within max_outer";
         return OV_ERR_NOT_CONVERGED;
       }
-    TRY(sync(F));  // the pointer staging feeds the copy below
-    std::vector<void*>& h = F.hptrs;
-    h.assign(2 * ns, nullptr);
-    for (int r = 0; r < ns; ++r) {
-      h[r] = F.sb[r].x64;
-      h[ns + r] = outs[r];
-    }
-    HIPCHK(c, hipMemcpyAsync(F.ptrs, h.data(), sizeof(void*) * h.size(), hipMemcpyHostToDevice,
-                             F.st));
-    k_unpack_axpy<<<F.nb_total, c->block, 0, F.st>>>(tab(F, T_APPLY), F.bmap, F.nb_total, F.ptrs,
-                                                     (double2* const*)(F.ptrs + ns), alpha);
+    k_unpack_axpy<<<F.nb_total, c->block, 0, F.st>>>(tab(F, T_APPLY), F.bmap, F.nb_total, alpha);
     return sync(F);
   }
   c->err = "shifted solve of the rational layer: FP64 retry did not finish";
@@ -3262,7 +3223,7 @@ static ov_status rational_impl(ov_ctx* c, double a0, int n, const double* alpha,
                     sizeof(double2);
   std::vector<ov_ctx*> sc(nrhs, c);
   std::vector<const void*> bv(nrhs), ph(nrhs, phi);
-  std::vector<void*> ov(nrhs), r64(nrhs);
+  std::vector<void*> ov(nrhs);
   for (int r = 0; r < nrhs; ++r) {
     bv[r] = (const char*)in + r * vb;
     ov[r] = (char*)out + r * vb;
@@ -3282,17 +3243,17 @@ static ov_status rational_impl(ov_ctx* c, double a0, int n, const double* alpha,
   if (!al_hi.empty()) {
     Engine E;
     TRY(engine_init(E, sc, true, false, solve_tol64(c), c->p.inner_tol, (int)al_hi.size()));
+    E.io.resize(nrhs);
+    for (int r = 0; r < nrhs; ++r) E.io[r] = {nullptr, nullptr, E.sb[r].r64, ov[r]};
     std::vector<int> iters;
     TRY(rational_core(c, E, a0, (int)al_hi.size(), al_hi.data(), be_hi.data(), bv, ph, iters));
-    for (int r = 0; r < nrhs; ++r) r64[r] = E.sb[r].r64;
-    TRY(unpack64(E, r64, ov));
-    TRY(sync(E));
-    std::vector<int> ctl;
-    std::vector<long long> st0;
-    TRY(read_ctl(E, ctl, st0, shift_res));
+    TRY(unpack64(E));
+    TRY(read_scalars(E));
     for (int r = 0; r < nrhs; ++r) {
+      const SysCtl k = sys_ctl(E, r);
       outer[r] += iters[r];
-      inner[r] += st0[r];
+      inner[r] += k.inner;
+      shift_res[r] = k.shift_res;
     }
   } else {  // out = a0 in, ordered after the caller's stream like every other launch
     HIPCHK(c, hipEventRecord(c->ev_in, c->stream));
@@ -3441,7 +3402,7 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   std::vector<ov_ctx*> v(1, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
   SysBuf& b = E.sb[0];
-  E.htab.assign((size_t)T_NT, SysDev{});
+  E.htab.assign((size_t)E.ntab, SysDev{});
   SysDev d = base_dev(b);
   d.phi = (const double2*)phi;
   d.e_in = b.x64;      // packed planes phi, W', conj W'
@@ -3453,12 +3414,9 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   launch_sym<double>(E, T_APPLY, SYM_BOSON);
   k_boson_finish<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
                                                     (double2*)G, (double2*)F);
-  TRY(sync(E));
-  std::vector<double> tmp(b.nblk);
-  HIPCHK(c, hipMemcpy(tmp.data(), b.part_c, sizeof(double) * tmp.size(), hipMemcpyDeviceToHost));
-  double acc = 0;
-  for (double x : tmp) acc += x;
-  *S_host = acc;
+  k_cg_scalar<<<1, 256, 0, E.st>>>(tab(E, T_APPLY), 1, 4);  // S_B -> BB
+  TRY(read_scalars(E));
+  *S_host = c->pinned[CG_BB];
   return OV_OK;
 }
 
@@ -3553,7 +3511,7 @@ static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats*
   std::vector<ov_ctx*> v(1, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
   TRY(reset_stats(E));
-  TRY(run_apply(E, OV_OP_DOV));  // e_in = x64, result in r64
+  TRY(run_apply(E, OV_OP_DOV, nullptr));  // e_in = x64, result in r64
   SysBuf& b = E.sb[0];
   const size_t V = b.V;
   // unit point source at the origin: x64 = 0, plane `spin` of site 0 = 1
@@ -3574,14 +3532,10 @@ static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats*
   TRY(check_launch(c));
   std::vector<double> h(rmax + 1);
   HIPCHK(c, hipMemcpyAsync(h.data(), fd, sizeof(double) * h.size(), hipMemcpyDeviceToHost, E.st));
-  TRY(sync(E));
+  TRY(read_scalars(E));
   for (int r = 0; r < nr; ++r) f[r] = r <= rmax ? h[r] : 0.0;
-  std::vector<int> ctl;
-  std::vector<long long> st0;
-  std::vector<double> ds;
-  TRY(read_ctl(E, ctl, st0, ds));
   fill_stats(st, 1, &E, nullptr, now_s() - t0, 16);
-  if (ctl[0] & (1 << 2)) {
+  if (sys_ctl(E, 0).bits & (1 << 2)) {
     c->err = "multi-shift did not converge within its basis";
     return OV_ERR_NOT_CONVERGED;
   }
@@ -3600,23 +3554,18 @@ ov_status ov_pack(ov_ctx* c, int prec, void* dst, const void* src, int nrhs) {
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
-  E.htab.assign((size_t)T_NT * nrhs, SysDev{});
+  E.htab.assign((size_t)E.ntab * nrhs, SysDev{});
   for (int s = 0; s < nrhs; ++s) E.htab[(size_t)T_APPLY * nrhs + s] = base_dev(E.sb[s]);
-  TRY(upload_tables(E));
   const size_t V = E.sb[0].V;
-  std::vector<void*>& h = E.hptrs;
-  h.assign(2 * nrhs, nullptr);
-  for (int r = 0; r < nrhs; ++r) {
-    h[r] = (char*)src + r * V * 4 * sizeof(double2);
-    h[nrhs + r] = (char*)dst + r * V * 4 * (prec ? sizeof(float2) : sizeof(double2));
-  }
-  HIPCHK(c, hipMemcpyAsync(E.ptrs, h.data(), sizeof(void*) * h.size(), hipMemcpyHostToDevice, E.st));
+  E.io.resize(nrhs);
+  for (int r = 0; r < nrhs; ++r)
+    E.io[r] = {(const char*)src + r * V * 4 * sizeof(double2),
+               (char*)dst + r * V * 4 * (prec ? sizeof(float2) : sizeof(double2)), nullptr, nullptr};
+  TRY(upload_tables(E));
   if (prec)
-    k_pack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
-                                                     (const double2* const*)E.ptrs, E.ptrs + nrhs, 1.0);
+    k_pack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   else
-    k_pack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
-                                                      (const double2* const*)E.ptrs, E.ptrs + nrhs, 1.0);
+    k_pack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return sync(E);
 }
 
@@ -3625,23 +3574,19 @@ ov_status ov_unpack(ov_ctx* c, int prec, void* dst, const void* src, int nrhs) {
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
-  E.htab.assign((size_t)T_NT * nrhs, SysDev{});
+  E.htab.assign((size_t)E.ntab * nrhs, SysDev{});
   for (int s = 0; s < nrhs; ++s) E.htab[(size_t)T_APPLY * nrhs + s] = base_dev(E.sb[s]);
-  TRY(upload_tables(E));
   const size_t V = E.sb[0].V;
-  std::vector<void*>& h = E.hptrs;
-  h.assign(2 * nrhs, nullptr);
-  for (int r = 0; r < nrhs; ++r) {
-    h[r] = (char*)src + r * V * 4 * (prec ? sizeof(float2) : sizeof(double2));
-    h[nrhs + r] = (char*)dst + r * V * 4 * sizeof(double2);
-  }
-  HIPCHK(c, hipMemcpyAsync(E.ptrs, h.data(), sizeof(void*) * h.size(), hipMemcpyHostToDevice, E.st));
+  E.io.resize(nrhs);
+  for (int r = 0; r < nrhs; ++r)
+    E.io[r] = {nullptr, nullptr,
+               (char*)const_cast<void*>(src) + r * V * 4 * (prec ? sizeof(float2) : sizeof(double2)),
+               (char*)dst + r * V * 4 * sizeof(double2)};
+  TRY(upload_tables(E));
   if (prec)
-    k_unpack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, E.ptrs,
-                                                       (double2* const*)(E.ptrs + nrhs));
+    k_unpack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   else
-    k_unpack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, E.ptrs,
-                                                        (double2* const*)(E.ptrs + nrhs));
+    k_unpack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return sync(E);
 }
 
@@ -3688,6 +3633,7 @@ ov_status ov_stencil_bench(ov_ctx* c, int prec, void* out, const void* in, int n
     return OV_ERR_INVALID_ARG;
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
+  std::vector<int> hbmap;
   // only tables / partials are needed: a tiny plan
   E.ctxs = v;
   E.nsys = nrhs;
@@ -3722,9 +3668,9 @@ ov_status ov_stencil_bench(ov_ctx* c, int prec, void* out, const void* in, int n
     for (int s = 0; s < nrhs; ++s) E.sb[s].part_c = (double*)bp.take(sizeof(double) * E.sb[s].nblk);
     E.tables = (SysDev*)bp.take(sizeof(SysDev) * nrhs);
     E.bmap = (int*)bp.take(sizeof(int) * (size_t)blk);
-    E.hbmap.assign(blk, 0);
+    hbmap.assign(blk, 0);
     for (int s = 0; s < nrhs; ++s)
-      for (int b = 0; b < E.sb[s].nblk; ++b) E.hbmap[E.sb[s].blk0 + b] = s;
+      for (int b = 0; b < E.sb[s].nblk; ++b) hbmap[E.sb[s].blk0 + b] = s;
   }
   const size_t V = E.sb[0].V;
   const size_t es = prec ? sizeof(float2) : sizeof(double2);
@@ -3737,7 +3683,7 @@ ov_status ov_stencil_bench(ov_ctx* c, int prec, void* out, const void* in, int n
   }
   HIPCHK(c, hipMemcpyAsync(E.tables, E.htab.data(), sizeof(SysDev) * nrhs, hipMemcpyHostToDevice,
                            E.st));
-  HIPCHK(c, hipMemcpyAsync(E.bmap, E.hbmap.data(), sizeof(int) * E.hbmap.size(),
+  HIPCHK(c, hipMemcpyAsync(E.bmap, hbmap.data(), sizeof(int) * hbmap.size(),
                            hipMemcpyHostToDevice, E.st));
   HIPCHK(c, hipStreamSynchronize(E.st));
   hipEvent_t e0, e1;
