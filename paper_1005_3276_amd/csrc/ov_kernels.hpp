@@ -397,6 +397,141 @@ __global__ void __launch_bounds__(256) k_hw_zm(const SysDev* __restrict__ sys, d
   }
 }
 
+// ---------------------------------------------------- H_W on the caller's fields
+// io_out = H_W io_in on complex128 fields with the spin innermost (ov_apply OV_OP_HW): the
+// stencil reads and writes the caller's layout itself, one pass over memory instead of
+// pack, stencil and unpack.  A site is 64 contiguous bytes, so a wave's four loads of a
+// component each share their cache lines.  Bound by memory: 128 bytes per site; 48 fields of
+// 16^4 take 80 us (5.0 TB/s; pack, k_hw and unpack took 92 + 127 + 155).
+__device__ __forceinline__ void load_io(const double2* __restrict__ f, int i, double2 v[4]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) v[s] = ldg2<double>(f, (size_t)i * 4 + s);
+}
+
+// Any lattice: one site per thread, nine spinors through the caches.
+__global__ void __launch_bounds__(256) k_hw_io(const SysDev* __restrict__ sys,
+                                               const int* __restrict__ bmap, int nb_total,
+                                               double diag) {
+  const int L = xcd_logical_block(nb_total);
+  const SysDev& S = sys[bmap[L]];
+  const Geo g = S.g;
+  const int lb = L - S.blk0;
+  const double2* in = S.io_in;
+  double2* out = S.io_out;
+  const int XY = g.X * g.Y, XYZ = XY * g.Z;
+  const int i0 = lb * S.spb;
+  const int i1 = min(g.V, i0 + S.spb);
+  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+    int r = i;
+    const int x = r % g.X; r /= g.X;
+    const int y = r % g.Y; r /= g.Y;
+    const int z = r % g.Z;
+    const int t = r / g.Z;
+    Nbr<double> nb;
+    load_io(in, i, nb.c);
+    load_io(in, (x + 1 < g.X) ? i + 1 : i + 1 - g.X, nb.xf);
+    load_io(in, (x > 0) ? i - 1 : i - 1 + g.X, nb.xb);
+    load_io(in, (y + 1 < g.Y) ? i + g.X : i + g.X - XY, nb.yf);
+    load_io(in, (y > 0) ? i - g.X : i - g.X + XY, nb.yb);
+    load_io(in, (z + 1 < g.Z) ? i + XY : i + XY - XYZ, nb.zf);
+    load_io(in, (z > 0) ? i - XY : i - XY + XYZ, nb.zb);
+    load_io(in, (t + 1 < g.T) ? i + XYZ : i + XYZ - g.V, nb.tf);
+    load_io(in, (t > 0) ? i - XYZ : i - XYZ + g.V, nb.tb);
+    double2 o[4];
+    hw_compute<double>(nb, g, i, diag, o);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) stg2<double>(out, (size_t)i * 4 + k, o[k]);
+  }
+}
+
+// z-marching form (k_hw_zm): xy planes of at most 256 sites, ZC planes per workgroup, every
+// system on one lattice.  The results of a plane go through LDS, so that a wave stores
+// whole lines.
+template <int ZC>
+__global__ void __launch_bounds__(256) k_hw_io_zm(const SysDev* __restrict__ sys, double diag) {
+  constexpr int P = 257;  // plane pitch: the transposed reads of a site fall on four banks
+  __shared__ double2 sh[4 * P];
+  const Geo g = sys[0].g;
+  const int X = g.X, Y = g.Y, Z = g.Z, T = g.T, V = g.V;
+  const int XY = X * Y, XYZ = XY * Z;
+  const int nzc = Z / ZC;
+  const int b = xcd_logical_block(gridDim.x);
+  const SysDev& S = sys[b / (T * nzc)];
+  const int t = b % T;  // time slices fastest, as in k_hw_zm in FP64
+  const int z0 = ((b / T) % nzc) * ZC;
+  const double2* in = S.io_in;
+  double2* out = S.io_out;
+  const int j = threadIdx.x;
+  const bool on = j < XY;
+  const int x = on ? j % X : 0, y = on ? j / X : 0;
+  const int tf_off = (t + 1 < T) ? XYZ : XYZ - V;
+  const int tb_off = (t > 0) ? -XYZ : V - XYZ;
+  const int jxf = y * X + ((x + 1 < X) ? x + 1 : 0);
+  const int jxb = y * X + ((x > 0) ? x - 1 : X - 1);
+  const int jyf = ((y + 1 < Y) ? y + 1 : 0) * X + x;
+  const int jyb = ((y > 0) ? y - 1 : Y - 1) * X + x;
+  auto site = [&](int z) { return j + XY * ((z < 0 ? z + Z : (z >= Z ? z - Z : z)) + Z * t); };
+  Nbr<double> nb;
+  double2 next2[4], tf2[4], tb2[4];
+  if (on) {
+    load_io(in, site(z0 - 1), nb.zb);
+    load_io(in, site(z0), nb.c);
+    load_io(in, site(z0 + 1), nb.zf);
+    load_io(in, site(z0) + tf_off, nb.tf);
+    load_io(in, site(z0) + tb_off, nb.tb);
+  }
+#pragma unroll
+  for (int zi = 0; zi < ZC; ++zi) {
+    const int z = z0 + zi;
+    if (on && zi + 1 < ZC) {
+      load_io(in, site(z + 2), next2);
+      load_io(in, site(z + 1) + tf_off, tf2);
+      load_io(in, site(z + 1) + tb_off, tb2);
+    }
+    if (zi > 0) __syncthreads();  // the previous plane's results have been stored
+    if (on) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sh[q * P + j] = nb.c[q];
+    }
+    __syncthreads();
+    double2 o[4];
+    if (on) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        nb.xf[q] = sh[q * P + jxf];
+        nb.xb[q] = sh[q * P + jxb];
+        nb.yf[q] = sh[q * P + jyf];
+        nb.yb[q] = sh[q * P + jyb];
+      }
+      hw_compute<double>(nb, g, site(z), diag, o);
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sh[q * P + j] = o[q];
+    }
+    __syncthreads();
+    double2* plane = out + (size_t)4 * XY * (z + Z * t);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = q * 256 + j;
+      if (e < 4 * XY) {
+        const double2 v = sh[(e & 3) * P + (e >> 2)];
+        const ev2<double> w = {v.x, v.y};
+        __builtin_nontemporal_store(w, (OV_GLOBAL ev2<double>*)(plane + e));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      nb.zb[q] = nb.c[q];
+      nb.c[q] = nb.zf[q];
+      nb.zf[q] = next2[q];
+      nb.tf[q] = tf2[q];
+      nb.tb[q] = tb2[q];
+    }
+  }
+}
+
 // H_W of f on the sites of a workgroup that owns zc consecutive z planes of one
 // time slice (X Y == blockDim.x; the block's sites i0 .. i0 + zc X Y - 1, zc
 // dividing Z), in the z-marching order of k_hw_zm: plane z below and above in

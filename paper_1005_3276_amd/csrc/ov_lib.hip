@@ -1416,7 +1416,29 @@ ov_status run_apply(Engine& E, int op, const void* phi) {
   return upload_tables(E);
 }
 
-ov_status apply_sequence(Engine& E, int op) {
+// H_W on the caller's fields (every system of an operator call is on one lattice).  The
+// marching form reads a plane's neighbours once, from registers and LDS, but holds 228
+// VGPRs, so it needs planes that fill its 256 threads and three workgroups per CU: whole
+// calls, marching against plain, 16^4: 4 systems (256 workgroups) 64 against 59 us, 12
+// (768) 89 against 103, 48 174 against 268; 6x22 planes, 12 systems 78 against 101; 4x4
+// planes, 40 systems of 4^2x24x48 184 against 120.
+void launch_hw_io(const Engine& E, double diag) {
+  const int* d = E.lead->p.dims;
+  const int plane = d[0] * d[1];
+  const int zc = d[2] % 4 == 0 ? 4 : 2;
+  const long nzm = (long)E.nsys * d[3] * (d[2] / zc);
+  const SysDev* T = tab(E, T_APPLY);
+  if (plane >= 128 && plane <= 256 && nzm >= 768) {
+    if (zc == 4)
+      k_hw_io_zm<4><<<nzm, 256, 0, E.st>>>(T, diag);
+    else
+      k_hw_io_zm<2><<<nzm, 256, 0, E.st>>>(T, diag);
+  } else {
+    k_hw_io<<<E.nb_total, E.lead->block, 0, E.st>>>(T, E.bmap, E.nb_total, diag);
+  }
+}
+
+ov_status apply_sequence(Engine& E, int op, bool direct) {
   const ov_ctx* c = E.lead;
   const double diag = 4.0 - c->p.M0;
   if (c->p.dirac != OV_DIRAC_OVERLAP_MS && op >= OV_OP_DOV && op <= OV_OP_MDAGM) {
@@ -1447,8 +1469,11 @@ ov_status apply_sequence(Engine& E, int op) {
     return check_launch(E.lead);
   }
   switch (op) {
-    case OV_OP_HW:
-      k_hw<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, diag, 0);
+    case OV_OP_HW:  // in place, the stencil reads a planar copy
+      if (direct)
+        launch_hw_io(E, diag);
+      else
+        k_hw<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, diag, 0);
       break;
     case -1:  // sign
       k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
@@ -2687,9 +2712,12 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   for (int r = 0; r < nrhs; ++r)
     E.io[r] = {(const char*)in + r * vb, E.sb[r].x64, E.sb[r].r64, (char*)out + r * vb};
   TRY(run_apply(E, op, phi));
-  TRY(pack64(E));
-  TRY(apply_sequence(E, op));
-  TRY(unpack64(E));
+  // H_W works on the caller's fields themselves, unless they overlap
+  const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
+  const bool direct = op == OV_OP_HW && (a > b ? a - b : b - a) >= nrhs * vb;
+  if (!direct) TRY(pack64(E));
+  TRY(apply_sequence(E, op, direct));
+  if (!direct) TRY(unpack64(E));
   TRY(read_scalars(E));
   ov_status rc = OV_OK;
   for (int s = 0; s < nrhs; ++s) {
@@ -3519,7 +3547,7 @@ static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats*
   static const double2 one = {1.0, 0.0};
   HIPCHK(c, hipMemcpyAsync(b.x64 + (size_t)spin * V, &one, sizeof(double2),
                            hipMemcpyHostToDevice, E.st));
-  TRY(apply_sequence(E, OV_OP_DOV));
+  TRY(apply_sequence(E, OV_OP_DOV, false));
   // norms of r64 into u64 (as doubles), then one workgroup per distance into basis64
   SysDev dn = E.htab[T_APPLY];
   dn.e_in = b.r64;
