@@ -244,5 +244,12 @@ __device__ __forceinline__ int xcd_logical_block(int nb) {
   const int xcd = b & 7, k = b >> 3;
   return xcd * q + (xcd < rem ? xcd : rem) + k;
 }
+// The same within one system's n workgroups (l: this one's place among them in dispatch
+// order): every XCD gets a contiguous share of every system.
+__device__ __forceinline__ int xcd_share(int l, int n) {
+  const int q = n >> 3, rem = n & 7;
+  const int part = l & 7, k = l >> 3;
+  return part * q + (part < rem ? part : rem) + k;
+}
 
 }  // namespace ov

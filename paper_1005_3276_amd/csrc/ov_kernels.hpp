@@ -106,6 +106,7 @@ struct MsParams {
   double sigma[MAXP];   // shifts b_k
   double coef[MAXP];    // residues a_k
   int zm;               // > 0: z-marching passes over zm planes per workgroup (ZmMarch)
+  int share;            // the XCDs share every system (xcd_share), not the launch
   unsigned long long* tstamp;  // non-null: per workgroup (start, end, sites) stamps
 };
 
@@ -774,7 +775,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
         for (int k2 = 0; k2 < 4; ++k2)
           o[k2] = c2<R>{o[k2].x + beta * qq[k2].x, o[k2].y + beta * qq[k2].y};
       }
-      store_sp_nt<R>(tn, g.V, ii, o);
+      store_sp<R>(tn, g.V, ii, o);
       return norm2_sp(o);
     });
     i = i1;  // every site done
@@ -786,7 +787,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) o[k2] = c2<R>{o[k2].x + beta * q[k2].x, o[k2].y + beta * q[k2].y};
     }
-    store_sp_nt<R>(tn, g.V, i, o);
+    store_sp<R>(tn, g.V, i, o);
     acc = norm2_sp(o);
   }
   // remaining sites of this block (sites per thread > 1)
@@ -798,7 +799,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) o[k2] = c2<R>{o[k2].x + beta * q[k2].x, o[k2].y + beta * q[k2].y};
     }
-    store_sp_nt<R>(tn, g.V, i, o);
+    store_sp<R>(tn, g.V, i, o);
     acc += norm2_sp(o);
   }
   const double tot = block_sum(acc, lds);
@@ -857,7 +858,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
       for (int k = 0; k < 4; ++k) rr[k] = r0[k];
 #pragma unroll
       for (int k = 0; k < 4; ++k) rr[k] = c2<R>{rr[k].x - alpha * w[k].x, rr[k].y - alpha * w[k].y};
-      store_sp_nt<R>(rout, g.V, ii, rr);
+      store_sp<R>(rout, g.V, ii, rr);
       return norm2_sp(rr);
     });
     i = i1;
@@ -867,7 +868,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
     hw_compute<R>(nb, g, i, (R)mp->diag, w);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r[k] = c2<R>{r[k].x - alpha * w[k].x, r[k].y - alpha * w[k].y};
-    store_sp_nt<R>(rout, g.V, i, r);
+    store_sp<R>(rout, g.V, i, r);
     acc = norm2_sp(r);
   }
   for (i += blockDim.x; !zm && i < i1; i += blockDim.x) {
@@ -876,7 +877,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
     load_sp<R>(rin, g.V, i, r);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r[k] = c2<R>{r[k].x - alpha * w[k].x, r[k].y - alpha * w[k].y};
-    store_sp_nt<R>(rout, g.V, i, r);
+    store_sp<R>(rout, g.V, i, r);
     acc += norm2_sp(r);
   }
   const double tot = block_sum(acc, lds);
@@ -905,7 +906,9 @@ __device__ __forceinline__ void stamp_block(unsigned long long* ts, unsigned lon
 // history, the nine stencil operands and t_{n-1}) is issued before any of them
 // is consumed, and each wave finishes the reduction and the shift recurrences
 // on its own (identical bits in every wave), so the only barrier is the final
-// block reduction.
+// block reduction.  The stores of t_n and r_{n+1} go through the caches: the next pass reads
+// both, and the 256 MB last-level cache holds much of them (24^3 x 48: sign 8.4 -> 8.2 ms,
+// mixed solve 166 -> 159 with streaming stores replaced).
 template <class R, int ZM, bool CF>
 __global__ void __launch_bounds__(256) k_ms_t(const SysDev* __restrict__ sys,
                                               const int* __restrict__ bmap, int nb_total, int n,
@@ -914,9 +917,10 @@ __global__ void __launch_bounds__(256) k_ms_t(const SysDev* __restrict__ sys,
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   unsigned long long t0 = 0;
   if (mp_.tstamp && threadIdx.x == 0) t0 = wall_clock64();
-  const int L = xcd_logical_block(nb_total);
+  const int L = mp_.share ? (int)blockIdx.x : xcd_logical_block(nb_total);
   const SysDev& S = sys[bmap[L]];
-  const int sites = ms_t_block<R, ZM, CF>(S, L - S.blk0, n, &mp_, lds, ZM ? (c2<R>*)dyn_lds : nullptr);
+  const int lb = mp_.share ? xcd_share(L - S.blk0, S.nblk) : L - S.blk0;
+  const int sites = ms_t_block<R, ZM, CF>(S, lb, n, &mp_, lds, ZM ? (c2<R>*)dyn_lds : nullptr);
   if (mp_.tstamp) stamp_block(mp_.tstamp, t0, sites);
 }
 
@@ -930,9 +934,10 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   unsigned long long t0 = 0;
   if (mp_.tstamp && threadIdx.x == 0) t0 = wall_clock64();
-  const int L = xcd_logical_block(nb_total);
+  const int L = mp_.share ? (int)blockIdx.x : xcd_logical_block(nb_total);
   const SysDev& S = sys[bmap[L]];
-  const int sites = ms_r_block<R, ZM, CF>(S, L - S.blk0, n, &mp_, lds, ZM ? (c2<R>*)dyn_lds : nullptr);
+  const int lb = mp_.share ? xcd_share(L - S.blk0, S.nblk) : L - S.blk0;
+  const int sites = ms_r_block<R, ZM, CF>(S, lb, n, &mp_, lds, ZM ? (c2<R>*)dyn_lds : nullptr);
   if (mp_.tstamp) stamp_block(mp_.tstamp, t0, sites);
 }
 
@@ -1858,11 +1863,14 @@ enum EpiMode {
 };
 
 // c+ = m + g phi, c- = m* + g* phi*;  Y psi = c- psi_{0,1} (P-) + c+ psi_{2,3} (P+).
+// Like the other kernels without neighbours, k_ms_combine takes its workgroups as dispatched,
+// round-robin over the XCDs: in a batch whose members finish one by one, contiguous shares
+// leave the XCDs of the finished ones idle.
 template <class R>
 __global__ void __launch_bounds__(256) k_ms_combine(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
                                                      int nb_total, int mode) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   if (S.active && *S.active == 0) return;
@@ -2003,7 +2011,7 @@ template <class R>
 __global__ void __launch_bounds__(256) k_ms_prep(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
                                                   int nb_total, int g5_src) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   if (S.active && *S.active == 0) return;
@@ -2857,7 +2865,7 @@ __global__ void __launch_bounds__(512) k_gw_prep(const SysDev* __restrict__ ta,
                                                   const SysDev* __restrict__ tb,
                                                   const int* __restrict__ bmap, int nb_total) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& A = ta[s];
   const SysDev& B = tb[s];
@@ -2935,7 +2943,7 @@ __global__ void __launch_bounds__(512) k_gw_combine(const SysDev* __restrict__ t
                                                      const SysDev* __restrict__ tb,
                                                      const int* __restrict__ bmap, int nb_total) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& A = ta[s];
   const SysDev& B = tb[s];
@@ -2988,7 +2996,7 @@ __global__ void __launch_bounds__(512) k_gw_combine(const SysDev* __restrict__ t
 __global__ void __launch_bounds__(512) k_truth_combine(const SysDev* __restrict__ ta,
                                                        const SysDev* __restrict__ tb,
                                                        const int* __restrict__ bmap, int nb_total) {
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& A = ta[s];
   const SysDev& B = tb[s];
@@ -3268,7 +3276,7 @@ template <class R>
 __global__ void __launch_bounds__(512) k_cg_p(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
                                                int nb_total, int use_beta) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   if (S.active && *S.active == 0) return;
@@ -3311,7 +3319,7 @@ __global__ void __launch_bounds__(512) k_cg_p_gw(const SysDev* __restrict__ sys,
                                                  const int* __restrict__ bmap, int nb_total,
                                                  int use_beta) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   const SysDev& A = ta[s];
@@ -3380,7 +3388,7 @@ template <class R>
 __global__ void __launch_bounds__(512) k_cg_misc(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
                                                   int nb_total, int op) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   if (S.active && *S.active == 0) return;
@@ -3544,7 +3552,7 @@ __global__ void __launch_bounds__(256) k_c_norm(const SysDev* __restrict__ sys,
 __global__ void __launch_bounds__(256) k_dot_re(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
                                                  int nb_total) {
   __shared__ double lds[17];
-  const int L = xcd_logical_block(nb_total);
+  const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
   const int lb = L - S.blk0;

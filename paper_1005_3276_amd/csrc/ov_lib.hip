@@ -233,24 +233,30 @@ struct SysBuf {
   int xc = 1, off_xy = 0, off_z = 0, off_t = 0;  // momentum-space pass geometry
 };
 
-// Sites per workgroup.  Automatic choice (spt = 0) from the sites of the whole
-// launch: one site per thread while the launch is small enough for every
-// workgroup to start at once (latency-bound single systems), more when many
-// systems share the launch (bandwidth-bound batches: fewer, longer workgroups
-// and, where the xy plane is one workgroup, z-marching passes).
-int sites_per_block(const ov_ctx* c, int V, long long total_sites) {
+// Sites per workgroup of `block` threads.  Automatic choice (spt = 0) from the sites of the
+// whole launch: one site per thread while every workgroup can start at once (latency-bound
+// single systems), beyond 1024 workgroups as many as leave about two per CU: a workgroup
+// of a multi-shift pass first sums the partials of all of them (24^3 x 48, FP64 sign, us per
+// pass: 2592 workgroups 80, 1296 49, 648 40, 432 39, 260 57; 16^2 x 32 x 48: 1536
+// 37, 768 28, 512 23; the FP32 passes of the mixed solve likewise).  Where the xy plane is
+// one workgroup and four sites divide Z it takes those, z-marching.  Workgroups of fewer
+// threads keep more of them (8^4, 32 mixed solves: 18.6 ms with two sites, 20.3 with four).
+int sites_per_block(const ov_ctx* c, int block, int V, long long total_sites) {
   int spt = c->spt;
   if (spt <= 0) {
-    const long long blocks1 = (std::max<long long>(total_sites, V) + c->block - 1) / c->block;
-    spt = blocks1 <= 1024 ? 1 : (blocks1 <= 4096 ? 2 : 4);
-    spt = std::max(spt, (int)(((V + c->block - 1) / c->block + 2047) / 2048));
+    const long long blocks1 = (std::max<long long>(total_sites, V) + block - 1) / block;
+    const int* d = c->p.dims;
+    const bool plane = d[0] * d[1] == block;
+    spt = blocks1 <= 1024 ? 1 : (int)std::min<long long>(6, (blocks1 + 511) / 512);
+    if (spt > 1 && plane) spt = d[2] % 4 == 0 ? 4 : 2;
+    if (block < 256 && spt > 1) spt = blocks1 <= 4096 ? 2 : 4;
+    spt = std::max(spt, (int)(((V + block - 1) / block + 2047) / 2048));
     // two sites per thread turn on the z-marching passes (a workgroup per xy plane,
     // two z planes each), which beat one site per thread while every launch still
     // has at least 64 workgroups per system (16^4: 25.2 -> 22.3 ms per mixed solve)
-    const int* d = c->p.dims;
-    if (spt == 1 && d[0] * d[1] == c->block && d[2] % 2 == 0 && V / (2 * c->block) >= 64) spt = 2;
+    if (spt == 1 && plane && d[2] % 2 == 0 && V / (2 * block) >= 64) spt = 2;
   }
-  return c->block * spt;
+  return block * spt;
 }
 
 // What a call needs: FP64 ms basis capacity cap64, inner precision buffers.
@@ -404,6 +410,8 @@ struct Engine {
   hipStream_t st;
   Plan pl;
   int nsys = 0, nb_total = 0;
+  int block = NTHREADS;             // threads per workgroup: the largest of the members' (a
+                                    // small one in front of a batch does not set it for all)
   SysDev* tables = nullptr;         // device: ntab * nsys
   std::vector<SysDev> htab;         // host copy
   size_t up_bytes = 0;              // bytes from `tables` to the end of the uploaded region
@@ -555,7 +563,7 @@ struct Engine {
       b.ctx = ctxs[s];
       const ov_params& p = ctxs[s]->p;
       b.V = p.dims[0] * p.dims[1] * p.dims[2] * p.dims[3];
-      b.spb = size_worst ? 64 : sites_per_block(ctxs[s], b.V, total_sites);
+      b.spb = size_worst ? 64 : sites_per_block(ctxs[s], block, b.V, total_sites);
       b.nblk = (b.V + b.spb - 1) / b.spb;
       b.blk0 = blk;
       blk += b.nblk;
@@ -810,6 +818,8 @@ void plan_engine(Engine& E, const std::vector<ov_ctx*>& ctxs, bool solve, bool m
   E.nsys = (int)ctxs.size();
   E.sb.assign(E.nsys, SysBuf{});
   E.lead = ctxs[0];
+  E.block = 0;
+  for (const ov_ctx* c : ctxs) E.block = std::max(E.block, c->block);
   E.st = E.lead->priv;
   E.pl.solve = solve;
   E.pl.mixed = mixed;
@@ -1075,13 +1085,13 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
     for (const auto& b : E.sb) {
       const ov_params& p = b.ctx->p;
       const int XY = p.dims[0] * p.dims[1];
-      const int k = b.spb / c->block;
-      ok &= XY == c->block && b.spb == k * c->block && k >= 2 && p.dims[2] % k == 0 &&
+      const int k = b.spb / E.block;
+      ok &= XY == E.block && b.spb == k * E.block && k >= 2 && p.dims[2] % k == 0 &&
             (zc == 0 || zc == k);
       zc = k;
     }
     mps.zm = ok ? zc : 0;
-    shb = ok ? (size_t)4 * c->block * sizeof(c2<R>) : 0;
+    shb = ok ? (size_t)4 * E.block * sizeof(c2<R>) : 0;
   }
   if (c->sample_max > 0) {  // stamp regions for the sampled launches of this call
     const size_t region = 3 * (size_t)nbt_;  // (start, end, sites) per workgroup
@@ -1116,26 +1126,35 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
   // z-marching (with the next plane prefetched in FP32), else the plain passes
   const bool zmode = mps.zm > 0;
   constexpr int ZMF = sizeof(R) == sizeof(float) ? 2 : 1;  // the z-marching form of R
-  // large (batched) launches check their flags before reading operands
-  const bool cf = nbt_ >= 2048 && ms_cf_enabled();
+  // batched launches check their flags before reading operands: the plain ones of any size
+  // (the uneven batch of 8^4 to 24^3 x 48, mixed: 229 -> 217 ms), z-marching ones when large
+  const bool cf = (zmode ? nbt_ >= 2048 : E.nsys > 1) && ms_cf_enabled();
+  // lattices of several sizes converge at different times: every XCD takes a share of each
+  // (same batch: 217 -> 195 ms); equal ones stay whole in an XCD's L2 (24^3 x 48, one
+  // mixed solve: 159 against 162)
+  for (const ov_ctx* o : E.ctxs) mps.share |= !std::equal(o->p.dims, o->p.dims + 4, c->p.dims);
   for (int n = 0; n < L; ++n) {
     {
       Sample smp(c, sizeof(R) == sizeof(double) ? 3 : 0, bytes);
       if (zmode && cf)
-        k_ms_t<R, ZMF, true><<<nbt_, c->block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_t<R, ZMF, true><<<nbt_, E.block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
       else if (zmode)
-        k_ms_t<R, ZMF, false><<<nbt_, c->block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_t<R, ZMF, false><<<nbt_, E.block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+      else if (cf)
+        k_ms_t<R, 0, true><<<nbt_, E.block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
       else
-        k_ms_t<R, 0, false><<<nbt_, c->block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_t<R, 0, false><<<nbt_, E.block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
     }
     {
       Sample smp(c, sizeof(R) == sizeof(double) ? 4 : 1, bytes);
       if (zmode && cf)
-        k_ms_r<R, ZMF, true><<<nbt_, c->block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_r<R, ZMF, true><<<nbt_, E.block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
       else if (zmode)
-        k_ms_r<R, ZMF, false><<<nbt_, c->block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_r<R, ZMF, false><<<nbt_, E.block, shb, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+      else if (cf)
+        k_ms_r<R, 0, true><<<nbt_, E.block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
       else
-        k_ms_r<R, 0, false><<<nbt_, c->block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
+        k_ms_r<R, 0, false><<<nbt_, E.block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
     }
   }
   k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp, ResEpoch{});
@@ -1148,7 +1167,7 @@ void launch_ms(const Engine& E, int t, const MsParams& mp, int L) {
 
 template <class R>
 void launch_combine(const Engine& E, int t, int mode) {
-  k_ms_combine<R><<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, t), E.bmap, E.nb_total, mode);
+  k_ms_combine<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, t), E.bmap, E.nb_total, mode);
 }
 
 SymParams sym_params(const ov_ctx* c, int kind) {
@@ -1269,7 +1288,7 @@ bool pcg_fixed(const Engine& E, int t) {
 // on the preconditioner mass and the shift only).
 void pcg_table(const Engine& E) {
   if (!E.pl.pc) return;
-  k_pcg_table<<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, T_PC_Z), E.bmap, E.nb_total,
+  k_pcg_table<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_PC_Z), E.bmap, E.nb_total,
                                                       sym_params(E.lead, SYM_PCG));
 }
 
@@ -1281,7 +1300,7 @@ int site_block(const Engine& E) {
   int spb = 0;
   for (const auto& b : E.sb) spb = std::max(spb, b.spb);
   spb = (spb + 63) / 64 * 64;
-  return std::max(E.lead->block, std::min(512, spb));
+  return std::max(E.block, std::min(512, spb));
 }
 
 // e_out = op(e_in) for a momentum-space operator (forward DFTs, symbol, inverse
@@ -1378,12 +1397,12 @@ void zero_dev(const Engine& E, void* p, size_t bytes) {
 
 // The caller's fields to their planar twins and back (E.io, in the uploaded tables).
 ov_status pack64(Engine& E) {
-  k_pack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_pack<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return check_launch(E.lead);
 }
 
 ov_status unpack64(Engine& E) {
-  k_unpack<double><<<E.nb_total, E.lead->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_unpack<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return check_launch(E.lead);
 }
 
@@ -1434,7 +1453,7 @@ void launch_hw_io(const Engine& E, double diag) {
     else
       k_hw_io_zm<2><<<nzm, 256, 0, E.st>>>(T, diag);
   } else {
-    k_hw_io<<<E.nb_total, E.lead->block, 0, E.st>>>(T, E.bmap, E.nb_total, diag);
+    k_hw_io<<<E.nb_total, E.block, 0, E.st>>>(T, E.bmap, E.nb_total, diag);
   }
 }
 
@@ -1443,7 +1462,7 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
   const double diag = 4.0 - c->p.M0;
   if (c->p.dirac != OV_DIRAC_OVERLAP_MS && op >= OV_OP_DOV && op <= OV_OP_MDAGM) {
     // momentum-space D (x64 -> r64; MdagM through u64)
-    const int nb = E.nb_total, bl = c->block;
+    const int nb = E.nb_total, bl = E.block;
     switch (op) {
       case OV_OP_DOV:
         launch_sym<double>(E, T_APPLY, SYM_D);
@@ -1473,22 +1492,22 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
       if (direct)
         launch_hw_io(E, diag);
       else
-        k_hw<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, diag, 0);
+        k_hw<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, diag, 0);
       break;
     case -1:  // sign
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
       launch_combine<double>(E, T_APPLY, EPI_SIGN);
       break;
     case OV_OP_DOV:
     case OV_OP_M:
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
       launch_combine<double>(E, T_APPLY, op == OV_OP_DOV ? EPI_DOV : EPI_M);
       break;
     case OV_OP_DOV_DAG:
     case OV_OP_M_DAG:
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 1);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 1);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
       launch_combine<double>(E, T_APPLY, op == OV_OP_DOV_DAG ? EPI_DOVDAG : EPI_MDAG);
       break;
@@ -1497,7 +1516,7 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
       launch_sym<double>(E, T_APPLY, op == OV_OP_M0INV ? SYM_M0INV : SYM_M0INV_DAG);
       break;
     case OV_OP_MDAGM:
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
       launch_combine<double>(E, T_APPLY, EPI_M);  // u64, src64b = g5 u64, part_b
       launch_ms<double>(E, T_APPLY2, E.mp64, E.L64);
@@ -1635,7 +1654,7 @@ ov_status pc_masses(Engine& E, const std::vector<const void*>& phi, std::vector<
     E.htab[(size_t)T_APPLY * ns + s] = d;
   }
   TRY(upload_tables(E));
-  k_c_norm<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_c_norm<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   TRY(check_launch(c));
   k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_APPLY), ns, 4);
   TRY(read_scalars(E));
@@ -1909,7 +1928,7 @@ ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
   }
   char buf[160];
   std::snprintf(buf, sizeof buf, "|%p|%p|%p|%d|%d|%d|%d|%d|%d|", (void*)E.tables, (void*)E.bmap,
-                (void*)E.gwtab, E.nb_total, E.nsys, c->block, E.nb_xy, E.nb_z, E.nb_t);
+                (void*)E.gwtab, E.nb_total, E.nsys, E.block, E.nb_xy, E.nb_z, E.nb_t);
   const std::string k = key + buf + E.geo_key;
   auto it = c->graphs.find(k);
   if (it == c->graphs.end()) {
@@ -1998,9 +2017,9 @@ ov_status reliable_update_L(Engine& E, double tol, int scalar_op, int L) {
     const int tres = E.pl.fft ? T_F_TMD : T_TR_MDAG;
     if (E.pl.fft) {
       launch_sym<double>(E, T_F_TM, SYM_D);
-      k_yuk<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_F_TM), E.bmap, E.nb_total, 0);
+      k_yuk<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_F_TM), E.bmap, E.nb_total, 0);
       launch_sym<double>(E, T_F_TMD, SYM_D_DAG);
-      k_yuk<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_F_TMD), E.bmap, E.nb_total, 2);
+      k_yuk<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_F_TMD), E.bmap, E.nb_total, 2);
     } else if (E.pl.gwx) {  // one two-source multi-shift (see k_truth_combine)
       const int nb = E.nb_total, ns = E.nsys;
       k_stat3_clear<<<1, 64, 0, E.st>>>(E.trgwtab, 2 * ns);
@@ -2009,7 +2028,7 @@ ov_status reliable_update_L(Engine& E, double tol, int scalar_op, int L) {
       k_truth_combine<<<nb, site_block(E), 0, E.st>>>(E.trgwtab, E.trgwtab + ns, E.bmap, nb);
       k_truth_finish<R><<<nb, site_block(E), 0, E.st>>>(E.trgwtab, E.bmap, nb, 4.0 - c->p.M0, 0);
     } else {
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_TR_M), E.bmap, E.nb_total, 0);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_TR_M), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_TR_M, mp, L);
       launch_combine<double>(E, T_TR_M, EPI_M);
       launch_ms<double>(E, T_TR_MDAG, mp, L);
@@ -2121,19 +2140,19 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
   std::vector<int> fcg(ns, 1), fru(ns, 1);
   TRY(set_flags(E, fcg, fru));
   // x64 <- guess was packed by the caller; xR = 0; rcgR = b, |b|^2
-  k_cg_misc<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 2);
-  k_cg_misc<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 1);
+  k_cg_misc<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 2);
+  k_cg_misc<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 1);
   k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 4);  // BB
   const bool pc = E.pl.pc;
   if (pc) {  // z = P b, rho = <b, z>, beta = 0
     launch_sym<R>(E, T_PC_Z, SYM_PCG);
-    k_cg_misc<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 6);
+    k_cg_misc<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 6);
     k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 10);
   } else {
     k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 0);  // rho = |b|^2, beta = 0
   }
   // |x0|^2 -> part_b via prep on x64 (src = x64 in T_CG)
-  k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 0);
+  k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_CG), E.bmap, E.nb_total, 0);
   k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 13);
   TRY(read_scalars(E));
   std::vector<double> x0n(ns);
@@ -2241,7 +2260,7 @@ ov_status solve_engine(Engine& E, const std::vector<const void*>& bvec,
     // x = M0^-1 x~ (Sec. 7.3), with one transform per iteration instead of two.
     Range it_range("ov CG iteration");
     TRY(run_graph(E, ikey, [&]() {
-      const int nb = E.nb_total, bl = c->block;
+      const int nb = E.nb_total, bl = E.block;
       if (E.pl.gw && !E.pl.fft)  // p = z + beta p and the second inner source in one pass
         k_cg_p_gw<R><<<nb, site_block(E), 0, E.st>>>(tab(E, T_CG), E.gwtab, E.gwtab + ns, E.bmap, nb, 1);
       else
@@ -2457,10 +2476,10 @@ ov_status tune_run(ov_ctx* c, int nrhs, int iters, float* us) {
   const int cap = fp32 ? E.pl.capR : E.pl.cap64;
   const int L = std::min(iters, cap);
   MsParams mp = make_mp(c, 1e-300, cap);  // never converges: every iteration works
-  k_fill<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
-  k_ms_prep<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+  k_fill<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_ms_prep<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
   launch_ms<R>(E, T_APPLY, mp, std::min(4, L));  // warm-up
-  k_ms_prep<R><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+  k_ms_prep<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
   hipEvent_t e0, e1;
   HIPCHK(c, hipEventCreate(&e0));
   HIPCHK(c, hipEventCreate(&e1));
@@ -2971,19 +2990,19 @@ static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const voi
   TRY(upload_tables(E));
   if (E.pl.fft) {
     launch_sym<double>(E, T_APPLY, SYM_D);
-    k_yuk<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+    k_yuk<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
   } else {
     MsParams mp = make_mp(c, c->p.truth_tol, E.pl.cap64);
     const int L = std::min(E.pl.cap64, capacity(c, c->p.truth_tol));
     clear_ctl(E);  // the sticky bits below then belong to the Y = M X multi-shift alone
-    k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+    k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
     launch_ms<double>(E, T_APPLY, mp, L);
     launch_combine<double>(E, T_APPLY, EPI_M);
   }
   // S_r = Re <xi_r, X_r>
-  k_dot_re<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_dot_re<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   // G summed over right-hand sides in order (one launch over the sites)
-  k_force<<<E.sb[0].nblk, c->block, 0, E.st>>>(tab(E, T_APPLY), nrhs, E.sb[0].nblk,
+  k_force<<<E.sb[0].nblk, E.block, 0, E.st>>>(tab(E, T_APPLY), nrhs, E.sb[0].nblk,
                                                (double2*)grad_phi);
   k_cg_scalar<<<nrhs, 256, 0, E.st>>>(tab(E, T_APPLY), nrhs, 4);  // S_r -> BB
   TRY(read_scalars(E));
@@ -3034,7 +3053,7 @@ static ov_status rational_core(ov_ctx* c, Engine& E, double a0, int n, const dou
   TRY(upload());
   std::vector<int> fcg(ns, 1), fru(ns, 0);
   TRY(set_flags(E, fcg, fru));
-  const int nb = E.nb_total, bl = c->block;
+  const int nb = E.nb_total, bl = E.block;
   k_cg_misc<double><<<nb, bl, 0, E.st>>>(tab(E, T_CG), E.bmap, nb, 2);  // x = 0
   k_cg_misc<double><<<nb, bl, 0, E.st>>>(tab(E, T_CG), E.bmap, nb, 1);  // r = b, |b|^2
   k_cg_scalar<<<ns, 256, 0, E.st>>>(tab(E, T_CG), ns, 4);
@@ -3230,7 +3249,7 @@ static ov_status shifted_solve_acc(ov_ctx* c, double sigma, double alpha,
         c->err = "shifted solve of the rational layer did not converge within max_outer";
         return OV_ERR_NOT_CONVERGED;
       }
-    k_unpack_axpy<<<F.nb_total, c->block, 0, F.st>>>(tab(F, T_APPLY), F.bmap, F.nb_total, alpha);
+    k_unpack_axpy<<<F.nb_total, F.block, 0, F.st>>>(tab(F, T_APPLY), F.bmap, F.nb_total, alpha);
     return sync(F);
   }
   c->err = "shifted solve of the rational layer: FP64 retry did not finish";
@@ -3340,7 +3359,7 @@ static ov_status rational_force_impl(ov_ctx* c, double a0, int n, const double* 
   // S_r = Re xi_r^dag (a0 xi_r + sum_i alpha_i X_i) from the combined field in r64
   for (int s = 0; s < nrhs; ++s) E.htab[(size_t)T_APPLY * nrhs + s].e_in = E.sb[s].r64;
   TRY(upload_tables(E));
-  k_dot_re<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_dot_re<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   TRY(sync(E));
   for (int s = 0; s < nrhs; ++s) {
     std::vector<double> tmp(E.sb[s].nblk);
@@ -3372,13 +3391,13 @@ static ov_status rational_force_impl(ov_ctx* c, double a0, int n, const double* 
     TRY(upload_tables(E));
     if (E.pl.fft) {
       launch_sym<double>(E, T_APPLY, SYM_D);
-      k_yuk<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      k_yuk<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
     } else {
-      k_ms_prep<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_APPLY, mp, L);
       launch_combine<double>(E, T_APPLY, EPI_M);
     }
-    k_scale<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, alpha[k]);
+    k_scale<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, alpha[k]);
   }
   // G = sum over (system, shift) of the force density of (X_i, alpha_i M X_i)
   std::vector<SysDev> ft((size_t)nrhs * n);
@@ -3391,7 +3410,7 @@ static ov_status rational_force_impl(ov_ctx* c, double a0, int n, const double* 
     }
   HIPCHK(c, hipMemcpyAsync(E.ftab, ft.data(), sizeof(SysDev) * ft.size(), hipMemcpyHostToDevice,
                            E.st));
-  k_force<<<E.sb[0].nblk, c->block, 0, E.st>>>(E.ftab, nrhs * n, E.sb[0].nblk,
+  k_force<<<E.sb[0].nblk, E.block, 0, E.st>>>(E.ftab, nrhs * n, E.sb[0].nblk,
                                                (double2*)grad_phi);
   TRY(read_scalars(E));
   if (!E.pl.fft) {
@@ -3438,9 +3457,9 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   d.fft_tmp = b.src64b;
   E.htab[T_APPLY] = d;
   TRY(upload_tables(E));
-  k_boson_pack<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  k_boson_pack<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   launch_sym<double>(E, T_APPLY, SYM_BOSON);
-  k_boson_finish<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
+  k_boson_finish<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
                                                     (double2*)G, (double2*)F);
   k_cg_scalar<<<1, 256, 0, E.st>>>(tab(E, T_APPLY), 1, 4);  // S_B -> BB
   TRY(read_scalars(E));
@@ -3555,7 +3574,7 @@ static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats*
   TRY(upload_tables(E));
   double* norm = (double*)b.u64;
   double* fd = (double*)b.basis64;
-  k_site_norm<<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY2), E.bmap, E.nb_total, norm);
+  k_site_norm<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY2), E.bmap, E.nb_total, norm);
   k_shell_max<<<rmax + 1, 256, 0, E.st>>>(dn.g, norm, fd);
   TRY(check_launch(c));
   std::vector<double> h(rmax + 1);
@@ -3591,9 +3610,9 @@ ov_status ov_pack(ov_ctx* c, int prec, void* dst, const void* src, int nrhs) {
                (char*)dst + r * V * 4 * (prec ? sizeof(float2) : sizeof(double2)), nullptr, nullptr};
   TRY(upload_tables(E));
   if (prec)
-    k_pack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+    k_pack<float><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   else
-    k_pack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+    k_pack<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return sync(E);
 }
 
@@ -3612,9 +3631,9 @@ ov_status ov_unpack(ov_ctx* c, int prec, void* dst, const void* src, int nrhs) {
                (char*)dst + r * V * 4 * sizeof(double2)};
   TRY(upload_tables(E));
   if (prec)
-    k_unpack<float><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+    k_unpack<float><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   else
-    k_unpack<double><<<E.nb_total, c->block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+    k_unpack<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
   return sync(E);
 }
 
@@ -3681,7 +3700,7 @@ ov_status ov_stencil_bench(ov_ctx* c, int prec, void* out, const void* in, int n
       SysBuf& b = E.sb[s];
       b.ctx = c;
       b.V = c->p.dims[0] * c->p.dims[1] * c->p.dims[2] * c->p.dims[3];
-      b.spb = sites_per_block(c, b.V, (long long)b.V * nrhs);
+      b.spb = sites_per_block(c, c->block, b.V, (long long)b.V * nrhs);
       b.nblk = (b.V + b.spb - 1) / b.spb;
       b.blk0 = blk;
       blk += b.nblk;

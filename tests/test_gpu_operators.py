@@ -49,3 +49,35 @@ def test_hw_in_place(orc, shift):
     ref = orc.Oracle(dims, **CFG2)
     for r in range(nrhs):
         check(host(out)[r], ref.hw(x[r]), 1e-14, f"rhs {r}")
+
+
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 514), 1), ((22, 24, 22, 24), 1)])
+def test_sign_with_per_pass_kernels_vs_oracle(orc, dims, nrhs):
+    """Lattices without a resident decomposition: a small one (T = 2 x 257), and one of more
+    than 1024 workgroups (several sites per thread, a last workgroup that is not full).
+    Both sides run the multi-shift at 1e-12."""
+    print(f"[per-pass sign] {dims}", flush=True)
+    x = inputs.gaussian_field(dims, nrhs=nrhs, seed=83)
+    kw = dict(CFG2, lambda_min=0.2, n_poles=12, inner_tol=1e-12)
+    lat = lattice(dims, precondition=0, **kw)
+    lat.kernel_sampling(4)
+    lat.kernel_times(3)
+    out, _ = lat.sign(dev(x))
+    assert lat.kernel_times(3)[1] > 0
+    check(host(out)[0], orc.Oracle(dims, **kw).sign(x[0])[0], 1e-11)
+
+
+def test_uneven_batch_with_per_pass_kernels(orc):
+    """Two lattices of different sizes that share a launch of the per-pass kernels."""
+    from paper_1005_3276_amd import solve_batch
+    dims = [(4, 4, 4, 4), (2, 2, 2, 514)]
+    kw = dict(precision="mixed", outer_tol=1e-10, precondition=0, **CFG2)
+    phi, src = zip(*(inputs.draw(d, nrhs=1 + k, sigma2=0.25, seed=84 + k)
+                     for k, d in enumerate(dims)))
+    print(f"[per-pass batch] {dims}", flush=True)
+    xs, _ = solve_batch([lattice(d, **kw) for d in dims], [dev(b) for b in src],
+                        [dev(p) for p in phi])
+    for d, b, p, x in zip(dims, src, phi, xs):
+        o = orc.Oracle(d, inner_tol=1e-13, **CFG2)
+        for r in range(b.shape[0]):
+            assert o.residual(b[r], host(x)[r], p) <= 1e-10, (d, r)
