@@ -82,7 +82,7 @@ struct SysDev {
   const double* shc;        //   per-shift coefficients (SHC_* layout)
   int nshift;
   void* fft_tmp;            // momentum-space scratch field (kernel precision)
-  int off_xy, off_z, off_t; // first workgroup of this system in each transform pass
+  int off_xy, off_z, off_t, off_zt; // first workgroup of this system in each transform pass
   int xc;                   // x values per workgroup in the t pass (divides X, xc T <= 64)
   double* pcs;              // [V] preconditioner scale per momentum (k_pcg_table), or null
   // the caller's fields (complex128, spin innermost) and their planar twins of a call:
@@ -2100,7 +2100,10 @@ struct SymParams {
 __device__ __forceinline__ int find_sys(const SysDev* __restrict__ sys, int nsys, int b, int which) {
   int s = 0;
   for (int k = 1; k < nsys; ++k) {
-    const int o = which == 0 ? sys[k].off_xy : (which == 1 ? sys[k].off_z : sys[k].off_t);
+    const int o = which == 0   ? sys[k].off_xy
+                  : which == 1 ? sys[k].off_z
+                  : which == 2 ? sys[k].off_t
+                               : sys[k].off_zt;
     if (o <= b) s = k;
   }
   return s;
@@ -2117,99 +2120,301 @@ __device__ __forceinline__ void twiddles(c2<R>* tw, int L, double sgn) {
   }
 }
 
-template <class R>
-__device__ __forceinline__ c2<R> cmad(c2<R> acc, c2<R> a, c2<R> w) {
-  return c2<R>{acc.x + a.x * w.x - a.y * w.y, acc.y + a.x * w.y + a.y * w.x};
+// W' = m phi + g phi^2 / 2 at a site.
+__device__ __forceinline__ double2 w_prime(const SysDev& S, double2 f) {
+  const double lr = 0.5 * S.g_re, li = 0.5 * S.g_im;
+  const double f2r = f.x * f.x - f.y * f.y, f2i = 2.0 * f.x * f.y;
+  return double2{S.m_re * f.x - S.m_im * f.y + lr * f2r - li * f2i,
+                 S.m_re * f.y + S.m_im * f.x + lr * f2i + li * f2r};
 }
 
-// x and y axes of one (z, t, spin) plane.  inv = 0: e_in -> fft_tmp with the
-// time twist; inv = 1: fft_tmp -> e_out with the untwist and 1/V.  Needs
-// X, Y <= 64 and X Y <= 1024.
+// What a transform reads and writes.
+struct SymIo {
+  int in = 0;   // 0: planar e_in; 1: the caller's io_in; 2: phi, W', conj W' of phi
+  int out = 0;  // 0: planar e_out; 1: the caller's io_out
+  int yuk = 0;  // 1, 2: adds Y psi, Y^dag psi, psi the field read (k_yuk)
+  int zt = 0;   // fft_tmp holds a site line (z, t) after the other (k_fft_zt), else planes
+};
+
+// e / d for 0 <= e < 2^16, 1 <= d < 2^16 by a multiplication (e (d - 1) < 2^32).
+struct SmallDiv {
+  unsigned m;
+  int d;
+  __device__ __forceinline__ explicit SmallDiv(int d_) : m(0xffffffffu / (unsigned)d_ + 1u), d(d_) {}
+  __device__ __forceinline__ int div(int e) const {
+    return d == 1 ? e : (int)__umulhi((unsigned)e, m);
+  }
+};
+
+// n > 0 values to LDS, four loads of a thread in flight: get(e) reads one (a thread without
+// a value reads the last one), put(e, v) stores it, `between` runs while the first four are on
+// their way.
+template <class Get, class Put, class F>
+__device__ __forceinline__ void stage_in(int n, Get get, Put put, F between) {
+  const int bd = blockDim.x;
+  int e0 = threadIdx.x;
+  decltype(get(0)) v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
+  between();
+  for (;;) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * bd < n) put(e0 + u * bd, v[u]);
+    e0 += 4 * bd;
+    if (e0 >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
+  }
+}
+
+// Values k = g, N - g, N/2 - g and N/2 + g of the transform of one line of even length N
+// (elements a[j st] in LDS, twiddles tw[m] = (cos, sin) 2 pi m / N, sgn the exponent's sign),
+// 0 <= g <= N/4 (all values over all g; the ends of the range give two values twice).  With
+// s_j = a_j + a_{N-j}, d_j = a_j - a_{N-j} the four share their sums over even and odd j,
+//   X_k = a_0 + (-1)^k a_{N/2} + sum_j s_j cos(2 pi j k / N) + i sgn sum_j d_j sin(2 pi j k / N):
+// 3 N / 8 LDS reads and N / 2 real multiplications per value, where the plain sum takes 2 N
+// and 4 N (LDS reads bound these passes).
 template <class R>
-__global__ void __launch_bounds__(256) k_fft_xy(const SysDev* __restrict__ sys, int nsys, int inv,
-                                                int periodic) {
-  __shared__ c2<R> A[1024], B[1024];
-  __shared__ c2<R> twx[64], twy[64];
+__host__ __device__ __forceinline__ void line_dft(const c2<R>* a, int st, int N, const c2<R>* tw, int g,
+                                         R sgn, c2<R> o[4]) {
+  const int h = N >> 1;
+  const c2<R> a0 = a[0], ah = a[h * st];
+  c2<R> ce{R(0), R(0)}, co = ce, de = ce, dd = ce;
+  const c2<R>* p = a + st;
+  const c2<R>* q = a + (N - 1) * st;
+  int m = 0;
+#pragma unroll 2
+  for (int j = 1; j < h; j += 2) {
+    m += g;
+    if (m >= N) m -= N;
+    {
+      const c2<R> u = *p, v = *q, w = tw[m];
+      co.x += (u.x + v.x) * w.x;
+      co.y += (u.y + v.y) * w.x;
+      dd.x += (u.x - v.x) * w.y;
+      dd.y += (u.y - v.y) * w.y;
+    }
+    if (j + 1 < h) {
+      m += g;
+      if (m >= N) m -= N;
+      const c2<R> u = p[st], v = q[-st], w = tw[m];
+      ce.x += (u.x + v.x) * w.x;
+      ce.y += (u.y + v.y) * w.x;
+      de.x += (u.x - v.x) * w.y;
+      de.y += (u.y - v.y) * w.y;
+    }
+    p += 2 * st;
+    q -= 2 * st;
+  }
+  const R s0 = g & 1 ? R(-1) : R(1), s1 = (h - g) & 1 ? R(-1) : R(1);
+  const c2<R> c0{a0.x + s0 * ah.x + (ce.x + co.x), a0.y + s0 * ah.y + (ce.y + co.y)};
+  const c2<R> c1{a0.x + s1 * ah.x + (ce.x - co.x), a0.y + s1 * ah.y + (ce.y - co.y)};
+  const c2<R> d0{sgn * (de.x + dd.x), sgn * (de.y + dd.y)};
+  const c2<R> d1{sgn * (dd.x - de.x), sgn * (dd.y - de.y)};
+  o[0] = c2<R>{c0.x - d0.y, c0.y + d0.x};
+  o[1] = c2<R>{c0.x + d0.y, c0.y - d0.x};
+  o[2] = c2<R>{c1.x - d1.y, c1.y + d1.x};
+  o[3] = c2<R>{c1.x + d1.y, c1.y - d1.x};
+}
+__host__ __device__ inline int dft_groups(int N) { return N / 4 + 1; }
+// The four places of group g in the line (stride st).
+__host__ __device__ __forceinline__ void dft_places(int N, int g, int st, int k[4]) {
+  k[0] = g * st;
+  k[1] = g > 0 ? (N - g) * st : 0;
+  k[2] = (N / 2 - g) * st;
+  k[3] = (N / 2 + g) * st;
+}
+
+// LDS of the xy pass: the rows of a plane one value longer than X (lanes of different rows
+// read different banks), the components' planes 2 mod 8 values apart (so do the four
+// components of a site).
+__host__ __device__ inline int fft_xy_plane(int X, int Y) { return Y * (X + 1) + (10 - Y * (X + 1) % 8) % 8; }
+
+// x and y axes of one (z, t) plane, all NS components.  inv = 0: the field -> fft_tmp; inv = 1:
+// fft_tmp -> the result; either with the time twist of the direction, the inverse with
+// 1/V.  Needs X, Y <= 64, X Y <= 1024, and 2 NS fft_xy_plane + X + Y + 1 values of LDS.  All
+// components, so that the caller's layout is read and written here, in whole lines.  Bound
+// by latency: 8.5 us on 16^3 x 32 in FP64 (512 workgroups), 2 until the field is there,
+// 1.8 for each axis, 2.5 for the store; one component per workgroup and plain sums took 15,
+// and pack, k_yuk and unpack 19 more.
+template <class R, int NS>
+__global__ void __launch_bounds__(512) k_fft_xy(const SysDev* __restrict__ sys, int nsys, int inv,
+                                                int periodic, const SymIo io) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
   const SysDev& S = sys[find_sys(sys, nsys, blockIdx.x, 0)];
   if (S.active && *S.active == 0) return;
   const int X = S.g.X, Y = S.g.Y, Z = S.g.Z, T = S.g.T, V = S.g.V;
-  const int loc = blockIdx.x - S.off_xy;
-  const int spin = loc & 3;
-  const int zt = loc >> 2;  // z + Z t
+  const int zt = blockIdx.x - S.off_xy;  // z + Z t
   const int t = zt / Z;
-  const int XY = X * Y;
-  const c2<R>* in = (const c2<R>*)(inv ? S.fft_tmp : S.e_in) + (size_t)spin * V + (size_t)zt * XY;
-  c2<R>* out = (c2<R>*)(inv ? S.e_out : S.fft_tmp) + (size_t)spin * V + (size_t)zt * XY;
-  const double sgn = inv ? 1.0 : -1.0;
-  twiddles<R>(twx, X, sgn);
-  twiddles<R>(twy, Y, sgn);
-  double tr = 1.0, ti = 0.0;  // twist (forward) / untwist and normalisation (inverse)
-  if (S.g.bc < 0 && !periodic) sincospi(sgn * (double)t / (double)T, &ti, &tr);
-  if (inv) {
-    tr /= (double)V;
-    ti /= (double)V;
-  }
-  for (int i = threadIdx.x; i < XY; i += blockDim.x) {
-    const c2<R> v = in[i];
-    A[i] = inv ? v : c2<R>{(R)(v.x * tr - v.y * ti), (R)(v.x * ti + v.y * tr)};
+  const int XY = X * Y, ZT = Z * T, P = X + 1, SP = fft_xy_plane(X, Y);
+  const SmallDiv dX(X), dXY(XY);
+  const size_t base = (size_t)zt * XY;
+  c2<R>* A = (c2<R>*)dyn_lds;
+  c2<R>* B = A + NS * SP;
+  c2<R>* twx = B + NS * SP;
+  c2<R>* twy = twx + X;
+  double2* const tws = (double2*)(twy + Y);  // e^{-+ i pi t / T}, 1 / V
+  auto between = [&]() {
+    for (int j = threadIdx.x; j < X + Y; j += blockDim.x) {
+      double sn, cs;
+      sincospi(j < X ? 2.0 * j / X : 2.0 * (j - X) / Y, &sn, &cs);
+      twx[j] = c2<R>{(R)cs, (R)sn};
+    }
+    if (threadIdx.x == blockDim.x - 1) {  // the last wave: the first ones are busy above
+      double2 w{1.0, 0.0};
+      if (S.g.bc < 0 && !periodic) sincospi((inv ? 1.0 : -1.0) * t / T, &w.y, &w.x);
+      const double f = inv ? 1.0 / V : 1.0;
+      *tws = double2{w.x * f, w.y * f};
+    }
+  };
+  auto cell = [&](int k, int i) -> c2<R>& {
+    const int y = dX.div(i);
+    return A[k * SP + y * P + (i - y * X)];
+  };
+  // value e of a plane whose sites hold their components side by side
+  auto comp = [](int e) { return e % NS; };
+  auto spot = [](int e) { return e / NS; };
+  if (NS == 3 && !inv) {
+    stage_in(XY, [&](int i) { return S.phi[base + i]; },
+             [&](int i, double2 f) {
+               const double2 w = w_prime(S, f);
+               cell(0, i) = c2<R>{(R)f.x, (R)f.y};
+               cell(1, i) = c2<R>{(R)w.x, (R)w.y};
+               cell(2, i) = c2<R>{(R)w.x, -(R)w.y};
+             },
+             between);
+  } else if (!inv && io.in == 1) {
+    const double2* in = S.io_in + NS * base;
+    stage_in(NS * XY, [&](int e) { return ldg2<double>(in, e); },
+             [&](int e, double2 v) { cell(comp(e), spot(e)) = c2<R>{(R)v.x, (R)v.y}; }, between);
+  } else if (inv && io.zt) {
+    const c2<R>* in = (const c2<R>*)S.fft_tmp;
+    stage_in(NS * XY,
+             [&](int e) { return ldg2<R>(in, ((size_t)spot(e) * ZT + zt) * NS + comp(e)); },
+             [&](int e, c2<R> v) { cell(comp(e), spot(e)) = v; }, between);
+  } else {
+    const c2<R>* in = (const c2<R>*)(inv ? S.fft_tmp : S.e_in) + base;
+    stage_in(NS * XY,
+             [&](int e) {
+               const int k = dXY.div(e);
+               return ldg2<R>(in, (size_t)k * V + (e - k * XY));
+             },
+             [&](int e, c2<R> v) {
+               const int k = dXY.div(e);
+               cell(k, e - k * XY) = v;
+             },
+             between);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < XY; i += blockDim.x) {  // x axis
-    const int kx = i % X, y = i / X;
-    c2<R> acc{(R)0, (R)0};
-    int w = 0;
-    for (int x = 0; x < X; ++x) {
-      acc = cmad<R>(acc, A[y * X + x], twx[w]);
-      w += kx;
-      if (w >= X) w -= X;
-    }
-    B[i] = acc;
+  const R sgn = inv ? R(1) : R(-1);
+  const SmallDiv dY(Y), dlx(NS * Y), dly(NS * X);
+  int at[4];
+  c2<R> o[4];
+  for (int it = threadIdx.x; it < NS * Y * dft_groups(X); it += blockDim.x) {  // x axis
+    const int g = dlx.div(it), ln = it - g * (NS * Y);
+    const int k = dY.div(ln), row = k * SP + (ln - k * Y) * P;
+    line_dft<R>(A + row, 1, X, twx, g, sgn, o);
+    dft_places(X, g, 1, at);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) B[row + at[q]] = o[q];
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < XY; i += blockDim.x) {  // y axis
-    const int kx = i % X, ky = i / X;
-    c2<R> acc{(R)0, (R)0};
-    int w = 0;
-    for (int y = 0; y < Y; ++y) {
-      acc = cmad<R>(acc, B[y * X + kx], twy[w]);
-      w += ky;
-      if (w >= Y) w -= Y;
+  const bool staged = inv ? io.out == 1 || io.yuk : io.zt;  // out through LDS
+  c2<R>* out = (c2<R>*)(inv ? S.e_out : S.fft_tmp) + base;
+  const double2 w = *tws;
+  for (int it = threadIdx.x; it < NS * X * dft_groups(Y); it += blockDim.x) {  // y axis
+    const int g = dly.div(it), ln = it - g * (NS * X);
+    const int k = dX.div(ln), kx = ln - k * X;
+    line_dft<R>(B + k * SP + kx, P, Y, twy, g, sgn, o);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      o[q] = c2<R>{(R)(o[q].x * w.x - o[q].y * w.y), (R)(o[q].x * w.y + o[q].y * w.x)};
+    c2<R>* to = staged ? A + k * SP + kx : out + (size_t)k * V + kx;
+    dft_places(Y, g, staged ? P : X, at);
+    if (staged) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) A[k * SP + kx + at[q]] = o[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) to[at[q]] = o[q];
     }
-    out[i] = inv ? c2<R>{(R)(acc.x * tr - acc.y * ti), (R)(acc.x * ti + acc.y * tr)} : acc;
+  }
+  if (!staged) return;
+  __syncthreads();
+  if (!inv) {
+    c2<R>* tmp = (c2<R>*)S.fft_tmp + (size_t)zt * NS;
+    for (int e = threadIdx.x; e < NS * XY; e += blockDim.x)
+      tmp[(size_t)spot(e) * (ZT * NS) + comp(e)] = cell(comp(e), spot(e));
+    return;
+  }
+  if constexpr (sizeof(R) == sizeof(double) && NS == 4) {  // operator calls on the caller's fields
+    const bool aos = io.out == 1;
+    auto k_of = [&](int e) { return aos ? e & 3 : dXY.div(e); };
+    auto i_of = [&](int e) { return aos ? e >> 2 : e - XY * dXY.div(e); };
+    auto write = [&](int e, double2 v) {
+      if (aos)
+        S.io_out[4 * base + e] = v;
+      else
+        ((double2*)out)[(size_t)k_of(e) * V + i_of(e)] = v;
+    };
+    if (!io.yuk) {
+      for (int e = threadIdx.x; e < 4 * XY; e += blockDim.x) write(e, cell(k_of(e), i_of(e)));
+      return;
+    }
+    struct PsiPhi {
+      double2 psi, phi;
+    };
+    stage_in(4 * XY,
+             [&](int e) {
+               const size_t i = base + i_of(e);
+               return PsiPhi{io.in == 1 ? ldg2<double>(S.io_in, 4 * i + k_of(e))
+                                        : ldg2<double>((const double2*)S.e_in, k_of(e) * (size_t)V + i),
+                             ldg2<double>(S.phi, i)};
+             },
+             [&](int e, const PsiPhi& p) {
+               const int k = k_of(e);
+               const double2 v = cell(k, i_of(e));
+               const double cr = S.m_re + S.g_re * p.phi.x - S.g_im * p.phi.y;
+               double ci = S.m_im + S.g_re * p.phi.y + S.g_im * p.phi.x;
+               if ((k < 2) != (io.yuk == 2)) ci = -ci;
+               write(e, double2{v.x + cr * p.psi.x - ci * p.psi.y, v.y + cr * p.psi.y + ci * p.psi.x});
+             },
+             []() {});
   }
 }
 
-// z axis of the (x, z) slab of one (y, t, spin), in place on fft_tmp.
-// Needs Z <= 64 and X Z <= 1024.
-template <class R>
-__global__ void __launch_bounds__(256) k_fft_z(const SysDev* __restrict__ sys, int nsys, int inv) {
-  __shared__ c2<R> A[1024];
-  __shared__ c2<R> tw[64];
+// z axis of the (x, z) slab of one (y, t), all components, in place on fft_tmp.
+// Needs Z <= 64, X Z <= 1024, and NS X Z + Z values of LDS.
+template <class R, int NS>
+__global__ void __launch_bounds__(512) k_fft_z(const SysDev* __restrict__ sys, int nsys, int inv) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
   const SysDev& S = sys[find_sys(sys, nsys, blockIdx.x, 1)];
   if (S.active && *S.active == 0) return;
   const int X = S.g.X, Y = S.g.Y, Z = S.g.Z, V = S.g.V;
-  const int loc = blockIdx.x - S.off_z;
-  const int spin = loc & 3;
-  const int yt = loc >> 2;  // y + Y t
-  const int y = yt % Y, t = yt / Y;
-  c2<R>* f = (c2<R>*)S.fft_tmp + (size_t)spin * V;
-  twiddles<R>(tw, Z, inv ? 1.0 : -1.0);
-  const int n = X * Z;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int x = e % X, z = e / X;
-    A[e] = f[x + X * (y + Y * (z + Z * t))];
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int x = e % X, kz = e / X;
-    c2<R> acc{(R)0, (R)0};
-    int w = 0;
-    for (int z = 0; z < Z; ++z) {
-      acc = cmad<R>(acc, A[z * X + x], tw[w]);
-      w += kz;
-      if (w >= Z) w -= Z;
-    }
-    f[x + X * (y + Y * (kz + Z * t))] = acc;  // every read of f happened before the barrier
+  const int yt = blockIdx.x - S.off_z;  // y + Y t
+  const int t = yt / Y, y = yt - t * Y;
+  const int XZ = X * Z, XY = X * Y;
+  const SmallDiv dX(X), dZ(Z), dl(NS * X);
+  c2<R>* A = (c2<R>*)dyn_lds;
+  c2<R>* tw = A + NS * XZ;
+  c2<R>* f = (c2<R>*)S.fft_tmp + X * (y + Y * Z * t);
+  stage_in(NS * XZ,
+           [&](int e) {  // (k Z + z) X + x
+             const int q = dX.div(e), k = dZ.div(q);
+             return ldg2<R>((const c2<R>*)f, (size_t)k * V + (e - q * X) + XY * (q - k * Z));
+           },
+           [&](int e, c2<R> v) { A[e] = v; }, [&]() { twiddles<R>(tw, Z, 1.0); });
+  __syncthreads();  // every read of f happens before it
+  int at[4];
+  c2<R> o[4];
+  for (int it = threadIdx.x; it < NS * X * dft_groups(Z); it += blockDim.x) {
+    const int g = dl.div(it), ln = it - g * (NS * X);
+    const int k = dX.div(ln), x = ln - k * X;
+    line_dft<R>(A + k * XZ + x, X, Z, tw, g, inv ? R(1) : R(-1), o);
+    dft_places(Z, g, XY, at);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[(size_t)k * V + x + at[q]] = o[q];
   }
 }
 
@@ -2288,14 +2493,34 @@ __device__ __forceinline__ void apply_symbol(const SymParams& sp, double m_re, d
   }
 }
 
-// t axis forward, the momentum-space operator on all four spins, t axis
+// The operator of a transform pass at one momentum, from (sin, cos) of its components.
+__device__ __forceinline__ void site_symbol(const SymParams& sp, const SysDev& S, double2 px,
+                                            double2 py, double2 pz, double2 pt, double2 v[4]) {
+  const double w = sp.diag - (px.y + py.y + pz.y + pt.y);
+  if (sp.kind == SYM_BOSON) {
+    // scalar fields in planes 0-2: D_2 = 1 + w/s (scalar part of the exact overlap
+    // operator), then 1 - D_2/2 twice
+    const double d2 =
+        1.0 + w / sqrt(w * w + px.x * px.x + py.x * py.x + pz.x * pz.x + pt.x * pt.x);
+    v[0] = double2{d2 * v[0].x, d2 * v[0].y};
+    const double k2 = 1.0 - 0.5 * d2;
+    v[1] = double2{k2 * v[1].x, k2 * v[1].y};
+    v[2] = double2{k2 * v[2].x, k2 * v[2].y};
+  } else {
+    const bool m0 = sp.kind == SYM_M0INV || sp.kind == SYM_M0INV_DAG || sp.kind == SYM_PCG;
+    apply_symbol(sp, m0 ? S.pc_re : S.m_re, m0 ? S.pc_im : S.m_im, S.shift, px.x, py.x, pz.x,
+                 pt.x, w, v);
+  }
+}
+
+// t axis forward, the momentum-space operator on all components, t axis
 // inverse, in place on fft_tmp.  Workgroup: (chunk of xc x values, y, z);
 // needs T <= 64 and xc T <= 256.
-template <class R>
+template <class R, int NS>
 __global__ void __launch_bounds__(256) k_fft_t_sym(const SysDev* __restrict__ sys, int nsys,
                                                    const SymParams sp) {
   __shared__ c2<R> A[1024], B[1024];
-  __shared__ c2<R> twf[64], twi[64];
+  __shared__ c2<R> tw[64];
   __shared__ double2 csx[64], cst[64];  // (sin, cos) of the block's x momenta and of every t momentum
   const SysDev& S = sys[find_sys(sys, nsys, blockIdx.x, 2)];
   if (S.active && *S.active == 0) return;
@@ -2305,84 +2530,160 @@ __global__ void __launch_bounds__(256) k_fft_t_sym(const SysDev* __restrict__ sy
   const int nxc = X / XC;
   const int xb = (loc % nxc) * XC;
   const int yz = loc / nxc;  // y + Y z
-  const int y = yz % Y, z = yz / Y;
-  c2<R>* f = (c2<R>*)S.fft_tmp;
-  twiddles<R>(twf, T, -1.0);
-  twiddles<R>(twi, T, 1.0);
-  const double tshift = (S.g.bc < 0 && !sp.periodic) ? 1.0 : 0.0;
-  for (int j = threadIdx.x; j < XC + T; j += blockDim.x) {
-    double sn, cs;
-    if (j < XC) {
-      sincospi(2.0 * (double)(xb + j) / (double)X, &sn, &cs);
-      csx[j] = double2{sn, cs};
-    } else {
-      sincospi((2.0 * (j - XC) + tshift) / (double)T, &sn, &cs);
-      cst[j - XC] = double2{sn, cs};
-    }
-  }
-  const int n = 4 * XC * T;  // element e = (spin T + t) XC + xl
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int xl = e % XC, q = e / XC;
-    const int t = q % T, spin = q / T;
-    A[e] = f[(size_t)spin * V + (xb + xl) + X * (y + Y * (z + Z * t))];
+  const int z = yz / Y, y = yz - z * Y;
+  const SmallDiv dC(XC), dT(T), dl(NS * XC);
+  c2<R>* f = (c2<R>*)S.fft_tmp + xb + X * (y + Y * z);
+  const int XYZ = X * Y * Z;
+  double2 py, pz;
+  stage_in(NS * XC * T,  // element e = (k T + t) XC + xl
+           [&](int e) {
+             const int q = dC.div(e), k = dT.div(q);
+             return ldg2<R>((const c2<R>*)f,
+                            (size_t)k * V + (e - q * XC) + (size_t)XYZ * (q - k * T));
+           },
+           [&](int e, c2<R> v) { A[e] = v; },
+           [&]() {
+             const double shift = S.g.bc < 0 && !sp.periodic ? 1.0 : 0.0;
+             for (int j = threadIdx.x; j < 2 * T + XC; j += blockDim.x) {
+               double2 sc;
+               const double a = j < T       ? 2.0 * j / T
+                                : j < 2 * T ? (2.0 * (j - T) + shift) / T
+                                            : 2.0 * (xb + j - 2 * T) / X;
+               sincospi(a, &sc.x, &sc.y);
+               if (j < T) tw[j] = c2<R>{(R)sc.y, (R)sc.x};
+               else if (j < 2 * T) cst[j - T] = sc;
+               else csx[j - 2 * T] = sc;
+             }
+             sincospi(2.0 * y / Y, &py.x, &py.y);
+             sincospi(2.0 * z / Z, &pz.x, &pz.y);
+           });
+  __syncthreads();
+  int at[4];
+  c2<R> o[4];
+  const int lines = NS * XC, items = lines * dft_groups(T);
+  for (int it = threadIdx.x; it < items; it += blockDim.x) {  // forward t
+    const int g = dl.div(it), ln = it - g * lines;
+    const int k = dC.div(ln), l0 = k * T * XC + (ln - k * XC);
+    line_dft<R>(A + l0, XC, T, tw, g, R(-1), o);
+    dft_places(T, g, XC, at);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) B[l0 + at[q]] = o[q];
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {  // forward t
-    const int xl = e % XC, q = e / XC;
-    const int kt = q % T, spin = q / T;
-    c2<R> acc{(R)0, (R)0};
-    int w = 0;
-    for (int t = 0; t < T; ++t) {
-      acc = cmad<R>(acc, A[(spin * T + t) * XC + xl], twf[w]);
-      w += kt;
-      if (w >= T) w -= T;
-    }
-    B[e] = acc;
-  }
-  __syncthreads();
-  double sy, cy, sz, cz;
-  sincospi(2.0 * (double)y / (double)Y, &sy, &cy);
-  sincospi(2.0 * (double)z / (double)Z, &sz, &cz);
   for (int q = threadIdx.x; q < XC * T; q += blockDim.x) {  // operator at (kx, ky, kz, kt)
-    const int xl = q % XC, kt = q / XC;
-    const double sx = csx[xl].x, cx = csx[xl].y, st = cst[kt].x, ct = cst[kt].y;
-    const double w = sp.diag - (cx + cy + cz + ct);
+    const int kt = dC.div(q), xl = q - kt * XC;
     double2 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const c2<R> u = B[(k * T + kt) * XC + xl];
+      const c2<R> u = k < NS ? B[(k * T + kt) * XC + xl] : c2<R>{R(0), R(0)};
       v[k] = double2{(double)u.x, (double)u.y};
     }
-    if (sp.kind == SYM_BOSON) {
-      // scalar fields in planes 0-2: D_2 = 1 + w/s (scalar part of the exact overlap
-      // operator), then 1 - D_2/2 twice; plane 3 unused
-      const double d2 = 1.0 + w / sqrt(w * w + sx * sx + sy * sy + sz * sz + st * st);
-      v[0] = double2{d2 * v[0].x, d2 * v[0].y};
-      const double k2 = 1.0 - 0.5 * d2;
-      v[1] = double2{k2 * v[1].x, k2 * v[1].y};
-      v[2] = double2{k2 * v[2].x, k2 * v[2].y};
-      v[3] = double2{0.0, 0.0};
-    } else {
-      const bool m0 = sp.kind == SYM_M0INV || sp.kind == SYM_M0INV_DAG || sp.kind == SYM_PCG;
-      apply_symbol(sp, m0 ? S.pc_re : S.m_re, m0 ? S.pc_im : S.m_im, S.shift, sx, sy, sz, st, w,
-                   v);
-    }
+    site_symbol(sp, S, csx[xl], py, pz, cst[kt], v);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) A[(k * T + kt) * XC + xl] = c2<R>{(R)v[k].x, (R)v[k].y};
+    for (int k = 0; k < NS; ++k) A[(k * T + kt) * XC + xl] = c2<R>{(R)v[k].x, (R)v[k].y};
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {  // inverse t
-    const int xl = e % XC, q = e / XC;
-    const int t = q % T, spin = q / T;
-    c2<R> acc{(R)0, (R)0};
-    int w = 0;
-    for (int kt = 0; kt < T; ++kt) {
-      acc = cmad<R>(acc, A[(spin * T + kt) * XC + xl], twi[w]);
-      w += t;
-      if (w >= T) w -= T;
-    }
-    f[(size_t)spin * V + (xb + xl) + X * (y + Y * (z + Z * t))] = acc;
+  for (int it = threadIdx.x; it < items; it += blockDim.x) {  // inverse t
+    const int g = dl.div(it), ln = it - g * lines;
+    const int k = dC.div(ln), xl = ln - k * XC;
+    line_dft<R>(A + k * T * XC + xl, XC, T, tw, g, R(1), o);
+    dft_places(T, g, XYZ, at);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[(size_t)k * V + xl + at[q]] = o[q];
   }
+}
+
+// z and t axes of one (x, y) line, all components: forward, the momentum-space operator,
+// inverse, in place on fft_tmp in the site-line order ((x y) T + t) Z + z with a site's
+// components side by side.  One pass instead of three (k_fft_z twice and k_fft_t_sym): the
+// line stays in LDS, 2 NS fft_xy_plane(Z, T) + Z + T values and 2 (Z + T) doubles.  Bound by
+// the LDS reads of its sums: 16^3 x 32 in FP64 (256 workgroups) 14 us, 3 for each t axis, 2
+// for each z axis, 1.3 for the operator; the three passes took 44.
+template <class R, int NS>
+__global__ void __launch_bounds__(1024) k_fft_zt(const SysDev* __restrict__ sys, int nsys,
+                                                 const SymParams sp) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const SysDev& S = sys[find_sys(sys, nsys, blockIdx.x, 3)];
+  if (S.active && *S.active == 0) return;
+  const int X = S.g.X, Y = S.g.Y, Z = S.g.Z, T = S.g.T;
+  const int xy = blockIdx.x - S.off_zt;
+  const int ZT = Z * T, P = Z + 1, SP = fft_xy_plane(Z, T);
+  const SmallDiv dZ(Z), dT(T), dlz(NS * T), dlt(NS * Z);
+  double2* csz = (double2*)dyn_lds;  // (sin, cos) of every z and t momentum
+  double2* cst = csz + Z;
+  c2<R>* A = (c2<R>*)(cst + T);
+  c2<R>* B = A + NS * SP;
+  c2<R>* twz = B + NS * SP;
+  c2<R>* twt = twz + Z;
+  c2<R>* f = (c2<R>*)S.fft_tmp + (size_t)xy * ZT * NS;
+  auto cell = [&](int e) -> c2<R>& {
+    const int i = e / NS, k = e - i * NS, t = dZ.div(i);
+    return A[k * SP + t * P + (i - t * Z)];
+  };
+  double2 px, py;
+  stage_in(NS * ZT, [&](int e) { return ldg2<R>((const c2<R>*)f, e); },
+           [&](int e, c2<R> v) { cell(e) = v; },
+           [&]() {
+             const double shift = S.g.bc < 0 && !sp.periodic ? 1.0 : 0.0;
+             for (int j = threadIdx.x; j < Z + 2 * T; j += blockDim.x) {
+               double2 sc;
+               const double a = j < Z       ? 2.0 * j / Z
+                                : j < Z + T ? 2.0 * (j - Z) / T
+                                            : (2.0 * (j - Z - T) + shift) / T;
+               sincospi(a, &sc.x, &sc.y);
+               if (j < Z) csz[j] = sc;
+               if (j < Z + T) twz[j] = c2<R>{(R)sc.y, (R)sc.x};
+               else cst[j - Z - T] = sc;
+             }
+             const int y = xy / X;
+             sincospi(2.0 * (xy - y * X) / X, &px.x, &px.y);
+             sincospi(2.0 * y / Y, &py.x, &py.y);
+           });
+  int at[4];
+  c2<R> o[4];
+  // z lines (row (k, t)) and t lines (column (k, z)), from one buffer to the other
+  auto z_axis = [&](const c2<R>* from, c2<R>* to, R sgn) {
+    __syncthreads();
+    for (int it = threadIdx.x; it < NS * T * dft_groups(Z); it += blockDim.x) {
+      const int g = dlz.div(it), ln = it - g * (NS * T);
+      const int k = dT.div(ln), row = k * SP + (ln - k * T) * P;
+      line_dft<R>(from + row, 1, Z, twz, g, sgn, o);
+      dft_places(Z, g, 1, at);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) to[row + at[q]] = o[q];
+    }
+  };
+  auto t_axis = [&](const c2<R>* from, c2<R>* to, R sgn) {
+    __syncthreads();
+    for (int it = threadIdx.x; it < NS * Z * dft_groups(T); it += blockDim.x) {
+      const int g = dlt.div(it), ln = it - g * (NS * Z);
+      const int k = dZ.div(ln), col = k * SP + (ln - k * Z);
+      line_dft<R>(from + col, P, T, twt, g, sgn, o);
+      dft_places(T, g, P, at);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) to[col + at[q]] = o[q];
+    }
+  };
+  z_axis(A, B, R(-1));
+  t_axis(B, A, R(-1));
+  __syncthreads();
+  for (int i = threadIdx.x; i < ZT; i += blockDim.x) {  // operator at (kx, ky, kz, kt)
+    const int kt = dZ.div(i), kz = i - kt * Z;
+    c2<R>* a = A + kt * P + kz;
+    double2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const c2<R> u = k < NS ? a[k * SP] : c2<R>{R(0), R(0)};
+      v[k] = double2{(double)u.x, (double)u.y};
+    }
+    site_symbol(sp, S, px, py, csz[kz], cst[kt], v);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) a[k * SP] = c2<R>{(R)v[k].x, (R)v[k].y};
+  }
+  t_axis(A, B, R(1));
+  z_axis(B, A, R(1));
+  __syncthreads();
+  for (int e = threadIdx.x; e < NS * ZT; e += blockDim.x) f[e] = cell(e);
 }
 
 // ------------------------------------------- transforms of fixed length
@@ -3101,28 +3402,6 @@ __global__ void __launch_bounds__(512) k_truth_finish(const SysDev* __restrict__
   if (threadIdx.x == 0) S.part_c[lb] = tot;
 }
 
-// ------------------------------------------------- RHMC bosonic action (eq. acws)
-// phi: complex128 [V] (site order).  Pack planes of e_out2 (FP64 planar):
-// 0 = phi, 1 = W' = m phi + (g/2) phi^2, 2 = conj(W'), 3 = 0.
-__global__ void __launch_bounds__(256) k_boson_pack(const SysDev* __restrict__ sys,
-                                                     const int* __restrict__ bmap, int nb_total) {
-  const int L = xcd_logical_block(nb_total);
-  const SysDev& S = sys[bmap[L]];
-  const int lb = L - S.blk0;
-  const int V = S.g.V;
-  const int i0 = lb * S.spb;
-  const int i1 = min(V, i0 + S.spb);
-  const double lr = 0.5 * S.g_re, li = 0.5 * S.g_im;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    const double2 f = S.phi[i];
-    const double f2r = f.x * f.x - f.y * f.y, f2i = 2.0 * f.x * f.y;
-    const double wr = S.m_re * f.x - S.m_im * f.y + lr * f2r - li * f2i;
-    const double wi = S.m_re * f.y + S.m_im * f.x + lr * f2i + li * f2r;
-    double2 v[4] = {f, double2{wr, wi}, double2{wr, -wi}, double2{0.0, 0.0}};
-    store_sp<double>((double2*)S.e_in, V, i, v);
-  }
-}
-
 // From the transformed planes (e_out: D_2 phi, K W', K conj(W'), K = 1 - D_2/2):
 //   S partials  2 Re conj(phi) D_2 phi + Re conj(W') K W'  -> part_c
 //   G = 2 [2 D_2 phi + conj(m + g phi) K W']   (G_out, may be null)
@@ -3140,10 +3419,10 @@ __global__ void __launch_bounds__(256) k_boson_finish(const SysDev* __restrict__
   const int i1 = min(V, i0 + S.spb);
   double acc = 0.0;
   for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    double2 a[4], t[4];
-    load_sp<double>((const double2*)S.e_in, V, i, a);   // phi, W', conj W'
-    load_sp<double>((const double2*)S.e_out, V, i, t);  // D_2 phi, K W', K conj W'
-    const double2 f = a[0], w = a[1];
+    double2 t[3];  // D_2 phi, K W', K conj W'
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = ldg2<double>((const double2*)S.e_out, (size_t)k * V + i);
+    const double2 f = S.phi[i], w = w_prime(S, f);
     acc += 2.0 * (f.x * t[0].x + f.y * t[0].y) + (w.x * t[1].x + w.y * t[1].y);
     if (G_out) {
       // conj(m + g phi)

@@ -230,7 +230,7 @@ struct SysBuf {
   double2 *shx = nullptr, *shp = nullptr;  // multi-shift CG on MdagM: solutions, directions
   double* shc = nullptr;        //   per-shift coefficients
   int nshift = 0;
-  int xc = 1, off_xy = 0, off_z = 0, off_t = 0;  // momentum-space pass geometry
+  int xc = 1, off_xy = 0, off_z = 0, off_t = 0, off_zt = 0;  // momentum-space pass geometry
 };
 
 // Sites per workgroup of `block` threads.  Automatic choice (spt = 0) from the sites of the
@@ -377,13 +377,16 @@ enum Table {
   T_NT
 };
 
-// x values per workgroup of the t pass: the largest divisor of X with xc T <= 64 (at 16^4,
-// 1024 workgroups: four per CU hide the latency of the per-momentum symbol; 256 took 15 us
-// per pass, 1024 take 12.6 us).
+// LDS a transform pass may take (of 160 KiB); the xy and z passes of the largest lattices
+// (X Y = X Z = 1024, extents up to 64) need 141 KiB.
+constexpr size_t FFT_LDS = 148 * 1024;
+
+// x values per workgroup of the t pass: the largest divisor of X with xc T <= 256 (the
+// kernel's LDS; MdagM of the 24^3 x 48 fermion with 64, 128, 256: 621, 509, 453 us).
 int pick_xc(int X, int T) {
   int best = 1;
   for (int d = 1; d <= X; ++d)
-    if (X % d == 0 && d * T <= 64) best = d;
+    if (X % d == 0 && d * T <= 256) best = d;
   return best;
 }
 
@@ -443,7 +446,7 @@ struct Engine {
                                     // fallback solver gets what the mixed one left)
   bool force_fallback = false;      // hand every system to the FP64 solver at its first
                                     // reliable update (OV_FORCE_FALLBACK=1; tests)
-  int nb_xy = 0, nb_z = 0, nb_t = 0;  // workgroups of the momentum-space passes
+  int nb_xy = 0, nb_z = 0, nb_t = 0, nb_zt = 0;  // workgroups of the momentum-space passes
   SysDev* ftab = nullptr;           // device: (system, shift) table of the rational force
   SysDev* gwtab = nullptr;          // device: 2 nsys multi-shift entries of the GW inner operator
   int* gwbmap = nullptr;            // device: 2 nb_total workgroups -> entry
@@ -552,7 +555,7 @@ struct Engine {
     ctl_all = dry ? nullptr : (int*)(dstat_all + (size_t)6 * nsys);
     ctl_words = ctl_bytes / sizeof(int);
     act_all = (int*)bp.take(sizeof(int) * 2 * nsys);
-    int blk = 0, nxy = 0, nz = 0, nt = 0;
+    int blk = 0, nxy = 0, nz = 0, nt = 0, nzt = 0;
     long long total_sites = 0;
     for (int s = 0; s < nsys; ++s) {
       const ov_params& p = ctxs[s]->p;
@@ -571,11 +574,13 @@ struct Engine {
       const int X = p.dims[0], Y = p.dims[1], Z = p.dims[2], T = p.dims[3];
       b.xc = pick_xc(X, T);
       b.off_xy = nxy;
-      nxy += 4 * Z * T;
+      nxy += Z * T;
       b.off_z = nz;
-      nz += 4 * Y * T;
+      nz += Y * T;
       b.off_t = nt;
       nt += (X / b.xc) * Y * Z;
+      b.off_zt = nzt;
+      nzt += X * Y;
       b.cg_s = dry ? nullptr : cg_all + (size_t)s * CG_NSLOT;
       b.stat = dry ? nullptr : stat_all + (size_t)s * 4;
       b.ms_b_stat = (dry || !pl.gw) ? nullptr : stat_all + (size_t)(nsys + s) * 4;
@@ -593,6 +598,7 @@ struct Engine {
     nb_xy = nxy;
     nb_z = nz;
     nb_t = nt;
+    nb_zt = nzt;
     // everything a captured launch sequence bakes in besides the table and workspace
     // addresses: per system its lattice, boundary, partition and transform chunking
     geo_key.clear();
@@ -788,6 +794,13 @@ ov_status res_setup(ov_ctx* c) {
   const void* kern[] = {res_kernel<double>(1), res_kernel<float>(1), res_kernel<float>(2)};
   for (const void* k : kern)
     HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RES_MAX_LDS));
+  const void* fft[] = {(const void*)k_fft_xy<double, 4>, (const void*)k_fft_xy<float, 4>,
+                       (const void*)k_fft_xy<double, 3>, (const void*)k_fft_z<double, 4>,
+                       (const void*)k_fft_z<float, 4>,   (const void*)k_fft_z<double, 3>,
+                       (const void*)k_fft_zt<double, 4>, (const void*)k_fft_zt<float, 4>,
+                       (const void*)k_fft_zt<double, 3>};
+  for (const void* k : fft)
+    HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS));
   HIPCHK(c, hipMalloc((void**)&c->res_sh, sizeof(ResShared)));
   HIPCHK(c, hipMemsetAsync(c->res_sh, 0, sizeof(ResShared), c->priv));
   HIPCHK(c, hipEventCreateWithFlags(&c->ev_res, hipEventDisableTiming));
@@ -912,6 +925,7 @@ SysDev base_dev(const SysBuf& b) {
   d.off_xy = b.off_xy;
   d.off_z = b.off_z;
   d.off_t = b.off_t;
+  d.off_zt = b.off_zt;
   return d;
 }
 
@@ -941,11 +955,13 @@ ov_status upload_tables(Engine& E) {
   std::memcpy(c->stage, E.htab.data(), sizeof(SysDev) * (size_t)E.ntab * E.nsys);
   if (!E.io.empty())
     for (int s = 0; s < E.nsys; ++s) {
-      SysDev& d = ((SysDev*)c->stage)[(size_t)T_APPLY * E.nsys + s];
-      d.io_in = (const double2*)E.io[s].in;
-      d.io_pin = E.io[s].pin;
-      d.io_pout = E.io[s].pout;
-      d.io_out = (double2*)E.io[s].out;
+      for (int t : {(int)T_APPLY, (int)T_APPLY2}) {
+        SysDev& d = ((SysDev*)c->stage)[(size_t)t * E.nsys + s];
+        d.io_in = (const double2*)E.io[s].in;
+        d.io_pin = E.io[s].pin;
+        d.io_pout = E.io[s].pout;
+        d.io_out = (double2*)E.io[s].out;
+      }
     }
   int* m = (int*)at(E.bmap);
   for (int s = 0; s < E.nsys; ++s)
@@ -1305,16 +1321,43 @@ int site_block(const Engine& E) {
 
 // e_out = op(e_in) for a momentum-space operator (forward DFTs, symbol, inverse
 // DFTs through fft_tmp); e_out may alias e_in.
-template <class R>
-void launch_sym(const Engine& E, int t, int kind) {
+template <class R, int NS = 4>
+void launch_sym(const Engine& E, int t, int kind, SymIo io = {}) {
   if (kind == SYM_PCG && pcg_fixed<R>(E, t)) return;
   const SymParams sp = sym_params(E.lead, kind);
   const SysDev* T = tab(E, t);
-  k_fft_xy<R><<<E.nb_xy, 256, 0, E.st>>>(T, E.nsys, 0, sp.periodic);
-  k_fft_z<R><<<E.nb_z, 256, 0, E.st>>>(T, E.nsys, 0);
-  k_fft_t_sym<R><<<E.nb_t, 256, 0, E.st>>>(T, E.nsys, sp);
-  k_fft_z<R><<<E.nb_z, 256, 0, E.st>>>(T, E.nsys, 1);
-  k_fft_xy<R><<<E.nb_xy, 256, 0, E.st>>>(T, E.nsys, 1, sp.periodic);
+  // threads: the groups of a workgroup's lines in as few equal rounds as `most` threads allow
+  auto threads = [](int items, int most) {
+    const int rounds = (items + most - 1) / most;
+    return ((items + rounds - 1) / rounds + 63) / 64 * 64;
+  };
+  int nxy = 64, nz = 64, nt = 64, nzt = 64;
+  size_t lxy = 0, lz = 0, lzt = 0;
+  for (const SysBuf& b : E.sb) {
+    const int* d = b.ctx->p.dims;
+    const int gx = dft_groups(d[0]), gy = dft_groups(d[1]), gz = dft_groups(d[2]), gt = dft_groups(d[3]);
+    nxy = std::max(nxy, threads(NS * std::max(d[1] * gx, d[0] * gy), 512));
+    nz = std::max(nz, threads(NS * d[0] * gz, 512));
+    nt = std::max(nt, threads(std::max(NS * b.xc * gt, b.xc * d[3]), 256));
+    nzt = std::max(nzt, threads(NS * std::max(d[3] * gz, d[2] * gt), 1024));
+    lxy = std::max(lxy, sizeof(c2<R>) * (2 * NS * fft_xy_plane(d[0], d[1]) + d[0] + d[1]) + sizeof(double2));
+    lz = std::max(lz, sizeof(c2<R>) * (NS * d[0] * d[2] + d[2]));
+    lzt = std::max(lzt, sizeof(c2<R>) * (2 * NS * fft_xy_plane(d[2], d[3]) + d[2] + d[3]) +
+                            sizeof(double2) * (d[2] + d[3]));
+  }
+  // the (z, t) line in one pass where LDS holds it; three passes over planes else (M of the
+  // overlap_exact form: 22x14x10x26 103 against 124 us, 16^3 x 32 85 against 101, 4^2 x
+  // 24 x 48, of 16 workgroups, 69 against 69)
+  io.zt = lzt <= FFT_LDS;
+  k_fft_xy<R, NS><<<E.nb_xy, nxy, lxy, E.st>>>(T, E.nsys, 0, sp.periodic, io);
+  if (io.zt) {
+    k_fft_zt<R, NS><<<E.nb_zt, nzt, lzt, E.st>>>(T, E.nsys, sp);
+  } else {
+    k_fft_z<R, NS><<<E.nb_z, nz, lz, E.st>>>(T, E.nsys, 0);
+    k_fft_t_sym<R, NS><<<E.nb_t, nt, 0, E.st>>>(T, E.nsys, sp);
+    k_fft_z<R, NS><<<E.nb_z, nz, lz, E.st>>>(T, E.nsys, 1);
+  }
+  k_fft_xy<R, NS><<<E.nb_xy, nxy, lxy, E.st>>>(T, E.nsys, 1, sp.periodic, io);
 }
 
 ov_status check_launch(ov_ctx* c) {
@@ -1461,29 +1504,24 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
   const ov_ctx* c = E.lead;
   const double diag = 4.0 - c->p.M0;
   if (c->p.dirac != OV_DIRAC_OVERLAP_MS && op >= OV_OP_DOV && op <= OV_OP_MDAGM) {
-    // momentum-space D (x64 -> r64; MdagM through u64)
+    // momentum-space D and Y, on the caller's fields unless they overlap: then on the planar
+    // copies (x64 -> r64); MdagM through u64
     const int nb = E.nb_total, bl = E.block;
-    switch (op) {
-      case OV_OP_DOV:
-        launch_sym<double>(E, T_APPLY, SYM_D);
-        break;
-      case OV_OP_DOV_DAG:
-        launch_sym<double>(E, T_APPLY, SYM_D_DAG);
-        break;
-      case OV_OP_M:
-        launch_sym<double>(E, T_APPLY, SYM_D);
-        k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY), E.bmap, nb, 0);
-        break;
-      case OV_OP_M_DAG:
-        launch_sym<double>(E, T_APPLY, SYM_D_DAG);
-        k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY), E.bmap, nb, 1);
-        break;
-      case OV_OP_MDAGM:
-        launch_sym<double>(E, T_APPLY, SYM_D);
-        k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY), E.bmap, nb, 0);
-        launch_sym<double>(E, T_APPLY2, SYM_D_DAG);
-        k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY2), E.bmap, nb, 1);
-        break;
+    const bool dag = op == OV_OP_DOV_DAG || op == OV_OP_M_DAG;
+    const int kind = dag ? SYM_D_DAG : SYM_D;
+    const bool yuk = op >= OV_OP_M;
+    SymIo io;
+    io.in = direct;
+    io.out = direct && op != OV_OP_MDAGM;
+    io.yuk = direct && yuk ? 1 + dag : 0;
+    launch_sym<double>(E, T_APPLY, kind, io);
+    if (yuk && !direct) k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY), E.bmap, nb, dag);
+    if (op == OV_OP_MDAGM) {
+      io.in = 0;
+      io.out = direct;
+      io.yuk = direct ? 2 : 0;
+      launch_sym<double>(E, T_APPLY2, SYM_D_DAG, io);
+      if (!direct) k_yuk<double><<<nb, bl, 0, E.st>>>(tab(E, T_APPLY2), E.bmap, nb, 1);
     }
     return check_launch(E.lead);
   }
@@ -1513,7 +1551,11 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
       break;
     case OV_OP_M0INV:
     case OV_OP_M0INV_DAG:
-      launch_sym<double>(E, T_APPLY, op == OV_OP_M0INV ? SYM_M0INV : SYM_M0INV_DAG);
+    {
+      SymIo io;
+      io.in = io.out = direct;
+      launch_sym<double>(E, T_APPLY, op == OV_OP_M0INV ? SYM_M0INV : SYM_M0INV_DAG, io);
+    }
       break;
     case OV_OP_MDAGM:
       k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
@@ -2725,19 +2767,25 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
-  TRY(reset_stats(E));
+  // operators without a multi-shift work on the caller's fields themselves, unless they
+  // overlap, and report nothing from the device
+  const bool shifts = op != OV_OP_HW && op != OV_OP_M0INV && op != OV_OP_M0INV_DAG &&
+                      (op < OV_OP_DOV || c->p.dirac == OV_DIRAC_OVERLAP_MS);
+  if (shifts)
+    TRY(reset_stats(E));
+  else
+    std::memset(c->pinned, 0, sizeof(double) * CG_NSLOT * E.nsys + sizeof(int) * E.ctl_words);
   const size_t vb = (size_t)E.sb[0].V * 4 * sizeof(double2);
   E.io.resize(nrhs);
   for (int r = 0; r < nrhs; ++r)
     E.io[r] = {(const char*)in + r * vb, E.sb[r].x64, E.sb[r].r64, (char*)out + r * vb};
   TRY(run_apply(E, op, phi));
-  // H_W works on the caller's fields themselves, unless they overlap
   const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
-  const bool direct = op == OV_OP_HW && (a > b ? a - b : b - a) >= nrhs * vb;
+  const bool direct = !shifts && (a > b ? a - b : b - a) >= nrhs * vb;
   if (!direct) TRY(pack64(E));
   TRY(apply_sequence(E, op, direct));
   if (!direct) TRY(unpack64(E));
-  TRY(read_scalars(E));
+  TRY(shifts ? read_scalars(E) : sync(E));
   ov_status rc = OV_OK;
   for (int s = 0; s < nrhs; ++s) {
     const int bits = sys_ctl(E, s).bits;
@@ -3452,13 +3500,13 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   E.htab.assign((size_t)E.ntab, SysDev{});
   SysDev d = base_dev(b);
   d.phi = (const double2*)phi;
-  d.e_in = b.x64;      // packed planes phi, W', conj W'
-  d.e_out = b.r64;     // transformed planes
+  d.e_out = b.r64;     // transformed planes of phi, W', conj W'
   d.fft_tmp = b.src64b;
   E.htab[T_APPLY] = d;
   TRY(upload_tables(E));
-  k_boson_pack<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
-  launch_sym<double>(E, T_APPLY, SYM_BOSON);
+  SymIo io;
+  io.in = 2;
+  launch_sym<double, 3>(E, T_APPLY, SYM_BOSON, io);
   k_boson_finish<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total,
                                                     (double2*)G, (double2*)F);
   k_cg_scalar<<<1, 256, 0, E.st>>>(tab(E, T_APPLY), 1, 4);  // S_B -> BB

@@ -3,6 +3,7 @@ their remainders, and a call in place.  Tolerance: nine FP64 terms of unit-size 
 per value, 1e-14 of the field's norm as in the parity tests."""
 import ctypes as C
 
+import numpy as np
 import pytest
 
 from paper_1005_3276_amd import _lib as L
@@ -81,3 +82,55 @@ def test_uneven_batch_with_per_pass_kernels(orc):
         o = orc.Oracle(d, inner_tol=1e-13, **CFG2)
         for r in range(b.shape[0]):
             assert o.residual(b[r], host(x)[r], p) <= 1e-10, (d, r)
+
+
+# momentum-space operators: the smallest, planes and slabs of 1024 sites, extents of 2 mod
+# 4, and (z, t) lines beyond LDS (2 x 4 x 64 x 64: separate z and t passes)
+MOMENTUM = [((2, 2, 2, 2), 1), ((64, 16, 2, 4), -1), ((16, 2, 64, 6), -1), ((22, 6, 10, 14), -1),
+            ((4, 2, 26, 46), 1), ((2, 4, 64, 64), -1)]
+
+
+@pytest.mark.parametrize("dims,bc", MOMENTUM)
+def test_momentum_operators_closed_form(dims, bc):
+    """D, D^dag, M, M^dag and MdagM of the exact overlap form on the caller's fields and in
+    place, against the momentum-space 4 x 4 matrix.  Sums of at most 64 terms per axis
+    and direction, eight of them: 1e-12 as for the full sizes in the parity tests."""
+    import closed_form as cf
+    print(f"[momentum] {dims} bc={bc}", flush=True)
+    phi, x = inputs.draw(dims, nrhs=2, sigma2=0.25, seed=86)
+    lat = lattice(dims, bc_t=bc, dirac="overlap_exact", m=0.05, g=0.3)
+    sym = cf.dov_symbol(cf.exact_sign_symbol(dims, bc))
+    dag = np.conj(np.swapaxes(sym, -1, -2))
+    cp = (0.05 + 0.3 * phi)[..., None]
+    c = np.concatenate([np.conj(cp), np.conj(cp), cp, cp], axis=-1)  # Y psi = c psi
+    D = lambda v: cf.apply_symbol(sym, v, dims, bc)
+    Dd = lambda v: cf.apply_symbol(dag, v, dims, bc)
+    M = lambda v: D(v) + c * v
+    Md = lambda v: Dd(v) + np.conj(c) * v
+    want = dict(dov=D, dov_dag=Dd, m=M, m_dag=Md, mdagm=lambda v: Md(M(v)))
+    for op, f in want.items():
+        y = host(lat.apply(op, dev(x), dev(phi))[0])
+        z = dev(x)
+        p = dev(phi)
+        torch.cuda.synchronize()
+        st = (L.OvStats * 2)()
+        assert L.lib().ov_apply(lat._h, L.OPS[op], C.c_void_p(z.data_ptr()), C.c_void_p(z.data_ptr()),
+                                C.c_void_p(p.data_ptr()), 2, st) == 0
+        for r in range(2):
+            w = f(x[r])
+            check(y[r], w, 1e-12, f"{op} rhs {r}")
+            check(host(z)[r], w, 1e-12, f"{op} in place rhs {r}")
+
+
+@pytest.mark.parametrize("dims", [(6, 4, 10, 2), (2, 2, 40, 44)])
+def test_boson_ragged_vs_oracle(orc, dims):
+    """The bosonic action's three planes, in one (z, t) pass and in separate passes; 1e-12
+    as above."""
+    print(f"[boson] {dims}", flush=True)
+    kw = dict(m=0.05, g=0.3)
+    phi, _ = inputs.draw(dims, nrhs=1, sigma2=0.25, seed=87)
+    S, G, F = lattice(dims, **kw).boson(dev(phi))
+    So, Go, Fo = orc.Oracle(dims, **kw).boson(phi)
+    assert abs(S - So) <= 1e-12 * abs(So)
+    check(host(G), Go, 1e-12)
+    check(host(F), Fo, 1e-12)
