@@ -91,6 +91,7 @@ struct SysDev {
   void* io_pin;
   void* io_pout;
   double2* io_out;
+  int src_io;               // resident multi-shift source: 1 io_in, 2 g5 io_in (0: src)
 };
 
 // CG scalar slots
@@ -1518,7 +1519,18 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
   c2<R> r[K][4], t[K][4], hops[K][4];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    load_sp<R>((const c2<R>*)S.src, g.V, site[k].gi, r[k]);
+    if constexpr (sizeof(R) == sizeof(double)) {
+      if (S.src_io) {  // the caller's field: no packed copy, no pass that makes g5 times it
+        load_io(S.io_in, site[k].gi, r[k]);
+        if (S.src_io == 2)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) r[k][q] = c2<R>{-r[k][q].x, -r[k][q].y};
+      } else {
+        load_sp<R>((const c2<R>*)S.src, g.V, site[k].gi, r[k]);
+      }
+    } else {
+      load_sp<R>((const c2<R>*)S.src, g.V, site[k].gi, r[k]);
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) t[k][q] = c2<R>{R(0), R(0)};
   }
@@ -1605,6 +1617,28 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
   }
 }
 
+// n > 0 values to LDS, four loads of a thread in flight: get(e) reads one (a thread without
+// a value reads the last one), put(e, v) stores it, `between` runs while the first four are on
+// their way.
+template <class Get, class Put, class F>
+__device__ __forceinline__ void stage_in(int n, Get get, Put put, F between) {
+  const int bd = blockDim.x;
+  int e0 = threadIdx.x;
+  decltype(get(0)) v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
+  between();
+  for (;;) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * bd < n) put(e0 + u * bd, v[u]);
+    e0 += 4 * bd;
+    if (e0 >= n) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
+  }
+}
+
 // ------------------------------------------------- multi-shift: coefficients
 // One workgroup per system.  Shift k ran N_k iterations (first n with its bit
 // clear in h_active).  With z^j = zeta_k^j, alpha_{j,k} = alpha_j z^{j+1}/z^j,
@@ -1612,6 +1646,7 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
 //   y_k = sum_j z^j S_k^j r_j,  S_k^j = alpha_{j,k} + beta_{j,k} S_k^{j+1},  S_k^{N_k} = 0,
 //   acc = sum_j c_j r_j,  c_j = sum_k a_k z^j S_k^j,
 //   eps = H acc = sum_j d_j t_j,  d_j = c_j - beta_j c_{j+1}   (H r_j = t_j - beta_{j-1} t_{j-1}).
+constexpr int COEF_THREADS = 512;
 constexpr int COEF_LDS_ITERS = 160;  // history rows staged in LDS (larger N reads global)
 
 // LDS of k_ms_coef.  The staged path works on these arrays only (no pointer that may
@@ -1702,7 +1737,7 @@ __device__ __forceinline__ void coef_second(const SysDev& S, const MsParams* mp,
   }
 }
 
-__global__ void __launch_bounds__(256) k_ms_coef(const SysDev* __restrict__ sys, int nsys,
+__global__ void __launch_bounds__(COEF_THREADS) k_ms_coef(const SysDev* __restrict__ sys, int nsys,
                                                  int launched, const MsParams mp_,
                                                  const ResEpoch re) {
   __shared__ CoefLds L;
@@ -1742,12 +1777,16 @@ __global__ void __launch_bounds__(256) k_ms_coef(const SysDev* __restrict__ sys,
   const int N = L.N;
   if (N <= COEF_LDS_ITERS) {
     // stage rows 0..N of the history (coalesced)
-    for (int j = threadIdx.x; j <= N; j += blockDim.x) {
-      L.rho[j] = S.h_rho[j];
-      L.alpha[j] = S.h_alpha[j];
-      L.act[j] = S.h_active[j];
-    }
-    for (int q = threadIdx.x; q < (N + 1) * MAXP; q += blockDim.x) L.zeta[q] = S.h_zeta[q];
+    const double* zeta = S.h_zeta;
+    stage_in((N + 1) * MAXP, [&](int q) { return ldg(zeta, q); },
+             [&](int q, double v) { L.zeta[q] = v; },
+             [&]() {
+               for (int j = threadIdx.x; j <= N; j += blockDim.x) {
+                 L.rho[j] = S.h_rho[j];
+                 L.alpha[j] = S.h_alpha[j];
+                 L.act[j] = S.h_active[j];
+               }
+             });
     __syncthreads();
     // N_k, the first iteration with shift k inactive: one wave per shift, a ballot per
     // 64 iterations
@@ -1764,23 +1803,41 @@ __global__ void __launch_bounds__(256) k_ms_coef(const SysDev* __restrict__ sys,
       }
       if (lane == 0) L.nk[k] = nk;
     }
+    for (int j = threadIdx.x; j < N; j += blockDim.x) L.g[j] = L.rho[j + 1] / L.rho[j];
+    __syncthreads();
     // the recurrence factors alpha_{j,k}, beta_{j,k} for every (k, j) at once; the
-    // per-shift chains below are then multiply-adds on LDS operands
+    // per-shift chains below are then multiply-adds on LDS operands, read eight
+    // iterations at a time (one by one, each waited for, N = 111 took 14 us, not 6)
     for (int q = threadIdx.x; q < np * N; q += blockDim.x) {
       const int k = q / N, j = q - k * N;
       const double zj = L.zeta[j * MAXP + k];
       const double zr = L.zeta[(j + 1) * MAXP + k] / zj;
       L.u[k][j] = L.alpha[j] * zr;
-      L.cp[k][j] = (L.rho[j + 1] / L.rho[j]) * zr * zr;
+      L.cp[k][j] = L.g[j] * zr * zr;
     }
     __syncthreads();
     const double rho0 = L.rho[0];
     for (int k = threadIdx.x; k < np; k += blockDim.x) {
       const int Nk = L.nk[k];
+      const double ck = mp->coef[k];
       double Sk = 0.0;
-      for (int j = Nk - 1; j >= 0; --j) {
-        Sk = L.u[k][j] + L.cp[k][j] * Sk;
-        L.u[k][j] = mp->coef[k] * L.zeta[j * MAXP + k] * Sk;  // term (k, j)
+      for (int j = Nk - 1; j >= 0; j -= 8) {  // the last eight may reach below 0
+        double u[8], b[8], z[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int q = max(j - i, 0);
+          u[i] = L.u[k][q];
+          b[i] = L.cp[k][q];
+          z[i] = L.zeta[q * MAXP + k];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          Sk = u[i] + b[i] * Sk;
+          u[i] = ck * z[i] * Sk;  // term (k, j - i)
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (j >= i) L.u[k][j - i] = u[i];
       }
       for (int j = Nk; j < N; ++j) L.u[k][j] = 0.0;
       if (rho0 > 0.0) L.res[k] = fabs(L.zeta[Nk * MAXP + k]) * sqrt(L.rho[Nk] / rho0);
@@ -1795,7 +1852,7 @@ __global__ void __launch_bounds__(256) k_ms_coef(const SysDev* __restrict__ sys,
     __syncthreads();
     for (int j = threadIdx.x; j < N; j += blockDim.x) {
       const double cn = (j + 1 < N) ? L.c[j + 1] : 0.0;
-      S.coef_d[j] = L.c[j] - (L.rho[j + 1] / L.rho[j]) * cn;
+      S.coef_d[j] = L.c[j] - L.g[j] * cn;
     }
     if (S.coef_d2 && N > 0)
       coef_second(S, mp, N, L.rho, L.alpha, &L.u[0][0], &L.cp[0][0], L.g, L.td, L.to,
@@ -1866,10 +1923,15 @@ enum EpiMode {
 // Like the other kernels without neighbours, k_ms_combine takes its workgroups as dispatched,
 // round-robin over the XCDs: in a batch whose members finish one by one, contiguous shares
 // leave the XCDs of the finished ones idle.
+// A site's sum runs over jw groups of threads, each with every jw-th pair of basis fields,
+// added up in LDS (jw > 1 for small lattices, whose one thread per site leaves the chip idle
+// and waits for memory N / 2 times: launch_combine).  aos: 1 psi is the caller's io_in,
+// 2 the result goes to io_out.
 template <class R>
-__global__ void __launch_bounds__(256) k_ms_combine(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
-                                                     int nb_total, int mode) {
+__global__ void __launch_bounds__(512) k_ms_combine(const SysDev* __restrict__ sys, const int* __restrict__ bmap,
+                                                     int mode, int jw, int aos) {
   __shared__ double lds[17];
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int L = blockIdx.x;
   const int s = bmap[L];
   const SysDev& S = sys[s];
@@ -1886,12 +1948,16 @@ __global__ void __launch_bounds__(256) k_ms_combine(const SysDev* __restrict__ s
   double alpha = 0.0;
   if (mode == EPI_MDAG_CG) alpha = S.cg_s[CG_ALPHA];
   double acc = 0.0;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+  const int nt = blockDim.x / jw;  // sites at a time
+  const int grp = threadIdx.x / nt, tl = threadIdx.x - grp * nt;
+  for (int ib = i0; ib < i1; ib += nt) {
+    const bool on = ib + tl < i1;
+    const int i = on ? ib + tl : i1 - 1;
     double2 e[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) e[k] = double2{0.0, 0.0};
-    int j = 0;
-    for (; j + 1 < N; j += 2) {
+    int j = 2 * grp;
+    for (; j + 1 < N; j += 2 * jw) {
       const double d0 = d[j], d1 = d[j + 1];
       const c2<R>* b0 = basis + (size_t)j * slot;
       const c2<R>* b1 = b0 + slot;
@@ -1914,15 +1980,49 @@ __global__ void __launch_bounds__(256) k_ms_combine(const SysDev* __restrict__ s
         e[k].y += d0 * (double)v0[k].y;
       }
     }
+    if (jw > 1) {
+      double2* part = (double2*)dyn_lds;  // [group - 1][component][site]
+      if (ib > i0) __syncthreads();
+      if (grp > 0)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part[((grp - 1) * 4 + k) * nt + tl] = e[k];
+      __syncthreads();
+      if (grp > 0) continue;
+      for (int q = 0; q < jw - 1; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double2 v = part[(q * 4 + k) * nt + tl];
+          e[k].x += v.x;
+          e[k].y += v.y;
+        }
+    }
+    if (!on) continue;
+    auto write = [&](const c2<R> v[4]) {
+      if constexpr (sizeof(R) == sizeof(double)) {
+        if (aos & 2) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) stg2<double>(S.io_out, (size_t)i * 4 + k, v[k]);
+          return;
+        }
+      }
+      store_sp<R>((c2<R>*)S.e_out, V, i, v);
+    };
     if (mode == EPI_SIGN) {
       c2<R> o[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) o[k] = c2<R>{(R)e[k].x, (R)e[k].y};
-      store_sp<R>((c2<R>*)S.e_out, V, i, o);
+      write(o);
       continue;
     }
     c2<R> p[4];
-    load_sp<R>((const c2<R>*)S.e_in, V, i, p);
+    if constexpr (sizeof(R) == sizeof(double)) {
+      if (aos & 1)
+        load_io(S.io_in, i, p);
+      else
+        load_sp<R>((const c2<R>*)S.e_in, V, i, p);
+    } else {
+      load_sp<R>((const c2<R>*)S.e_in, V, i, p);
+    }
     double2 o[4];
     if (mode == EPI_DOV || mode == EPI_M) {
       o[0] = double2{(double)p[0].x - e[0].x, (double)p[0].y - e[0].y};
@@ -1987,7 +2087,7 @@ __global__ void __launch_bounds__(256) k_ms_combine(const SysDev* __restrict__ s
     c2<R> ov[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) ov[k] = c2<R>{(R)o[k].x, (R)o[k].y};
-    store_sp<R>((c2<R>*)S.e_out, V, i, ov);
+    write(ov);
     if (mode == EPI_M) {
       acc += norm2_sp(ov);
       if (S.e_out2) {
@@ -2145,28 +2245,6 @@ struct SmallDiv {
     return d == 1 ? e : (int)__umulhi((unsigned)e, m);
   }
 };
-
-// n > 0 values to LDS, four loads of a thread in flight: get(e) reads one (a thread without
-// a value reads the last one), put(e, v) stores it, `between` runs while the first four are on
-// their way.
-template <class Get, class Put, class F>
-__device__ __forceinline__ void stage_in(int n, Get get, Put put, F between) {
-  const int bd = blockDim.x;
-  int e0 = threadIdx.x;
-  decltype(get(0)) v[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
-  between();
-  for (;;) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (e0 + u * bd < n) put(e0 + u * bd, v[u]);
-    e0 += 4 * bd;
-    if (e0 >= n) return;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = get(min(e0 + u * bd, n - 1));
-  }
-}
 
 // Values k = g, N - g, N/2 - g and N/2 + g of the transform of one line of even length N
 // (elements a[j st] in LDS, twiddles tw[m] = (cos, sin) 2 pi m / N, sgn the exponent's sign),

@@ -418,6 +418,7 @@ struct Engine {
   SysDev* tables = nullptr;         // device: ntab * nsys
   std::vector<SysDev> htab;         // host copy
   size_t up_bytes = 0;              // bytes from `tables` to the end of the uploaded region
+  size_t up_head = 0;               // bytes from stat_all to `tables`
   int ntab = T_NT;                  // tables this engine has: the first two, or all (solves)
   int* bmap = nullptr;              // device: logical workgroup -> system
   // the caller's fields and their planar twins per system (SysDev io_*), copied into the
@@ -544,16 +545,6 @@ struct Engine {
     Bump bp(base, cap, dry);
     const size_t fb = plan_residents();
     face = fb ? (char*)bp.take(fb) : nullptr;
-    // the CG scalars and, right after them, the counters of entries A, B (inner) and
-    // B (true residual) -- read back with one copy -- then the entries' shift residuals
-    // and control words: everything from stat_all on is cleared by one fill kernel
-    const size_t ctl_bytes = sizeof(long long) * 12 * nsys + sizeof(double) * 6 * nsys +
-                             sizeof(int) * 12 * nsys;
-    cg_all = (double*)bp.take(sizeof(double) * CG_NSLOT * nsys + ctl_bytes);
-    stat_all = dry ? nullptr : (long long*)(cg_all + (size_t)CG_NSLOT * nsys);
-    dstat_all = dry ? nullptr : (double*)(stat_all + (size_t)12 * nsys);
-    ctl_all = dry ? nullptr : (int*)(dstat_all + (size_t)6 * nsys);
-    ctl_words = ctl_bytes / sizeof(int);
     act_all = (int*)bp.take(sizeof(int) * 2 * nsys);
     int blk = 0, nxy = 0, nz = 0, nt = 0, nzt = 0;
     long long total_sites = 0;
@@ -581,16 +572,6 @@ struct Engine {
       nt += (X / b.xc) * Y * Z;
       b.off_zt = nzt;
       nzt += X * Y;
-      b.cg_s = dry ? nullptr : cg_all + (size_t)s * CG_NSLOT;
-      b.stat = dry ? nullptr : stat_all + (size_t)s * 4;
-      b.ms_b_stat = (dry || !pl.gw) ? nullptr : stat_all + (size_t)(nsys + s) * 4;
-      b.tb_stat = (dry || !pl.gwx) ? nullptr : stat_all + (size_t)(2 * nsys + s) * 4;
-      b.dstat = dry ? nullptr : dstat_all + (size_t)s * 2;
-      b.h_ctl = dry ? nullptr : ctl_all + (size_t)s * 4;
-      b.ms_b_dstat = (dry || !pl.gw) ? nullptr : dstat_all + (size_t)(nsys + s) * 2;
-      b.ms_b_h_ctl = (dry || !pl.gw) ? nullptr : ctl_all + (size_t)(nsys + s) * 4;
-      b.tb_dstat = (dry || !pl.gwx) ? nullptr : dstat_all + (size_t)(2 * nsys + s) * 2;
-      b.tb_h_ctl = (dry || !pl.gwx) ? nullptr : ctl_all + (size_t)(2 * nsys + s) * 4;
       b.act_cg = dry ? nullptr : act_all + s;
       b.act_ru = dry ? nullptr : act_all + nsys + s;
     }
@@ -611,6 +592,30 @@ struct Engine {
       geo_key += g;
     }
     ftab = pl.nshift > 0 ? (SysDev*)bp.take(sizeof(SysDev) * nsys * pl.nshift) : nullptr;
+    // the CG scalars and, right after them, the counters of entries A, B (inner) and
+    // B (true residual) -- read back with one copy -- then the entries' shift residuals
+    // and control words: everything from stat_all on is cleared together
+    const size_t ctl_bytes = sizeof(long long) * 12 * nsys + sizeof(double) * 6 * nsys +
+                             sizeof(int) * 12 * nsys;
+    cg_all = (double*)bp.take(sizeof(double) * CG_NSLOT * nsys + ctl_bytes);
+    const size_t stat0 = bp.off - ctl_bytes;
+    stat_all = dry ? nullptr : (long long*)(cg_all + (size_t)CG_NSLOT * nsys);
+    dstat_all = dry ? nullptr : (double*)(stat_all + (size_t)12 * nsys);
+    ctl_all = dry ? nullptr : (int*)(dstat_all + (size_t)6 * nsys);
+    ctl_words = ctl_bytes / sizeof(int);
+    for (int s = 0; s < nsys; ++s) {
+      SysBuf& b = sb[s];
+      b.cg_s = dry ? nullptr : cg_all + (size_t)s * CG_NSLOT;
+      b.stat = dry ? nullptr : stat_all + (size_t)s * 4;
+      b.ms_b_stat = (dry || !pl.gw) ? nullptr : stat_all + (size_t)(nsys + s) * 4;
+      b.tb_stat = (dry || !pl.gwx) ? nullptr : stat_all + (size_t)(2 * nsys + s) * 4;
+      b.dstat = dry ? nullptr : dstat_all + (size_t)s * 2;
+      b.h_ctl = dry ? nullptr : ctl_all + (size_t)s * 4;
+      b.ms_b_dstat = (dry || !pl.gw) ? nullptr : dstat_all + (size_t)(nsys + s) * 2;
+      b.ms_b_h_ctl = (dry || !pl.gw) ? nullptr : ctl_all + (size_t)(nsys + s) * 4;
+      b.tb_dstat = (dry || !pl.gwx) ? nullptr : dstat_all + (size_t)(2 * nsys + s) * 2;
+      b.tb_h_ctl = (dry || !pl.gwx) ? nullptr : ctl_all + (size_t)(2 * nsys + s) * 4;
+    }
     // one region, uploaded with one copy (upload_tables)
     ntab = pl.solve ? T_NT : 2;
     tables = (SysDev*)bp.take(sizeof(SysDev) * ntab * nsys);
@@ -620,6 +625,7 @@ struct Engine {
     trgwtab = pl.gwx ? (SysDev*)bp.take(sizeof(SysDev) * 2 * nsys) : nullptr;
     gwbmap = (pl.gw || pl.gwx) ? (int*)bp.take(sizeof(int) * 2 * (size_t)nb_total) : nullptr;
     up_bytes = bp.off - up0;
+    up_head = up0 - stat0;
     return bp.off + 256;
   }
 };
@@ -675,7 +681,7 @@ ov_status ensure_ws(ov_ctx* c, size_t need, void** base) {
 constexpr size_t kHostScalars = sizeof(double) * (CG_NSLOT + 24) * kNoAllocSystems;
 constexpr size_t kHostFlags = 256;  // two ints per system
 static_assert(2 * kNoAllocSystems * sizeof(int) <= kHostFlags, "flags");
-static_assert(2 * kNoAllocSystems * sizeof(SysDev) + 16384 <= kNoAllocStage, "tables");
+static_assert(kNoAllocSystems * (2 * sizeof(SysDev) + 256) + 16384 <= kNoAllocStage, "tables");
 constexpr size_t kHostBlock = kHostScalars + kHostFlags + kNoAllocStage + 64;
 ov_status host_setup(ov_ctx* c) {
   HIPCHK(c, hipHostMalloc((void**)&c->host_block, kHostBlock));
@@ -948,15 +954,19 @@ ov_status ensure_stage(ov_ctx* c, size_t bytes) {
 
 // The engine's host tables to the device: one asynchronous copy from pinned memory (a copy
 // per table, each waited for, took 20 us of a call that runs 60 us of kernels).
-ov_status upload_tables(Engine& E) {
+// With `clear` it zeroes the counters and control words in front of them as well (reset_stats).
+ov_status upload_tables(Engine& E, bool clear = false) {
   ov_ctx* c = E.lead;
-  TRY(ensure_stage(c, E.up_bytes));
-  auto at = [&](const void* dev) { return c->stage + ((const char*)dev - (const char*)E.tables); };
-  std::memcpy(c->stage, E.htab.data(), sizeof(SysDev) * (size_t)E.ntab * E.nsys);
+  const size_t head = clear ? E.up_head : 0;
+  TRY(ensure_stage(c, head + E.up_bytes));
+  std::memset(c->stage, 0, head);
+  char* const base = c->stage + head;
+  auto at = [&](const void* dev) { return base + ((const char*)dev - (const char*)E.tables); };
+  std::memcpy(base, E.htab.data(), sizeof(SysDev) * (size_t)E.ntab * E.nsys);
   if (!E.io.empty())
     for (int s = 0; s < E.nsys; ++s) {
       for (int t : {(int)T_APPLY, (int)T_APPLY2}) {
-        SysDev& d = ((SysDev*)c->stage)[(size_t)t * E.nsys + s];
+        SysDev& d = ((SysDev*)base)[(size_t)t * E.nsys + s];
         d.io_in = (const double2*)E.io[s].in;
         d.io_pin = E.io[s].pin;
         d.io_pout = E.io[s].pout;
@@ -975,7 +985,8 @@ ov_status upload_tables(Engine& E) {
     for (int s = 0; s < 2 * E.nsys; ++s)
       for (int b = 0; b < E.sb[s % E.nsys].nblk; ++b) *m++ = s;
   }
-  HIPCHK(c, hipMemcpyAsync(E.tables, c->stage, E.up_bytes, hipMemcpyHostToDevice, E.st));
+  HIPCHK(c, hipMemcpyAsync((char*)E.tables - head, c->stage, head + E.up_bytes,
+                           hipMemcpyHostToDevice, E.st));
   c->stage_busy = true;
   return OV_OK;
 }
@@ -1073,7 +1084,7 @@ void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double 
     eoff += range;
     for (int k = 0; k < l.nrun; ++k) nent += l.run[k].ne;
   }
-  k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
+  k_ms_coef<<<nent, COEF_THREADS, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
 }
 
 template <class R>
@@ -1173,7 +1184,7 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
         k_ms_r<R, 0, false><<<nbt_, E.block, 0, E.st>>>(T, bmap_, nbt_, n, stamped(smp));
     }
   }
-  k_ms_coef<<<nent, 256, 0, E.st>>>(T, nent, L, mp, ResEpoch{});
+  k_ms_coef<<<nent, COEF_THREADS, 0, E.st>>>(T, nent, L, mp, ResEpoch{});
 }
 
 template <class R>
@@ -1182,8 +1193,13 @@ void launch_ms(const Engine& E, int t, const MsParams& mp, int L) {
 }
 
 template <class R>
-void launch_combine(const Engine& E, int t, int mode) {
-  k_ms_combine<R><<<E.nb_total, E.block, 0, E.st>>>(tab(E, t), E.bmap, E.nb_total, mode);
+void launch_combine(const Engine& E, int t, int mode, int aos = 0) {
+  // groups per site: as many as fit 512 threads, four at most (whole calls with 1, 2, 4, 8
+  // groups: sign 4^4 120, 113, 106, 111 us, M 8^4 476, 462, 457, 457; 16^4 in 256 threads,
+  // MdagM, 1648, 1609 with 1 and 2)
+  const int jw = std::min(4, 512 / E.block);
+  k_ms_combine<R><<<E.nb_total, E.block * jw, sizeof(double2) * 4 * E.block * (jw - 1), E.st>>>(
+      tab(E, t), E.bmap, mode, jw, aos);
 }
 
 SymParams sym_params(const ov_ctx* c, int kind) {
@@ -1451,7 +1467,7 @@ ov_status unpack64(Engine& E) {
 
 // --------------------------------------------------------- apply / sign
 // Tables of an operator on x64 (planar FP64) with the result in r64.
-ov_status run_apply(Engine& E, int op, const void* phi) {
+ov_status run_apply(Engine& E, int op, const void* phi, bool direct, bool clear) {
   E.htab.assign((size_t)E.ntab * E.nsys, SysDev{});
   for (int s = 0; s < E.nsys; ++s) {
     SysBuf& b = E.sb[s];
@@ -1472,10 +1488,11 @@ ov_status run_apply(Engine& E, int op, const void* phi) {
     d2.e_in = b.u64;
     d2.src = b.src64b;
     d2.e_out = b.r64;
+    if (direct) d1.src_io = op == OV_OP_DOV_DAG || op == OV_OP_M_DAG ? 2 : 1;
     E.htab[(size_t)T_APPLY * E.nsys + s] = d1;
     E.htab[(size_t)T_APPLY2 * E.nsys + s] = d2;
   }
-  return upload_tables(E);
+  return upload_tables(E, clear);
 }
 
 // H_W on the caller's fields (every system of an operator call is on one lattice).  The
@@ -1533,22 +1550,24 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
         k_hw<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, diag, 0);
       break;
     case -1:  // sign
-      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
-      launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
-      launch_combine<double>(E, T_APPLY, EPI_SIGN);
-      break;
     case OV_OP_DOV:
     case OV_OP_M:
-      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
-      launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
-      launch_combine<double>(E, T_APPLY, op == OV_OP_DOV ? EPI_DOV : EPI_M);
-      break;
     case OV_OP_DOV_DAG:
-    case OV_OP_M_DAG:
-      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 1);
+    case OV_OP_M_DAG: {
+      // on the caller's fields, a resident multi-shift takes its source from them too
+      const bool dag = op == OV_OP_DOV_DAG || op == OV_OP_M_DAG;
+      if (!direct)
+        k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, dag);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
-      launch_combine<double>(E, T_APPLY, op == OV_OP_DOV_DAG ? EPI_DOVDAG : EPI_MDAG);
+      launch_combine<double>(E, T_APPLY,
+                             op == -1              ? EPI_SIGN
+                             : op == OV_OP_DOV     ? EPI_DOV
+                             : op == OV_OP_M       ? EPI_M
+                             : op == OV_OP_DOV_DAG ? EPI_DOVDAG
+                                                   : EPI_MDAG,
+                             direct ? 3 : 0);
       break;
+    }
     case OV_OP_M0INV:
     case OV_OP_M0INV_DAG:
     {
@@ -1558,11 +1577,12 @@ ov_status apply_sequence(Engine& E, int op, bool direct) {
     }
       break;
     case OV_OP_MDAGM:
-      k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
+      if (!direct)
+        k_ms_prep<double><<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total, 0);
       launch_ms<double>(E, T_APPLY, E.mp64, E.L64);
-      launch_combine<double>(E, T_APPLY, EPI_M);  // u64, src64b = g5 u64, part_b
+      launch_combine<double>(E, T_APPLY, EPI_M, direct);  // u64, src64b = g5 u64, part_b
       launch_ms<double>(E, T_APPLY2, E.mp64, E.L64);
-      launch_combine<double>(E, T_APPLY2, EPI_MDAG);
+      launch_combine<double>(E, T_APPLY2, EPI_MDAG, direct ? 2 : 0);
       break;
     default:
       return OV_ERR_INVALID_ARG;
@@ -2767,21 +2787,20 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   Engine E;
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
-  // operators without a multi-shift work on the caller's fields themselves, unless they
-  // overlap, and report nothing from the device
+  // Operators without a multi-shift, and those whose multi-shift runs in resident launches,
+  // work on the caller's fields themselves, unless they overlap; the former report nothing
+  // from the device.
   const bool shifts = op != OV_OP_HW && op != OV_OP_M0INV && op != OV_OP_M0INV_DAG &&
                       (op < OV_OP_DOV || c->p.dirac == OV_DIRAC_OVERLAP_MS);
-  if (shifts)
-    TRY(reset_stats(E));
-  else
+  if (!shifts)
     std::memset(c->pinned, 0, sizeof(double) * CG_NSLOT * E.nsys + sizeof(int) * E.ctl_words);
   const size_t vb = (size_t)E.sb[0].V * 4 * sizeof(double2);
   E.io.resize(nrhs);
   for (int r = 0; r < nrhs; ++r)
     E.io[r] = {(const char*)in + r * vb, E.sb[r].x64, E.sb[r].r64, (char*)out + r * vb};
-  TRY(run_apply(E, op, phi));
   const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
-  const bool direct = !shifts && (a > b ? a - b : b - a) >= nrhs * vb;
+  const bool direct = (a > b ? a - b : b - a) >= nrhs * vb && (!shifts || E.resident<double>(1));
+  TRY(run_apply(E, op, phi, direct && shifts, shifts));
   if (!direct) TRY(pack64(E));
   TRY(apply_sequence(E, op, direct));
   if (!direct) TRY(unpack64(E));
@@ -3606,7 +3625,7 @@ static ov_status locality_impl(ov_ctx* c, int spin, double* f, int nr, ov_stats*
   std::vector<ov_ctx*> v(1, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
   TRY(reset_stats(E));
-  TRY(run_apply(E, OV_OP_DOV, nullptr));  // e_in = x64, result in r64
+  TRY(run_apply(E, OV_OP_DOV, nullptr, false, false));  // e_in = x64, result in r64
   SysBuf& b = E.sb[0];
   const size_t V = b.V;
   // unit point source at the origin: x64 = 0, plane `spin` of site 0 = 1

@@ -134,3 +134,28 @@ def test_boson_ragged_vs_oracle(orc, dims):
     assert abs(S - So) <= 1e-12 * abs(So)
     check(host(G), Go, 1e-12)
     check(host(F), Fo, 1e-12)
+
+
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 2), 1), ((2, 4, 6, 10), 3), ((8, 8, 12, 14), 2)])
+def test_overlap_operators_on_caller_fields_vs_oracle(orc, dims, nrhs):
+    """sign, D, M and their adjoints with the multi-shift's source read from, and the
+    combination written to, the caller's fields (workgroups of 64 threads in four groups per
+    site and of 256 in two, a last workgroup that is not full), and in place, on the packed
+    copies.  Both sides run the multi-shift at 1e-12, as in the parity tests."""
+    print(f"[overlap io] {dims}", flush=True)
+    phi, x = inputs.draw(dims, nrhs=nrhs, sigma2=0.25, seed=88)
+    lat = lattice(dims, inner_tol=1e-12, **CFG2)
+    o = orc.Oracle(dims, inner_tol=1e-12, **CFG2)
+    r = nrhs - 1
+    ops = dict(dov=orc.OP_DOV, dov_dag=orc.OP_DOV_DAG, m=orc.OP_M, m_dag=orc.OP_M_DAG,
+               mdagm=orc.OP_MDAGM)
+    check(host(lat.sign(dev(x))[0])[r], o.sign(x[r])[0], 1e-11, "sign")
+    for op, code in ops.items():
+        want = o.apply(code, x[r], phi)
+        check(host(lat.apply(op, dev(x), dev(phi))[0])[r], want, 1e-11, op)
+        z, p = dev(x), dev(phi)
+        torch.cuda.synchronize()
+        st = (L.OvStats * nrhs)()
+        assert L.lib().ov_apply(lat._h, L.OPS[op], C.c_void_p(z.data_ptr()), C.c_void_p(z.data_ptr()),
+                                C.c_void_p(p.data_ptr()), nrhs, st) == 0
+        check(host(z)[r], want, 1e-11, f"{op} in place")
