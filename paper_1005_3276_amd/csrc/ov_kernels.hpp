@@ -952,16 +952,17 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
 //      spinors (1 -+ g_mu) psi (two of four components: the hop needs no more) of the
 //      block's faces to the neighbouring workgroups by device-scope (sc1) stores;
 //   2. while these travel they apply the hops inside the block out of LDS, then read the
-//      neighbours' faces (device-scope loads) once their words say that they are out;
+//      neighbours' faces (device-scope loads) until every value is there (RES_EMPTY);
 //      meanwhile the service wave sends the block's partial norm and collects everybody's:
 //      words that carry the pass's epoch, so one exchange is the reduction and the barrier;
 //   3. with the sum they update t or r, while the service wave advances the recurrences.
 // Nothing else crosses workgroups, so no cache is written back or invalidated, and t_n goes
 // to the basis with streaming stores that nothing waits for.  Bound by latency: an FP64 pass
-// at 16^4 (one source, 128 workgroups of 512 sites) takes 3.7 us, a quarter of it update and
+// at 16^4 (one source, 128 workgroups of 512 sites) takes 3.2 us, a quarter of it update and
 // publish, a quarter the hops out of LDS, the rest waits for faces and the sum (the per-pass
-// kernels: 10 us and the launch gap); 8^4 takes 2.4 us (4.5 us), 4^4, one workgroup and no
-// exchange, 1.4 us (3.3 us).
+// kernels: 10 us and the launch gap; with a flag per workgroup for its faces 3.7); 8^4 takes
+// 1.9 us (4.5 us), 4^4, one workgroup and no exchange, 1.4 us (3.3 us).  Two sources of 16^4
+// at once, 256 workgroups, 4.0 us; 16^3 x 32, all of them in one sum, 4.9 us.
 struct ResRun {          // consecutive entries on one lattice
   int e0, ne;            // table entries
   int wg0;               // first workgroup of the launch
@@ -987,10 +988,10 @@ struct ResShared {
   struct {
     u32x4 word, pad[3];
   } part[2][RES_WGS];                       // tagged partial sums by the epoch's parity
-  unsigned face[RES_WGS][16];               // [0]: epoch the workgroup's faces are out for
 };
 struct ResArgs {
   int nrun, L;                     // runs; iterations at most
+  int nap, nap_face;               // first looks, in 128 and 64 cycles (ResLaunch)
   unsigned eoff;                   // epoch offset of this launch
   ResShared* sh;
   int* abort_host;                 // pinned host word, set with sh->abort
@@ -1004,6 +1005,13 @@ struct ResEpoch {
   unsigned bump = 0;               // epochs the launches used
 };
 
+// A face value that has not arrived: every 32-bit word of the faces holds this pattern when a
+// launch starts and when it ends, and a reader puts it back.  Each value's first word (FP32),
+// high word (FP64) tells whether its eight bytes are there, so faces need no flag of their
+// own (waiting for the stores' end, a flag and its polling took a microsecond of every pass).
+// As the high word of a double it is a signalling NaN, which no arithmetic returns; a float
+// with this payload could only come from a caller's NaN, and would run into the wait limit.
+constexpr unsigned RES_EMPTY = 0x7ff45a5au;
 constexpr unsigned RES_OOB = 0x80000000u;  // beyond every buffer: loads 0, stores nothing
 constexpr int RES_SC1 = 16;                // device-scope cache policy of a buffer access
 constexpr int RES_VOLATILE = (int)0x80000000;
@@ -1023,8 +1031,17 @@ __device__ __forceinline__ Half<double> face_ld(__amdgpu_buffer_rsrc_t rs, unsig
 }
 __device__ __forceinline__ Half<float> face_ld(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned so,
                                                unsigned, float) {
-  return __builtin_bit_cast(Half<float>,
-                            __builtin_amdgcn_raw_buffer_load_b128(rs, o, so, RES_SC1));
+  return __builtin_bit_cast(
+      Half<float>, __builtin_amdgcn_raw_buffer_load_b128(rs, o, so, RES_SC1));
+}
+// Every eight bytes of the two values have arrived.
+__device__ __forceinline__ bool face_in(const Half<double>& h) {
+  const u32x4 p = __builtin_bit_cast(u32x4, h.a), q = __builtin_bit_cast(u32x4, h.b);
+  return p.y != RES_EMPTY && p.w != RES_EMPTY && q.y != RES_EMPTY && q.w != RES_EMPTY;
+}
+__device__ __forceinline__ bool face_in(const Half<float>& h) {
+  const u32x4 p = __builtin_bit_cast(u32x4, h);
+  return p.x != RES_EMPTY && p.z != RES_EMPTY;
 }
 // Stores add the field's byte to the vector offset: behind a 16-byte store with an offset in
 // a scalar register the compiler leaves no wait state before it reuses the data registers,
@@ -1069,6 +1086,17 @@ __device__ __forceinline__ void lds_put(unsigned char* sh, unsigned j, const flo
 #pragma unroll
   for (int q = 0; q < 2; ++q)
     p[q] = f32x4{v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y};
+}
+
+__device__ __forceinline__ void face_clear(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
+                                           double) {
+  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  __builtin_amdgcn_raw_buffer_store_b128(e, rs, o, 0, RES_SC1);
+  __builtin_amdgcn_raw_buffer_store_b128(e, rs, o + Fb, 0, RES_SC1);
+}
+__device__ __forceinline__ void face_clear(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned, float) {
+  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  __builtin_amdgcn_raw_buffer_store_b128(e, rs, o, 0, RES_SC1);
 }
 
 // Sum over the wave in lane 63, on the vector ALU alone (a shuffle tree through LDS takes
@@ -1218,9 +1246,19 @@ struct ResBlock {
     put<3>(v, s, fl, fld);
     if (s.j < S) lds_put(sh, (unsigned)s.j, v);
   }
-  __device__ __forceinline__ void halo(ResHalo<R>& h, const ResSite& s, unsigned fld) const {
+  // the half spinors received, and whether all of them are there
+  __device__ __forceinline__ bool halo(ResHalo<R>& h, const ResSite& s, unsigned fld) const {
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) h.h[mu] = face_ld(rs, s.ld[mu], fld, Fb[mu], R());
+    bool in = true;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) in &= face_in(h.h[mu]);
+    return in;
+  }
+  // empties the places of a site's received half spinors (o = s.ld), or of the sent ones
+  __device__ __forceinline__ void clear(const unsigned (&o)[4], unsigned fld) const {
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) face_clear(rs, opaque(o[mu]) + fld, Fb[mu], R());
   }
 
   // hops of an axis from inside the block
@@ -1285,28 +1323,38 @@ struct ResBlock {
   }
 };
 
+// Faces before the first resident launch of a call.
+__global__ void __launch_bounds__(256) k_res_empty(u32x4* __restrict__ face, size_t n) {
+  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (size_t)gridDim.x * blockDim.x)
+    face[i] = e;
+}
+
 // What the service wave and the compute waves tell each other.
 struct ResLds {
   double red[RES_WAVES];  // wave sums of the field just published
   double total;           // the entry's sum
   int stop;               // leave after the field is out (converged, broke down)
   int gone;               // a wait ran out
-  unsigned drained;       // compute waves whose faces have arrived, over all passes
-  unsigned faces;         // epoch the neighbours' faces are out for
 };
+
+// A wait has run out: every workgroup leaves, the host runs the call again (one lane).
+__device__ __forceinline__ void res_give_up(const ResArgs& A, ResLds& X) {
+  __hip_atomic_store(&A.sh->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(A.abort_host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&X.gone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 // The service wave's exchange: send the workgroup's partial s and wait for the G partials
 // of the entry; their sum (lane 63) in a fixed order, the same bits in every workgroup.
 // Each half of a 16-byte word carries the epoch, so that it need not arrive whole.
 // Partials alternate between two slots: a workgroup writes epoch e + 2 only after every
-// workgroup has sent e + 1, that is, has read e.  On the way it tells the compute waves
-// when the neighbours' faces are out (facew: this lane's face word, null for none); a face
-// word may already hold a later epoch: its writer went on, and the faces alternate between
-// t and r.  The wait is bounded: when `spin` ticks pass, or another workgroup has given up,
-// the abort words are raised, false is returned and every workgroup leaves.
+// workgroup has sent e + 1, that is, has read e.  The wait is bounded: when `spin` ticks pass,
+// or another workgroup has given up, the abort words are raised, false is returned and every
+// workgroup leaves.
 __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int slot0, int w, int G,
-                                             unsigned epoch, double s, const unsigned* facew,
-                                             double* total) {
+                                             unsigned epoch, double s, double* total) {
   const int lane = threadIdx.x & 63;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
       A.sh->part[epoch & 1] + slot0, 0, G * (int)sizeof(A.sh->part[0][0]), 0x00020000);
@@ -1316,30 +1364,17 @@ __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int sl
     __builtin_amdgcn_raw_buffer_store_b128(x, rs, w * 64, 0, RES_SC1);
   }
   // nothing arrives sooner; polls in the meantime slow the stores that are on their way
-  // (16^4 3.98 -> 3.78 us per pass, 8^4 2.54 -> 2.50; 44 instead of 30: 4.10 and 2.88)
-  __builtin_amdgcn_s_sleep(30);
+  for (int n = 0; n < A.nap; ++n) __builtin_amdgcn_s_sleep(2);
   long long t0 = 0;
-  bool faces = false;
   for (int n = 0;; ++n) {
-    bool ready = true, fready = true;
-    unsigned f = epoch;
-    if (facew && !faces)
-      f = __hip_atomic_load(facew, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool ready = true;
     double p = 0.0;
     for (int j = lane; j < G; j += 64) {
       const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, j * 64, 0, RES_SC1 | RES_VOLATILE);
       ready &= x.y == epoch && x.w == epoch;
       p += __longlong_as_double((long long)(((unsigned long long)x.z << 32) | x.x));
     }
-    if (!faces) {
-      fready = (int)(f - epoch) >= 0;
-      if (__all(fready)) {
-        faces = true;
-        if (lane == 0)
-          __hip_atomic_store(&X.faces, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    }
-    if (faces && __all(ready)) {
+    if (__all(ready)) {
       *total = wave_sum_last(p);
       return true;
     }
@@ -1348,12 +1383,7 @@ __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int sl
       if (n == 0) t0 = now;
       if (now - t0 >= A.spin ||
           __hip_atomic_load(&A.sh->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        if (lane == 0) {
-          __hip_atomic_store(&A.sh->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(A.abort_host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          X.gone = 1;
-          __hip_atomic_store(&X.faces, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        if (lane == 0) res_give_up(A, X);
         return false;
       }
     }
@@ -1380,23 +1410,11 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
   const int nwc = (int)(blockDim.x >> 6) - 1;  // compute waves; the last wave serves
   if (threadIdx.x == 0) {
     X.stop = X.gone = 0;
-    X.drained = X.faces = 0;
   }
   unsigned ep = A.sh->epoch + A.eoff;
 
   if (wave == nwc) {
     // ---------------------------------------------------------- service wave
-    // face word this lane watches: neighbour lane (axis lane / 2, side lane % 2)
-    const unsigned* face_nbr = nullptr;
-    if (lane < 8) {
-      const int mu = lane >> 1;
-      int ws = 1;
-      for (int m = 0; m < mu; ++m) ws *= U.nb[m];
-      const int n = U.nb[mu], c = (w / ws) % n;
-      const int nw = lane & 1 ? w + (c + 1 < n ? ws : ws - n * ws)
-                              : w - (c > 0 ? ws : ws - n * ws);
-      if (n > 1) face_nbr = A.sh->face[slot0 + nw];
-    }
     const int np = mp.np;
     const double sigma = lane < np ? mp.sigma[lane] : 0.0;
     const bool keep = w == 0;  // records the history
@@ -1414,7 +1432,7 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
       ++ep;
       bool ok = true;
       if (G > 1)
-        ok = res_exchange(A, X, slot0, w, G, ep, s, face_nbr, &s);
+        ok = res_exchange(A, X, slot0, w, G, ep, s, &s);
       if (lane == 63) X.total = s;
       *tot = __longlong_as_double(
           ((long long)__builtin_amdgcn_readlane((int)(__double_as_longlong(s) >> 32), 63) << 32) |
@@ -1428,6 +1446,7 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
       double rho, gam;
       ok = exchange(&rho);
       __syncthreads();  // total is in
+      ok &= X.gone == 0;
       if (!ok) break;
       const double srho = sqrt(rho);
       if (n == 0) thr = mp.tol * srho;
@@ -1467,6 +1486,7 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
       if (stop) break;
       ok = exchange(&gam);
       __syncthreads();  // total is in
+      ok &= X.gone == 0;
       if (!ok) break;
       const double alpha = rho / gam;
       if (keep && lane == 0) h_alpha[n] = alpha;
@@ -1511,8 +1531,6 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu)
     B.Fb[mu] = (unsigned)(B.S / U.b[mu]) * (unsigned)sizeof(c2<R>);
-  unsigned* const face_own = &A.sh->face[slot0 + w][0];
-  unsigned sent = 0;  // fields sent, times the compute waves
   c2<R>* basis = (c2<R>*)S.basis;
   const size_t slot = (size_t)4 * g.V;
 
@@ -1534,8 +1552,11 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
 #pragma unroll
     for (int q = 0; q < 4; ++q) t[k][q] = c2<R>{R(0), R(0)};
   }
-  // The field v of the next pass goes out, its hops inside the block follow; false: leave.
+  // The field v of the next pass goes out; false: leave.  Places emptied since the last one
+  // are so before it goes out: their writers write them again only after a sum that this
+  // workgroup's next partial is part of.
   auto send = [&](c2<R>(&v)[K][4], unsigned fo) -> bool {
+    if (G > 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -1545,38 +1566,49 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
     }
     acc = wave_sum_last(acc);
     if (lane == 63) X.red[wave] = acc;
-    ++ep;
     __syncthreads();
-    return X.stop == 0;
+    if (X.stop == 0) return true;
+    // every workgroup stops here: nobody reads what has just gone out
+#pragma unroll
+    for (int k = 0; k < K; ++k) B.clear(site[k].st, fo);
+    return false;
   };
   // hops = sum of the hops of the field just sent, its faces in the half at fo
   auto gather = [&](unsigned fo) {
 #pragma unroll
     for (int k = 0; k < K; ++k) B.inside(site[k], hops[k]);
     if (G == 1) return;
-    // the service wave says when; it also ends the wait when it gives up
-    while (__hip_atomic_load(&X.faces, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != ep)
-      __builtin_amdgcn_s_sleep(1);
     ResHalo<R> h[K];
+    for (int n = 0; n < A.nap_face; ++n) __builtin_amdgcn_s_sleep(1);
+    long long t0 = 0;
+    for (int n = 0;; ++n) {
+      asm volatile("" ::: "memory");  // every turn loads again
+      bool in = true;
 #pragma unroll
-    for (int k = 0; k < K; ++k) B.halo(h[k], site[k], fo);
+      for (int k = 0; k < K; ++k) in &= B.halo(h[k], site[k], fo);
+      // the service wave ends the wait when it gives up
+      if (__all(in) ||
+          __hip_atomic_load(&X.gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+        break;
+      if ((n & 15) == 0) {
+        const long long now = (long long)wall_clock64();
+        if (n == 0) t0 = now;
+        if (now - t0 > A.spin) {
+          if (lane == 0) res_give_up(A, X);
+          break;
+        }
+      }
+    }
 #pragma unroll
-    for (int k = 0; k < K; ++k) B.outside(h[k], site[k], hops[k]);
-  };
-  // this wave's faces have arrived; the last wave's word tells the neighbours
-  auto faces_out = [&]() {
-    sent += nwc;
-    if (G == 1) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0 && __hip_atomic_fetch_add(&X.drained, 1u, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP) + 1 == sent)
-      __hip_atomic_store(face_own, ep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int k = 0; k < K; ++k) {
+      B.clear(site[k].ld, fo);
+      B.outside(h[k], site[k], hops[k]);
+    }
   };
   double rho_m1 = 1.0;
   bool on = send(r, 0);
   for (int n = 0; n < A.L && on; ++n) {
     // ---- t pass: t_n = H r_n + beta_{n-1} t_{n-1}
-    faces_out();
     gather(0);
     __syncthreads();
     const double rho = X.total;
@@ -1594,7 +1626,6 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
     }
     if (!send(t, fb)) return;  // converged at n
     // ---- r pass: alpha_n = rho_n / |t_n|^2, r_{n+1} = r_n - alpha_n H t_n
-    faces_out();
     c2<R>* tn = basis + (size_t)n * slot;
 #pragma unroll
     for (int k = 0; k < K; ++k)

@@ -395,7 +395,16 @@ int pick_xc(int X, int T) {
 struct ResLaunch {
   ResRun run[RES_RUNS];
   int nrun = 0, grid = 0, threads = 64, K = 1;
+  int S = 0, G = 0;  // largest block and workgroups of an entry
   size_t lds = 0;
+  // When a pass first looks for the partials and the faces.  Partials, in 128 cycles: a look
+  // that comes too early costs a whole trip to memory more, and a line through the best of
+  // 2 to 24 stays below it (8^4, 32 workgroups of 128 sites: 2.23 us per pass with 2, 1.88 with
+  // 10, 2.60 with 24; 16^4 twice, 256 of 512: 4.70, 4.02 with 18, 4.08).  Faces: at once, but
+  // for entries on all CUs, whose stores take longer than the hops inside (16^3 x 32: 5.26 us
+  // at once, 4.88 after 20 times 64 cycles; 16^4 once 3.25 and 3.46).
+  int nap() const { return std::max(10, (int)(8.35 + 0.01 * S + 0.02 * grid)); }
+  int nap_face() const { return G >= 192 ? 20 : grid >= 192 ? 2 : 0; }
 };
 struct ResPlan {
   std::vector<ResLaunch> launches;
@@ -458,6 +467,7 @@ struct Engine {
   ResPlan res[2][2];                // resident launches: [FP64, FP32][copies of the systems - 1]
   bool no_res = false;              // per-pass kernels only (tuning, a tight workspace)
   char* face = nullptr;             // device: faces of the largest resident launch
+  size_t face_bytes = 0;
 
   template <class R>
   const ResPlan* resident(int copies) const {
@@ -516,6 +526,8 @@ struct Engine {
       l->grid += q.G;
       l->threads = std::max(l->threads, q.threads);
       l->K = std::max(l->K, q.K);
+      l->S = std::max(l->S, q.S);
+      l->G = std::max(l->G, q.G);
       l->lds = std::max(l->lds, (size_t)(q.S + 1) * (4 * esize + 16));
       faces += fb;
       us = std::max(us, q.us);
@@ -545,6 +557,7 @@ struct Engine {
     Bump bp(base, cap, dry);
     const size_t fb = plan_residents();
     face = fb ? (char*)bp.take(fb) : nullptr;
+    face_bytes = fb;
     act_all = (int*)bp.take(sizeof(int) * 2 * nsys);
     int blk = 0, nxy = 0, nz = 0, nt = 0, nzt = 0;
     long long total_sites = 0;
@@ -988,6 +1001,10 @@ ov_status upload_tables(Engine& E, bool clear = false) {
   HIPCHK(c, hipMemcpyAsync((char*)E.tables - head, c->stage, head + E.up_bytes,
                            hipMemcpyHostToDevice, E.st));
   c->stage_busy = true;
+  if (E.face_bytes) {  // a multiple of 64 bytes: whole face values of a block
+    const size_t n = E.face_bytes / sizeof(u32x4);
+    k_res_empty<<<(unsigned)std::min<size_t>((n + 255) / 256, 1024), 256, 0, E.st>>>((u32x4*)E.face, n);
+  }
   return OV_OK;
 }
 
@@ -1070,6 +1087,8 @@ void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double 
     a.nrun = l.nrun;
     a.L = L;
     a.eoff = eoff;
+    a.nap = l.nap();
+    a.nap_face = l.nap_face();
     a.sh = c->res_sh;
     a.abort_host = c->res_abort;
     a.face = E.face;
