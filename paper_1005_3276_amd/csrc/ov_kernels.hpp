@@ -958,11 +958,12 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
 //   3. with the sum they update t or r, while the service wave advances the recurrences.
 // Nothing else crosses workgroups, so no cache is written back or invalidated, and t_n goes
 // to the basis with streaming stores that nothing waits for.  Bound by latency: an FP64 pass
-// at 16^4 (one source, 128 workgroups of 512 sites) takes 3.2 us, a quarter of it update and
-// publish, a quarter the hops out of LDS, the rest waits for faces and the sum (the per-pass
-// kernels: 10 us and the launch gap; with a flag per workgroup for its faces 3.7); 8^4 takes
-// 1.9 us (4.5 us), 4^4, one workgroup and no exchange, 1.4 us (3.3 us).  Two sources of 16^4
-// at once, 256 workgroups, 4.0 us; 16^3 x 32, all of them in one sum, 4.9 us.
+// at 16^4 (one source, 128 workgroups of 512 sites) takes 2.9 us, a third of it update and
+// publish, a third the hops out of LDS, the rest waits for faces and the sum (the per-pass
+// kernels: 10 us and the launch gap; with a flag per workgroup for its faces and the
+// partials read one after the other 3.7); 8^4 takes 1.8 us (4.5 us), 4^4, one workgroup and
+// no exchange, 1.4 us (3.3 us).  Two sources of 16^4 at once, 256 workgroups, 3.9 us; 16^3 x
+// 32, all of them in one sum, 4.0 us.
 struct ResRun {          // consecutive entries on one lattice
   int e0, ne;            // table entries
   int wg0;               // first workgroup of the launch
@@ -1356,8 +1357,13 @@ __device__ __forceinline__ void res_give_up(const ResArgs& A, ResLds& X) {
 __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int slot0, int w, int G,
                                              unsigned epoch, double s, double* total) {
   const int lane = threadIdx.x & 63;
+  // scalar by construction, but not to the compiler, which would access the words in a loop
+  // over the lanes' descriptors
+  epoch = (unsigned)__builtin_amdgcn_readfirstlane((int)epoch);
+  const int first = (int)(epoch & 1) * RES_WGS + __builtin_amdgcn_readfirstlane(slot0);
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      A.sh->part[epoch & 1] + slot0, 0, G * (int)sizeof(A.sh->part[0][0]), 0x00020000);
+      &A.sh->part[0][0] + first, 0,
+      __builtin_amdgcn_readfirstlane(G) * (int)sizeof(A.sh->part[0][0]), 0x00020000);
   if (lane == 0) {
     const unsigned long long bits = (unsigned long long)__double_as_longlong(s);
     const u32x4 x = {(unsigned)bits, epoch, (unsigned)(bits >> 32), epoch};
@@ -1367,12 +1373,21 @@ __device__ __forceinline__ bool res_exchange(const ResArgs& A, ResLds& X, int sl
   for (int n = 0; n < A.nap; ++n) __builtin_amdgcn_s_sleep(2);
   long long t0 = 0;
   for (int n = 0;; ++n) {
+    // the lane's words (up to four) all in flight at once: a trip to memory is the cost, and
+    // one after the other they made G > 64 half a microsecond slower, G > 192 two; words
+    // beyond G read as zero
+    u32x4 x[4] = {};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u == 0 || G > 64 * u)
+        x[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (lane + 64 * u) * 64, 0,
+                                                     RES_SC1 | RES_VOLATILE);
     bool ready = true;
     double p = 0.0;
-    for (int j = lane; j < G; j += 64) {
-      const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, j * 64, 0, RES_SC1 | RES_VOLATILE);
-      ready &= x.y == epoch && x.w == epoch;
-      p += __longlong_as_double((long long)(((unsigned long long)x.z << 32) | x.x));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      ready &= lane + 64 * u >= G || (x[u].y == epoch && x[u].w == epoch);
+      p += __longlong_as_double((long long)(((unsigned long long)x[u].z << 32) | x[u].x));
     }
     if (__all(ready)) {
       *total = wave_sum_last(p);

@@ -399,12 +399,12 @@ struct ResLaunch {
   size_t lds = 0;
   // When a pass first looks for the partials and the faces.  Partials, in 128 cycles: a look
   // that comes too early costs a whole trip to memory more, and a line through the best of
-  // 2 to 24 stays below it (8^4, 32 workgroups of 128 sites: 2.23 us per pass with 2, 1.88 with
-  // 10, 2.60 with 24; 16^4 twice, 256 of 512: 4.70, 4.02 with 18, 4.08).  Faces: at once, but
-  // for entries on all CUs, whose stores take longer than the hops inside (16^3 x 32: 5.26 us
-  // at once, 4.88 after 20 times 64 cycles; 16^4 once 3.25 and 3.46).
-  int nap() const { return std::max(10, (int)(8.35 + 0.01 * S + 0.02 * grid)); }
-  int nap_face() const { return G >= 192 ? 20 : grid >= 192 ? 2 : 0; }
+  // 8 to 24 stays below it (8^4, 32 workgroups of 128 sites: 2.15 us per pass with 8, 1.89 with
+  // 11, 2.29 with 20; 16^4 twice, 256 of 512: 4.47, 3.94 with 18, 3.89).  Faces: at once, but
+  // for entries on all CUs, whose stores take longer than the hops inside (16^3 x 32: 4.01 us
+  // at once, 3.96 after 4 times 64 cycles; 12^4 twice 2.40 and 2.43).
+  int nap() const { return std::max(11, (int)(9.6 + 0.01 * S + 0.016 * grid)); }
+  int nap_face() const { return G >= 192 ? 4 : 0; }
 };
 struct ResPlan {
   std::vector<ResLaunch> launches;
