@@ -137,12 +137,17 @@ void free_spectrum(const ov_params* p, double& smin, double& smax) {
         }
 }
 
-// Modelled time of one pass of k_ms_res (us), fitted to a sweep of blocks on MI355X (FP64,
-// 4^4 to 16^3x32, 1 to 256 workgroups of 48 to 864 sites: within 12%): the sites of a
-// workgroup, the exchange among G of them, the faces, and short rows of x.
-static double res_us(const ResGeom& r, int esize) {
-  double us = 0.9 + r.S * (esize == 16 ? 0.0021 : 0.0013) + 0.3 / r.b[0];
-  if (r.G > 1) us += 0.95 + 0.0045 * r.G + (double)r.FT * esize * r.G / 5.5e6;
+// Modelled time of one pass of k_ms_res (us) with `entries` of them on the chip.  FP64: least
+// squares over a sweep of 859 launches, blocks of 27 lattices on MI355X (8^4 to 24^3 x 16, odd
+// and long extents; 8% rms, the chosen blocks 2% from the best ones): the exchange, the sites
+// (more each once a SIMD holds four waves), short and odd rows of x, the faces under way.
+// FP32 the same with its own cost of a site and of a face.
+static double res_us(const ResGeom& r, int esize, int entries) {
+  const bool f64 = esize == 16;
+  double us = 0.73 + r.S * (f64 ? 0.00205 : 0.0013) + (f64 ? 0.435 : 0.3) / r.b[0] +
+              (r.b[0] % 2 ? 0.09 : 0.0);
+  if (f64 && r.S > 576) us += 0.0041 * (r.S - 576);
+  if (r.G > 1) us += 0.6 + 2.5e-7 * esize * r.FT * r.G * entries;
   return us;
 }
 
@@ -176,9 +181,9 @@ ResGeom res_geom(const int dims[4], int esize, int ncu, int maxK) {
           r.G = (int)G;
           r.K = (r.S + RES_MAX_THREADS - 1) / RES_MAX_THREADS;
           r.threads = (r.S + 64 * r.K - 1) / (64 * r.K) * 64;
-          r.us = res_us(r, esize);
-          // two sources per system is the solver's launch: half the CUs each
-          const double c = r.us * (1 + (2 * r.G + ncu - 1) / ncu);
+          r.us = res_us(r, esize, 1);
+          // two sources per system is the solver's launch
+          const double c = r.us + (2 * r.G <= ncu ? res_us(r, esize, 2) : 2.0 * r.us);
           if (c < cost) {
             cost = c;
             best = r;
