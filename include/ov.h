@@ -349,7 +349,7 @@ ov_status ov_tune_ms(ov_ctx *ctx, int prec, int nrhs, int block, int sites_per_t
 /* Kernel-duration sampling with HIP events recorded on the context's stream.
  * While max_per_call > 0, the first max_per_call launches of each multi-shift
  * kernel (0 = FP32 t pass  t_n = H r_n + beta t_{n-1},  1 = FP32 r pass
- * r_{n+1} = r_n - alpha H t_n, 2 = the persistent kernel running every iteration
+ * r_{n+1} = r_n - alpha H t_n, 2 = the resident kernel running every iteration
  * of one multi-shift solve, 3 / 4 = the FP64 t / r passes) in every
  * sign/apply/solve/force call are bracketed by
  * events; the sampled per-pass launches (kernels 0 and 1) also record, in every
