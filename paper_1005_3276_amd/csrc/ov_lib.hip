@@ -468,6 +468,7 @@ struct Engine {
   bool no_res = false;              // per-pass kernels only (tuning, a tight workspace)
   char* face = nullptr;             // device: faces of the largest resident launch
   size_t face_bytes = 0;
+  bool shifts = true;               // this call runs multi-shift solves
 
   template <class R>
   const ResPlan* resident(int copies) const {
@@ -1001,7 +1002,7 @@ ov_status upload_tables(Engine& E, bool clear = false) {
   HIPCHK(c, hipMemcpyAsync((char*)E.tables - head, c->stage, head + E.up_bytes,
                            hipMemcpyHostToDevice, E.st));
   c->stage_busy = true;
-  if (E.face_bytes) {  // a multiple of 64 bytes: whole face values of a block
+  if (E.shifts && E.face_bytes) {  // a multiple of 64 bytes: whole face values of a block
     const size_t n = E.face_bytes / sizeof(u32x4);
     k_res_empty<<<(unsigned)std::min<size_t>((n + 255) / 256, 1024), 256, 0, E.st>>>((u32x4*)E.face, n);
   }
@@ -2811,6 +2812,7 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   // from the device.
   const bool shifts = op != OV_OP_HW && op != OV_OP_M0INV && op != OV_OP_M0INV_DAG &&
                       (op < OV_OP_DOV || c->p.dirac == OV_DIRAC_OVERLAP_MS);
+  E.shifts = shifts;
   if (!shifts)
     std::memset(c->pinned, 0, sizeof(double) * CG_NSLOT * E.nsys + sizeof(int) * E.ctl_words);
   const size_t vb = (size_t)E.sb[0].V * 4 * sizeof(double2);
@@ -3538,6 +3540,7 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   E.htab.assign((size_t)E.ntab, SysDev{});
   SysDev d = base_dev(b);
   d.phi = (const double2*)phi;
+  E.shifts = false;
   d.e_out = b.r64;     // transformed planes of phi, W', conj W'
   d.fft_tmp = b.src64b;
   E.htab[T_APPLY] = d;
