@@ -828,7 +828,8 @@ ov_status res_setup(ov_ctx* c) {
 }
 
 // Run a call; when a resident launch gave up waiting (another process held part of the
-// chip), run it again with the per-pass kernels.  Inputs are untouched until then.
+// chip), run it again with the per-pass kernels.  The calls write no output that may lie on
+// an input before they know of the expiry.
 template <class F>
 ov_status res_retry(ov_ctx* c, F&& call) {
   const ov_status rc = call();
@@ -2824,7 +2825,12 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   TRY(run_apply(E, op, phi, direct && shifts, shifts));
   if (!direct) TRY(pack64(E));
   TRY(apply_sequence(E, op, direct));
-  if (!direct) TRY(unpack64(E));
+  if (!direct) {
+    // overlapping fields: out may be in, which a call whose resident launch gave up
+    // waiting needs again, so it is written only once the launch is known to have ended well
+    if (shifts && E.resident<double>(1)) TRY(read_scalars(E));
+    TRY(unpack64(E));
+  }
   TRY(shifts ? read_scalars(E) : sync(E));
   ov_status rc = OV_OK;
   for (int s = 0; s < nrhs; ++s) {

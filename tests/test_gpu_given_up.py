@@ -1,0 +1,95 @@
+"""Calls whose resident launch gives up waiting (OV_RES_WAIT_US=0: at its first unfinished
+wait) run again with the per-pass kernels.  The second run needs the inputs as they were, so
+every result is compared bit for bit with a context that has only the per-pass kernels
+(OV_PERSISTENT=0); kernel sampling shows that a resident launch was made (kernel 2) and that
+the per-pass kernels followed (kernel 3, the FP64 t pass)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_1005_3276_amd import _lib as L
+from paper_1005_3276_amd import inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+from gpu_util import CFG2, bits, dev, host, lattice, require_gpu
+
+DIMS = (8, 8, 8, 8)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    require_gpu(torch)
+
+
+def per_pass(monkeypatch, dims=DIMS, **kw):
+    """A context without the resident kernel."""
+    monkeypatch.setenv("OV_PERSISTENT", "0")
+    lat = lattice(dims, **kw)
+    monkeypatch.delenv("OV_PERSISTENT")
+    return lat
+
+
+def giving_up(monkeypatch, dims=DIMS, **kw):
+    """A context whose resident launches give up at once."""
+    monkeypatch.setenv("OV_RES_WAIT_US", "0")
+    lat = lattice(dims, **kw)
+    monkeypatch.delenv("OV_RES_WAIT_US")
+    return lat
+
+
+def same_bits(a, b):
+    return np.array_equal(bits(a), bits(b))
+
+
+def ptr(t):
+    return C.c_void_p(t.data_ptr())
+
+
+def gave_up(lat, call):
+    """Runs call; True if a resident launch was made and the per-pass kernels followed."""
+    lat.kernel_sampling(4)
+    for k in (2, 3):
+        lat.kernel_times(k)
+    call()
+    n = [lat.kernel_times(k)[1] for k in (2, 3)]
+    lat.kernel_sampling(0)
+    return n[0] > 0 and n[1] > 0
+
+
+def operate(lat, op, out, x, phi, nrhs, noalloc=False):
+    st = (L.OvStats * nrhs)()
+    if op == "sign":
+        L.check(L.lib().ov_sign(lat._h, ptr(out), ptr(x), nrhs, st), lat._h)
+    else:
+        fn = L.lib().ov_apply_noalloc if noalloc else L.lib().ov_apply
+        L.check(fn(lat._h, L.OPS[op], ptr(out), ptr(x), ptr(phi), nrhs, st), lat._h)
+
+
+@pytest.mark.parametrize("op", ["sign", "dov", "dov_dag", "m", "m_dag", "mdagm"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_in_place(monkeypatch, op, shift):
+    """out on top of in, exactly or one field on."""
+    print(f"[given up] {op} shift={shift}", flush=True)
+    nrhs = 2
+    phi, src = inputs.draw(DIMS, nrhs=nrhs, sigma2=0.25, seed=90)
+    p = dev(phi)
+    kw = dict(inner_tol=1e-10, **CFG2)
+
+    def run(lat, noalloc=False):
+        buf = torch.cat([dev(src), torch.zeros_like(dev(src)[:1])])
+        out = buf[shift:shift + nrhs]
+        torch.cuda.synchronize()
+        operate(lat, op, out, buf, p, nrhs, noalloc)
+        return host(out)
+
+    want = run(per_pass(monkeypatch, **kw))
+    lat = giving_up(monkeypatch, **kw)
+    got = []
+    assert gave_up(lat, lambda: got.append(run(lat)))
+    if op != "sign":
+        got.append(run(lat, noalloc=True))
+    for g in got:
+        assert same_bits(g, want), op
