@@ -15,6 +15,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/ov.h"
@@ -829,19 +830,37 @@ ov_status res_setup(ov_ctx* c) {
 
 // Run a call; when a resident launch gave up waiting (another process held part of the
 // chip), run it again with the per-pass kernels.  The calls write no output that may lie on
-// an input before they know of the expiry.
+// an input before they know of the expiry.  A batch's engine is led by its first member, the
+// FP64 solver that finishes some of its members by the first of those: any of the call's
+// contexts may have given up.
+template <class F>
+ov_status res_retry(ov_ctx* const* cs, size_t n, F&& call) {
+  const ov_status rc = call();
+  bool gave_up = false;
+  for (size_t k = 0; k < n; ++k) gave_up |= cs[k] && *cs[k]->res_abort;
+  if (!gave_up) return rc;
+  std::vector<std::pair<ov_ctx*, bool>> was;  // (context, resident) of each, once
+  for (size_t k = 0; k < n; ++k) {
+    ov_ctx* c = cs[k];
+    bool seen = false;
+    for (const auto& w : was) seen |= w.first == c;
+    if (!c || seen) continue;
+    was.push_back({c, c->resident});
+    if (*c->res_abort) {
+      HIPCHK(c, hipStreamSynchronize(c->priv));
+      *c->res_abort = 0;
+      k_zero32<<<1, 64, 0, c->priv>>>(&c->res_sh->abort, 1);
+      if (++c->res_aborts >= 3) was.back().second = false;
+    }
+  }
+  for (const auto& w : was) w.first->resident = false;
+  const ov_status again = call();
+  for (const auto& w : was) w.first->resident = w.second;
+  return again;
+}
 template <class F>
 ov_status res_retry(ov_ctx* c, F&& call) {
-  const ov_status rc = call();
-  if (!c || !*c->res_abort) return rc;
-  HIPCHK(c, hipStreamSynchronize(c->priv));
-  *c->res_abort = 0;
-  k_zero32<<<1, 64, 0, c->priv>>>(&c->res_sh->abort, 1);
-  const bool was = c->resident;
-  c->resident = false;
-  const ov_status again = call();
-  c->resident = was && ++c->res_aborts < 3;
-  return again;
+  return res_retry(&c, 1, std::forward<F>(call));
 }
 
 // The plan of a call (buffers, basis capacities, multi-shift parameters) for `ctxs`
@@ -2986,7 +3005,7 @@ ov_status ov_solve(ov_ctx* c, void* x, const void* b, const void* phi, int nrhs,
     bv[r] = (const char*)b + r * vb;
     xv[r] = (char*)x + r * vb;
   }
-  return res_retry(sc[0], [&] { return solve_systems(sc, bv, xv, ph, st); });
+  return res_retry(c, [&] { return solve_systems(sc, bv, xv, ph, st); });
 }
 
 ov_status ov_solve_batch(int n, ov_ctx* const* ctx, void* const* x, const void* const* b,
@@ -3011,7 +3030,7 @@ ov_status ov_solve_batch(int n, ov_ctx* const* ctx, void* const* x, const void* 
       ph.push_back(phi[i]);
     }
   }
-  return res_retry(sc[0], [&] { return solve_systems(sc, bv, xv, ph, st); });
+  return res_retry(sc.data(), sc.size(), [&] { return solve_systems(sc, bv, xv, ph, st); });
 }
 
 static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const void* xi, const void* phi,

@@ -93,3 +93,27 @@ def test_in_place(monkeypatch, op, shift):
         got.append(run(lat, noalloc=True))
     for g in got:
         assert same_bits(g, want), op
+
+
+def test_fallback_engine_of_a_batch(orc, monkeypatch):
+    """A batch whose first system converges at once (b = 0) and whose second is handed to the
+    FP64 solver, which the second context leads and whose launches give up: the batch runs
+    again and is certified under the oracle."""
+    from paper_1005_3276_amd import solve_batch
+    monkeypatch.setenv("OV_FORCE_FALLBACK", "1")
+    kw = dict(precision="mixed", outer_tol=1e-10, **CFG2)
+    phi, src = inputs.draw(DIMS, nrhs=1, sigma2=0.25, seed=91)
+    lats = [lattice(DIMS, **kw), giving_up(monkeypatch, **kw)]
+    xs = []
+
+    def call():
+        xs[:], st = solve_batch(lats, [torch.zeros_like(dev(src)), dev(src)], [dev(phi)] * 2)
+        assert st[1]["fp64_fallback"]
+
+    print("[given up] batch, FP64 fallback", flush=True)
+    assert gave_up(lats[1], call)
+    assert not host(xs[0]).any()
+    o = orc.Oracle(DIMS, inner_tol=1e-13, **CFG2)
+    assert o.residual(src[0], host(xs[1])[0], phi) <= 1e-10
+    x, _ = lats[1].solve(dev(src), dev(phi))  # and the context goes on
+    assert o.residual(src[0], host(x)[0], phi) <= 1e-10
