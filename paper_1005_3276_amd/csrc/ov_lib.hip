@@ -2816,6 +2816,12 @@ ov_status ov_get_launch(const ov_ctx* c, int* block, int* spt) {
   return OV_OK;
 }
 
+// na bytes at a and nb at b share some.
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb && y < x + na;
+}
+
 static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const void* phi,
                             int nrhs, ov_stats* st) {
   if (!c || !out || !in || nrhs < 1) return OV_ERR_INVALID_ARG;
@@ -2828,8 +2834,8 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   std::vector<ov_ctx*> v(nrhs, c);
   TRY(engine_init(E, v, false, false, c->p.inner_tol, c->p.inner_tol));
   // Operators without a multi-shift, and those whose multi-shift runs in resident launches,
-  // work on the caller's fields themselves, unless they overlap; the former report nothing
-  // from the device.
+  // work on the caller's fields themselves, unless the result overlaps one that is read; the
+  // former report nothing from the device.
   const bool shifts = op != OV_OP_HW && op != OV_OP_M0INV && op != OV_OP_M0INV_DAG &&
                       (op < OV_OP_DOV || c->p.dirac == OV_DIRAC_OVERLAP_MS);
   E.shifts = shifts;
@@ -2839,8 +2845,11 @@ static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const 
   E.io.resize(nrhs);
   for (int r = 0; r < nrhs; ++r)
     E.io[r] = {(const char*)in + r * vb, E.sb[r].x64, E.sb[r].r64, (char*)out + r * vb};
-  const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
-  const bool direct = (a > b ? a - b : b - a) >= nrhs * vb && (!shifts || E.resident<double>(1));
+  // phi: a site's result may land on another site's phi
+  const bool yuk = op == OV_OP_M || op == OV_OP_M_DAG || op == OV_OP_MDAGM;
+  const bool apart = !overlap(out, nrhs * vb, in, nrhs * vb) &&
+                     !(yuk && overlap(out, nrhs * vb, phi, vb / 4));
+  const bool direct = apart && (!shifts || E.resident<double>(1));
   TRY(run_apply(E, op, phi, direct && shifts, shifts));
   if (!direct) TRY(pack64(E));
   TRY(apply_sequence(E, op, direct));
