@@ -3574,6 +3574,13 @@ ov_status ov_boson(ov_ctx* c, const void* phi, double* S_host, void* G, void* F)
   E.htab.assign((size_t)E.ntab, SysDev{});
   SysDev d = base_dev(b);
   d.phi = (const double2*)phi;
+  const size_t sb = (size_t)b.V * sizeof(double2);
+  if (overlap(G, G ? sb : 0, phi, sb) || overlap(F, F ? sb : 0, phi, sb)) {
+    // the last pass reads phi beside its results
+    k_scale_copy<<<(unsigned)std::min((b.V + 255) / 256, 4096), 256, 0, E.st>>>(
+        b.x64, (const double2*)phi, 1.0, (size_t)b.V);
+    d.phi = b.x64;
+  }
   E.shifts = false;
   d.e_out = b.r64;     // transformed planes of phi, W', conj W'
   d.fft_tmp = b.src64b;
