@@ -2822,6 +2822,15 @@ static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return x < y + nb && y < x + na;
 }
 
+// A gradient on top of xi or phi is written only once the launches of Y = M X are known to
+// have ended well: the call runs again, from its inputs, when one has given up waiting.
+static ov_status before_gradient(Engine& E, const void* grad, const void* xi, const void* phi) {
+  const size_t sb = (size_t)E.sb[0].V * sizeof(double2);
+  if (E.resident<double>(1) && (overlap(grad, sb, xi, 4 * sb * E.nsys) || overlap(grad, sb, phi, sb)))
+    return sync(E);
+  return OV_OK;
+}
+
 static ov_status apply_impl(ov_ctx* c, int op, void* out, const void* in, const void* phi,
                             int nrhs, ov_stats* st) {
   if (!c || !out || !in || nrhs < 1) return OV_ERR_INVALID_ARG;
@@ -3123,6 +3132,7 @@ static ov_status force_impl(ov_ctx* c, void* grad_phi, double* S_host, const voi
   }
   // S_r = Re <xi_r, X_r>
   k_dot_re<<<E.nb_total, E.block, 0, E.st>>>(tab(E, T_APPLY), E.bmap, E.nb_total);
+  TRY(before_gradient(E, grad_phi, xi, phi));
   // G summed over right-hand sides in order (one launch over the sites)
   k_force<<<E.sb[0].nblk, E.block, 0, E.st>>>(tab(E, T_APPLY), nrhs, E.sb[0].nblk,
                                                (double2*)grad_phi);
@@ -3532,6 +3542,7 @@ static ov_status rational_force_impl(ov_ctx* c, double a0, int n, const double* 
     }
   HIPCHK(c, hipMemcpyAsync(E.ftab, ft.data(), sizeof(SysDev) * ft.size(), hipMemcpyHostToDevice,
                            E.st));
+  TRY(before_gradient(E, grad_phi, xi, phi));
   k_force<<<E.sb[0].nblk, E.block, 0, E.st>>>(E.ftab, nrhs * n, E.sb[0].nblk,
                                                (double2*)grad_phi);
   TRY(read_scalars(E));

@@ -117,3 +117,37 @@ def test_fallback_engine_of_a_batch(orc, monkeypatch):
     assert o.residual(src[0], host(xs[1])[0], phi) <= 1e-10
     x, _ = lats[1].solve(dev(src), dev(phi))  # and the context goes on
     assert o.residual(src[0], host(x)[0], phi) <= 1e-10
+
+
+@pytest.mark.parametrize("onto", ["phi", "xi"])
+@pytest.mark.parametrize("rational", [False, True])
+def test_gradient_over_inputs(monkeypatch, onto, rational):
+    """Eight sources, whose two-source multi-shifts (the solve's) run per pass and whose
+    one-source ones (Y = M X, just before the gradient is written) as resident launches: the
+    wait runs out there, with the gradient on top of phi or inside xi."""
+    dims, nrhs = (8, 8, 8, 16), 8
+    print(f"[given up] gradient on {onto}, rational={rational}", flush=True)
+    phi, src = inputs.draw(dims, nrhs=nrhs, sigma2=0.25, seed=92)
+    kw = dict(m=0.05, g=0.3, n_poles=12, lambda_min=0.2, lambda_max=8.0, outer_tol=1e-10)
+    al, be = np.array([0.4, 0.6]), np.array([0.1, 1.0])
+    vp = lambda a: a.ctypes.data_as(C.c_void_p)
+
+    def run(lat):
+        x, p = dev(src), dev(phi)
+        grad = p.view(-1) if onto == "phi" else x.view(-1)[lat.V:2 * lat.V]
+        torch.cuda.synchronize()
+        S, st = (C.c_double * nrhs)(), (L.OvStats * nrhs)()
+        if rational:
+            rc = L.lib().ov_rational_force(lat._h, 0.2, 2, vp(al), vp(be), ptr(grad), S, ptr(x),
+                                           ptr(p), nrhs, st)
+        else:
+            rc = L.lib().ov_force(lat._h, ptr(grad), S, ptr(x), ptr(p), nrhs, st)
+        L.check(rc, lat._h)
+        return list(S), host(grad)
+
+    want = run(per_pass(monkeypatch, dims, **kw))
+    lat = giving_up(monkeypatch, dims, **kw)
+    got = []
+    assert gave_up(lat, lambda: got.append(run(lat)))
+    assert got[0][0] == want[0]
+    assert same_bits(got[0][1], want[1])

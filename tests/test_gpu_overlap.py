@@ -66,3 +66,32 @@ def test_boson_over_phi(which):
     assert s.value == S
     same = [np.array_equal(bits(host(a)), bits(host(b).ravel())) for a, b in ((g, G), (f, F))]
     assert all(same)
+
+
+@pytest.mark.parametrize("onto", ["phi", "xi"])
+def test_gradient_over_its_inputs(onto):
+    """grad_phi on top of phi, or inside xi: the same kernels as with buffers apart, bit for
+    bit, in ov_force and ov_rational_force."""
+    dims = (8, 8, 4, 4)
+    print(f"[overlap] gradient on {onto}", flush=True)
+    phi, src = inputs.draw(dims, nrhs=2, sigma2=0.25, seed=94)
+    kw = dict(m=0.05, g=0.3, n_poles=12, lambda_min=0.2, lambda_max=8.0)
+    al, be = np.array([0.4, 0.6]), np.array([0.1, 1.0])
+    vp = lambda a: a.ctypes.data_as(C.c_void_p)
+    for rational in (False, True):
+        lat = lattice(dims, outer_tol=1e-10, **kw)
+        want = (lat.rational_force(dev(src), dev(phi), 0.2, al, be) if rational
+                else lat.force(dev(src), dev(phi)))
+        x, p = dev(src), dev(phi)
+        grad = p.view(-1) if onto == "phi" else x.view(-1)[lat.V:2 * lat.V]
+        torch.cuda.synchronize()
+        S, st = (C.c_double * 2)(), (L.OvStats * 2)()
+        if rational:
+            rc = L.lib().ov_rational_force(lat._h, 0.2, 2, vp(al), vp(be), ptr(grad), S, ptr(x),
+                                           ptr(p), 2, st)
+        else:
+            rc = L.lib().ov_force(lat._h, ptr(grad), S, ptr(x), ptr(p), 2, st)
+        L.check(rc, lat._h)
+        assert list(S) == want[0]
+        same = np.array_equal(bits(host(grad)), bits(host(want[1]).ravel()))
+        assert same, f"rational={rational}"
