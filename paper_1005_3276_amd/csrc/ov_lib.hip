@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/ov.h"
+#include "ov_gate.hpp"
 #include "ov_host.hpp"
 #include "ov_kernels.hpp"
 
@@ -43,6 +44,7 @@ struct ov_ctx {
   long long res_spin = 0;        // wall-clock ticks a resident wait may take
   int res_aborts = 0;
   hipEvent_t ev_res = nullptr;   // marks this context's work for another context's launch
+  hipError_t gate_err = hipSuccess;  // that wait failed
   bool capturing = false;        // inside a graph capture of the private stream
   std::map<long long, int> n_est;  // (precision, tolerance) -> iterations the last multi-shift needed
   int device = 0;
@@ -768,25 +770,22 @@ MsParams make_mp(const ov_ctx* c, double tol, int cap) {
   return m;
 }
 
-// Build the engine for `ctxs` (one entry per system) and carve the workspace.
-// Two resident launches that share the chip wait for each other's workgroups: launches of
-// one stream follow one another, and a launch on another context's stream (of this process)
-// is ordered after the work enqueued on the last one that launched.
-struct ResGate {
-  std::mutex mu;
-  ov_ctx* last = nullptr;
-};
-ResGate g_res_gate[kMaxDevices];
+ResGate<ov_ctx> g_res_gate[kMaxDevices];
 
-void res_gate(ov_ctx* c) {
-  if (c->device < 0 || c->device >= kMaxDevices) return;
-  ResGate& g = g_res_gate[c->device];
-  std::lock_guard<std::mutex> lock(g.mu);
-  if (g.last && g.last != c) {
-    if (hipEventRecord(g.last->ev_res, g.last->priv) == hipSuccess)
-      (void)hipStreamWaitEvent(c->priv, g.last->ev_res, 0);
-  }
-  g.last = c;
+// Enqueues context c's resident work in the order of its device's gate.  An event on the
+// other stream costs nothing while one context launches; without it, wait on the host.
+template <class F>
+auto res_ordered(ov_ctx* c, F&& enqueue) {
+  if (c->device < 0 || c->device >= kMaxDevices) return enqueue();
+  return g_res_gate[c->device].pass(
+      c,
+      [c](ov_ctx* last) {
+        hipError_t e = hipEventRecord(last->ev_res, last->priv);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->priv, last->ev_res, 0);
+        if (e != hipSuccess) e = hipStreamSynchronize(last->priv);
+        if (e != hipSuccess) c->gate_err = e;  // check_launch
+      },
+      enqueue);
 }
 
 template <class R>
@@ -1099,32 +1098,37 @@ template <class R>
 void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double bytes,
                      const MsParams& mp, int L) {
   ov_ctx* c = E.lead;
-  if (!c->capturing) res_gate(c);
   const unsigned range = 2 * (unsigned)L + 4;  // epochs of one launch
-  unsigned eoff = 0;
-  int nent = 0;
-  for (const ResLaunch& l : P.launches) {
-    ResArgs a{};
-    a.nrun = l.nrun;
-    a.L = L;
-    a.eoff = eoff;
-    a.nap = l.nap();
-    a.nap_face = l.nap_face();
-    a.sh = c->res_sh;
-    a.abort_host = c->res_abort;
-    a.face = E.face;
-    a.spin = c->res_spin;
-    std::copy(l.run, l.run + l.nrun, a.run);
-    MsParams m = mp;
-    const SysDev* Tp = T;
-    void* args[] = {(void*)&Tp, (void*)&a, (void*)&m};
-    // written per iteration: t_n of the launch's entries
-    Sample smp(c, 2, bytes / 3.0 / P.launches.size(), E.sb[0].h_ctl + 1);
-    (void)hipLaunchKernel(res_kernel<R>(l.K), dim3(l.grid), dim3(l.threads + 64), args, l.lds, E.st);
-    eoff += range;
-    for (int k = 0; k < l.nrun; ++k) nent += l.run[k].ne;
-  }
-  k_ms_coef<<<nent, COEF_THREADS, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
+  auto enqueue = [&]() {
+    unsigned eoff = 0;
+    int nent = 0;
+    for (const ResLaunch& l : P.launches) {
+      ResArgs a{};
+      a.nrun = l.nrun;
+      a.L = L;
+      a.eoff = eoff;
+      a.nap = l.nap();
+      a.nap_face = l.nap_face();
+      a.sh = c->res_sh;
+      a.abort_host = c->res_abort;
+      a.face = E.face;
+      a.spin = c->res_spin;
+      std::copy(l.run, l.run + l.nrun, a.run);
+      MsParams m = mp;
+      const SysDev* Tp = T;
+      void* args[] = {(void*)&Tp, (void*)&a, (void*)&m};
+      // written per iteration: t_n of the launch's entries
+      Sample smp(c, 2, bytes / 3.0 / P.launches.size(), E.sb[0].h_ctl + 1);
+      (void)hipLaunchKernel(res_kernel<R>(l.K), dim3(l.grid), dim3(l.threads + 64), args, l.lds, E.st);
+      eoff += range;
+      for (int k = 0; k < l.nrun; ++k) nent += l.run[k].ne;
+    }
+    k_ms_coef<<<nent, COEF_THREADS, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
+  };
+  if (c->capturing)
+    enqueue();  // run_graph has the gate
+  else
+    res_ordered(c, enqueue);
 }
 
 template <class R>
@@ -1418,6 +1422,8 @@ void launch_sym(const Engine& E, int t, int kind, SymIo io = {}) {
 
 ov_status check_launch(ov_ctx* c) {
   hipError_t e = hipGetLastError();
+  if (c->gate_err != hipSuccess) e = c->gate_err;
+  c->gate_err = hipSuccess;
   if (e != hipSuccess) {
     c->err = std::string("kernel launch: ") + hipGetErrorString(e);
     return OV_ERR_DEVICE;
@@ -2018,16 +2024,10 @@ long long n_est_key(size_t rsize, double tol) {
   return (long long)rsize * 1000 + (long long)std::lround(-std::log10(tol) * 10.0);
 }
 
-// Run `enqueue` (kernel launches only) through a cached hipGraph keyed by
-// everything its launches bake in; direct launches while kernel sampling is on.
+// The cached graph of `key`, captured now if there is none, on the engine's stream.
 template <class F>
-ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
+ov_status graph_launch(Engine& E, const std::string& key, F&& enqueue) {
   ov_ctx* c = E.lead;
-  if (E.resident_any()) res_gate(c);
-  if (!c->use_graphs || c->sample_max > 0) {
-    enqueue();
-    return check_launch(c);
-  }
   char buf[160];
   std::snprintf(buf, sizeof buf, "|%p|%p|%p|%d|%d|%d|%d|%d|%d|", (void*)E.tables, (void*)E.bmap,
                 (void*)E.gwtab, E.nb_total, E.nsys, E.block, E.nb_xy, E.nb_z, E.nb_t);
@@ -2057,6 +2057,23 @@ ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
   }
   HIPCHK(c, hipGraphLaunch(it->second, E.st));
   return OV_OK;
+}
+
+// Run `enqueue` (kernel launches only) through a cached hipGraph keyed by
+// everything its launches bake in; direct launches while kernel sampling is on.  Capture and
+// launch are under the gate: an event of another context on a stream that is being captured
+// would draw that context into the capture.
+template <class F>
+ov_status run_graph(Engine& E, const std::string& key, F&& enqueue) {
+  ov_ctx* c = E.lead;
+  if (!c->use_graphs || c->sample_max > 0) {
+    enqueue();
+    return check_launch(c);
+  }
+  auto run = [&]() { return graph_launch(E, key, enqueue); };
+  if (E.resident_any()) return res_ordered(c, run);
+  if (c->device < 0 || c->device >= kMaxDevices) return run();
+  return g_res_gate[c->device].alone(run);
 }
 
 }  // namespace
@@ -2720,10 +2737,7 @@ ov_status ov_ctx_create(const ov_params* p, void* hip_stream, ov_ctx** out) {
 ov_status ov_ctx_destroy(ov_ctx* c) {
   if (!c) return OV_ERR_INVALID_ARG;
   if (c->priv) (void)hipStreamSynchronize(c->priv);
-  if (c->device >= 0 && c->device < kMaxDevices) {
-    std::lock_guard<std::mutex> lock(g_res_gate[c->device].mu);
-    if (g_res_gate[c->device].last == c) g_res_gate[c->device].last = nullptr;
-  }
+  if (c->device >= 0 && c->device < kMaxDevices) g_res_gate[c->device].forget(c);
   clear_graphs(c);
   if (c->ev_res) (void)hipEventDestroy(c->ev_res);
   if (c->res_sh) (void)hipFree(c->res_sh);
