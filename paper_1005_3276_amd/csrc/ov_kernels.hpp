@@ -952,7 +952,7 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
 //      spinors (1 -+ g_mu) psi (two of four components: the hop needs no more) of the
 //      block's faces to the neighbouring workgroups by device-scope (sc1) stores;
 //   2. while these travel they apply the hops inside the block out of LDS, then read the
-//      neighbours' faces (device-scope loads) until every value is there (RES_EMPTY);
+//      neighbours' faces (device-scope loads) until every value is there (res_empty);
 //      meanwhile the service wave sends the block's partial norm and collects everybody's:
 //      words that carry the pass's epoch, so one exchange is the reduction and the barrier;
 //   3. with the sum they update t or r, while the service wave advances the recurrences.
@@ -1006,13 +1006,17 @@ struct ResEpoch {
   unsigned bump = 0;               // epochs the launches used
 };
 
-// A face value that has not arrived: every 32-bit word of the faces holds this pattern when a
-// launch starts and when it ends, and a reader puts it back.  Each value's first word (FP32),
-// high word (FP64) tells whether its eight bytes are there, so faces need no flag of their
-// own (waiting for the stores' end, a flag and its polling took a microsecond of every pass).
-// As the high word of a double it is a signalling NaN, which no arithmetic returns; a float
-// with this payload could only come from a caller's NaN, and would run into the wait limit.
-constexpr unsigned RES_EMPTY = 0x7ff45a5au;
+// A face value that has not arrived: the faces hold this pattern when a launch starts and when
+// it ends, and a reader puts it back.  Each value's first word (FP32), high word (FP64) tells
+// whether its eight bytes are there, so faces need no flag of their own (waiting for the
+// stores' end, a flag and its polling took a microsecond of every pass).  Both words are
+// signalling NaNs of their type, which no arithmetic returns, whatever NaN the caller's fields
+// hold (a published value is a sum; the kernels run in IEEE mode, where a sum quiets them).
+constexpr unsigned RES_EMPTY32 = 0x7fa45a5au;  // a float; even words
+constexpr unsigned RES_EMPTY64 = 0x7ff45a5au;  // the high word of a double; odd words
+__device__ __forceinline__ u32x4 res_empty() {
+  return u32x4{RES_EMPTY32, RES_EMPTY64, RES_EMPTY32, RES_EMPTY64};
+}
 constexpr unsigned RES_OOB = 0x80000000u;  // beyond every buffer: loads 0, stores nothing
 constexpr int RES_SC1 = 16;                // device-scope cache policy of a buffer access
 constexpr int RES_VOLATILE = (int)0x80000000;
@@ -1038,11 +1042,11 @@ __device__ __forceinline__ Half<float> face_ld(__amdgpu_buffer_rsrc_t rs, unsign
 // Every eight bytes of the two values have arrived.
 __device__ __forceinline__ bool face_in(const Half<double>& h) {
   const u32x4 p = __builtin_bit_cast(u32x4, h.a), q = __builtin_bit_cast(u32x4, h.b);
-  return p.y != RES_EMPTY && p.w != RES_EMPTY && q.y != RES_EMPTY && q.w != RES_EMPTY;
+  return p.y != RES_EMPTY64 && p.w != RES_EMPTY64 && q.y != RES_EMPTY64 && q.w != RES_EMPTY64;
 }
 __device__ __forceinline__ bool face_in(const Half<float>& h) {
   const u32x4 p = __builtin_bit_cast(u32x4, h);
-  return p.x != RES_EMPTY && p.z != RES_EMPTY;
+  return p.x != RES_EMPTY32 && p.z != RES_EMPTY32;
 }
 // Stores add the field's byte to the vector offset: behind a 16-byte store with an offset in
 // a scalar register the compiler leaves no wait state before it reuses the data registers,
@@ -1091,12 +1095,12 @@ __device__ __forceinline__ void lds_put(unsigned char* sh, unsigned j, const flo
 
 __device__ __forceinline__ void face_clear(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned Fb,
                                            double) {
-  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  const u32x4 e = res_empty();
   __builtin_amdgcn_raw_buffer_store_b128(e, rs, o, 0, RES_SC1);
   __builtin_amdgcn_raw_buffer_store_b128(e, rs, o + Fb, 0, RES_SC1);
 }
 __device__ __forceinline__ void face_clear(__amdgpu_buffer_rsrc_t rs, unsigned o, unsigned, float) {
-  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  const u32x4 e = res_empty();
   __builtin_amdgcn_raw_buffer_store_b128(e, rs, o, 0, RES_SC1);
 }
 
@@ -1326,7 +1330,7 @@ struct ResBlock {
 
 // Faces before the first resident launch of a call.
 __global__ void __launch_bounds__(256) k_res_empty(u32x4* __restrict__ face, size_t n) {
-  const u32x4 e = {RES_EMPTY, RES_EMPTY, RES_EMPTY, RES_EMPTY};
+  const u32x4 e = res_empty();
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)
     face[i] = e;
