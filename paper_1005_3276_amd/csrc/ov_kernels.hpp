@@ -1667,6 +1667,23 @@ __global__ void __launch_bounds__(RES_THREADS) k_ms_res(const SysDev* __restrict
   }
 }
 
+// Sites times iterations of the ne entries of a sampled resident launch (its t_n written), as
+// the stamp of one workgroup without a time.
+__global__ void __launch_bounds__(64) k_res_sites(const SysDev* __restrict__ tab, int ne, int L,
+                                                  unsigned long long* __restrict__ stamp) {
+  double sum = 0.0;
+  for (int e = threadIdx.x; e < ne; e += 64) {
+    const SysDev& S = tab[e];
+    if (S.active && *S.active == 0) continue;
+    sum += (double)S.g.V * (S.h_ctl[0] ? S.h_ctl[1] : L);
+  }
+  sum = wave_sum_last(sum);
+  if (threadIdx.x == 63) {
+    stamp[0] = stamp[1] = 0;
+    stamp[2] = (unsigned long long)sum;
+  }
+}
+
 // n > 0 values to LDS, four loads of a thread in flight: get(e) reads one (a thread without
 // a value reads the last one), put(e, v) stores it, `between` runs while the first four are on
 // their way.

@@ -71,14 +71,13 @@ struct ov_ctx {
   std::vector<hipEvent_t> ev_pool;             // pairs
   struct EvUse {
     int kernel;
-    double bytes;          // bytes of the launch, or bytes per iteration when n_dev is set
-    const int* n_dev;      // device iteration count of a persistent launch
+    double bytes;          // bytes of the whole launch
     int ts_blocks;         // workgroups that stamped region ts_index (0: none)
     double sites;          // sites of the launch (all systems): its stamped site count
                            // scales bytes to the systems that took part
   };
   std::vector<EvUse> ev_use;
-  // kernels: 0 / 1 FP32 t / r pass, 2 persistent, 3 / 4 FP64 t / r pass
+  // kernels: 0 / 1 FP32 t / r pass, 2 resident, 3 / 4 FP64 t / r pass
   int ev_call_count[5] = {0, 0, 0, 0, 0};
   double ksum_ms[5] = {0, 0, 0, 0, 0}, ksum_bytes[5] = {0, 0, 0, 0, 0};
   double ksum_kernel_ms[5] = {0, 0, 0, 0, 0};  // device-stamped kernel spans
@@ -1036,7 +1035,7 @@ struct Sample {
   ov_ctx* c;
   int k;
   bool on = false;
-  Sample(ov_ctx* c_, int k_, double bytes, const int* n_dev = nullptr) : c(c_), k(k_) {
+  Sample(ov_ctx* c_, int k_, double bytes) : c(c_), k(k_) {
     if (c->sample_max <= 0 || c->ev_call_count[k] >= c->sample_max) return;
     const size_t idx = c->ev_use.size();
     if (2 * idx + 2 > c->ev_pool.size()) {
@@ -1045,7 +1044,7 @@ struct Sample {
       c->ev_pool.push_back(a);
       c->ev_pool.push_back(b);
     }
-    c->ev_use.push_back({k, bytes, n_dev, 0, 0.0});
+    c->ev_use.push_back({k, bytes, 0, 0.0});
     c->ev_call_count[k]++;
     on = hipEventRecord(c->ev_pool[2 * idx], c->priv) == hipSuccess;
   }
@@ -1053,6 +1052,28 @@ struct Sample {
     if (on) (void)hipEventRecord(c->ev_pool[2 * (c->ev_use.size() - 1) + 1], c->priv);
   }
 };
+
+// Stamp regions (start, end, sites per workgroup) for the sampled launches of a call.
+void ensure_stamps(ov_ctx* c, int blocks) {
+  const size_t region = 3 * (size_t)blocks;
+  const size_t regions = 4 * (size_t)c->sample_max + 2;
+  if (c->ts_region < region || c->ts_regions < regions) {
+    if (c->ts_dev) (void)hipFree(c->ts_dev);  // synchronises the device
+    c->ts_dev = nullptr;
+    c->ts_region = std::max(region, c->ts_region);
+    c->ts_regions = std::max(regions, c->ts_regions);
+    if (hipMalloc((void**)&c->ts_dev, sizeof(unsigned long long) * c->ts_region * c->ts_regions) !=
+        hipSuccess) {
+      c->ts_dev = nullptr;
+      c->ts_region = c->ts_regions = 0;
+    }
+  }
+  if (c->wall_khz <= 0) {
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device) == hipSuccess)
+      c->wall_khz = khz;
+  }
+}
 
 // Collect the sampled durations after the stream has been synchronised.
 void collect_samples(ov_ctx* c) {
@@ -1079,14 +1100,8 @@ void collect_samples(ov_ctx* c) {
     }
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, c->ev_pool[2 * i], c->ev_pool[2 * i + 1]) == hipSuccess) {
-      double bytes = u.bytes * frac;
-      if (u.n_dev) {  // persistent launch: bytes per iteration x iterations run
-        int n = 0;
-        if (hipMemcpy(&n, u.n_dev, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) n = 0;
-        bytes *= n;
-      }
       c->ksum_ms[u.kernel] += ms;
-      c->ksum_bytes[u.kernel] += bytes;
+      c->ksum_bytes[u.kernel] += u.bytes * frac;
       c->kcount[u.kernel]++;
     }
   }
@@ -1095,9 +1110,10 @@ void collect_samples(ov_ctx* c) {
 }
 
 template <class R>
-void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double bytes,
-                     const MsParams& mp, int L) {
+void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, const MsParams& mp,
+                     int L) {
   ov_ctx* c = E.lead;
+  if (c->sample_max > 0) ensure_stamps(c, 2 * E.nb_total);
   const unsigned range = 2 * (unsigned)L + 4;  // epochs of one launch
   auto enqueue = [&]() {
     unsigned eoff = 0;
@@ -1117,11 +1133,28 @@ void launch_resident(const Engine& E, const SysDev* T, const ResPlan& P, double 
       MsParams m = mp;
       const SysDev* Tp = T;
       void* args[] = {(void*)&Tp, (void*)&a, (void*)&m};
-      // written per iteration: t_n of the launch's entries
-      Sample smp(c, 2, bytes / 3.0 / P.launches.size(), E.sb[0].h_ctl + 1);
-      (void)hipLaunchKernel(res_kernel<R>(l.K), dim3(l.grid), dim3(l.threads + 64), args, l.lds, E.st);
+      const int e0 = nent;
+      double vol = 0.0;
+      for (int k = 0; k < l.nrun; ++k) {
+        nent += l.run[k].ne;
+        vol += (double)l.run[k].ne * E.sb[l.run[k].e0 % E.nsys].V;
+      }
+      bool sampled;
+      {
+        Sample smp(c, 2, 0.0);
+        (void)hipLaunchKernel(res_kernel<R>(l.K), dim3(l.grid), dim3(l.threads + 64), args, l.lds, E.st);
+        sampled = smp.on;
+      }
+      const size_t idx = c->ev_use.size() - 1;
+      if (sampled && c->ts_dev && idx < c->ts_regions) {
+        // written per iteration: t_n of every entry that still iterates, counted behind it
+        auto& u = c->ev_use[idx];
+        u.ts_blocks = 1;
+        u.sites = vol * L;
+        u.bytes = 4.0 * sizeof(c2<R>) * u.sites;
+        k_res_sites<<<1, 64, 0, E.st>>>(T + e0, nent - e0, L, c->ts_dev + idx * c->ts_region);
+      }
       eoff += range;
-      for (int k = 0; k < l.nrun; ++k) nent += l.run[k].ne;
     }
     k_ms_coef<<<nent, COEF_THREADS, 0, E.st>>>(T, nent, L, mp, ResEpoch{c->res_sh, eoff});
   };
@@ -1142,7 +1175,7 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
   const double bytes = 3.0 * 4.0 * sizeof(c2<R>) * vol;  // per pass
   ov_ctx* c = E.lead;
   if (const ResPlan* pl = E.resident<R>(copies)) {
-    launch_resident<R>(E, T, *pl, bytes, mp, L);
+    launch_resident<R>(E, T, *pl, mp, L);
     return;
   }
   // z-marching passes when every system's workgroup owns whole xy planes of one
@@ -1164,26 +1197,7 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
     mps.zm = ok ? zc : 0;
     shb = ok ? (size_t)4 * E.block * sizeof(c2<R>) : 0;
   }
-  if (c->sample_max > 0) {  // stamp regions for the sampled launches of this call
-    const size_t region = 3 * (size_t)nbt_;  // (start, end, sites) per workgroup
-    const size_t regions = 4 * (size_t)c->sample_max + 2;
-    if (c->ts_region < region || c->ts_regions < regions) {
-      if (c->ts_dev) (void)hipFree(c->ts_dev);  // synchronises the device
-      c->ts_dev = nullptr;
-      c->ts_region = std::max(region, c->ts_region);
-      c->ts_regions = std::max(regions, c->ts_regions);
-      if (hipMalloc((void**)&c->ts_dev, sizeof(unsigned long long) * c->ts_region * c->ts_regions) !=
-          hipSuccess) {
-        c->ts_dev = nullptr;
-        c->ts_region = c->ts_regions = 0;
-      }
-    }
-    if (c->wall_khz <= 0) {
-      int khz = 0;
-      if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device) == hipSuccess)
-        c->wall_khz = khz;
-    }
-  }
+  if (c->sample_max > 0) ensure_stamps(c, nbt_);
   auto stamped = [&](Sample& smp) -> MsParams {
     MsParams m = mps;
     const size_t idx = c->ev_use.size() - 1;
