@@ -151,3 +151,21 @@ def test_gradient_over_inputs(monkeypatch, onto, rational):
     assert gave_up(lat, lambda: got.append(run(lat)))
     assert got[0][0] == want[0]
     assert same_bits(got[0][1], want[1])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solves(monkeypatch, precision):
+    """Calls of many launches: a solve and a rational function with their own outputs."""
+    print(f"[given up] solves {precision}", flush=True)
+    phi, src = inputs.draw(DIMS, nrhs=2, sigma2=0.25, seed=99)
+    b, p = dev(src), dev(phi)
+    kw = dict(precision=precision, inner_tol=1e-10, outer_tol=1e-10, **CFG2)
+    al, be = np.array([0.4, 0.6]), np.array([0.1, 1.0])
+    calls = [lambda lat: host(lat.solve(b, p)[0]), lambda lat: host(lat.rational(b, p, 0.2, al, be)[0])]
+    ref = per_pass(monkeypatch, **kw)
+    want = [f(ref) for f in calls]
+    lat = giving_up(monkeypatch, **kw)
+    for f, w in zip(calls, want):
+        got = []
+        assert gave_up(lat, lambda: got.append(f(lat)))
+        assert same_bits(got[0], w)
