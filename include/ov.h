@@ -33,7 +33,19 @@
  * memory, e.g. from torch).  The library owns only the context.  All work is
  * enqueued on the context's HIP stream; entry points return after the result
  * is complete on that stream unless stated otherwise.  One context per
- * stream; contexts are not thread-safe.
+ * stream; contexts are not thread-safe, several may be used from several
+ * threads.
+ *
+ * Sharing a GPU: multi-shift solves on lattices whose fields fit the chip run as
+ * one launch whose workgroups exchange data and must all be on the chip at once.
+ * The launches of a process's contexts are ordered among each other.  When
+ * another process, or a kernel on another stream, holds compute units for longer
+ * than the wait limit (half a second; the environment variable OV_RES_WAIT_US, in
+ * microseconds, read by ov_ctx_create), the launch gives up and the call runs
+ * again with one launch per pass: same result to rounding, later by the wait and
+ * the second run (the stats are the second run's).  A context that this happened
+ * to three times keeps to the second form.  OV_PERSISTENT=0 at ov_ctx_create
+ * selects it from the start.
  *
  * Errors: every function returns ov_status; no exception or abort crosses the
  * ABI.  On OV_ERR_NOT_CONVERGED outputs hold the best iterate and the stats
@@ -202,7 +214,8 @@ size_t ov_workspace_bytes_rational(const ov_ctx *ctx, int nrhs, int nshift);
 /* Hand the context a caller-owned device buffer (256-byte aligned; dev_ptr = NULL
  * returns to library-owned workspace).  While one is set, a call that needs more than
  * `bytes` returns OV_ERR_WORKSPACE and launches nothing: the library never adds a
- * hidden allocation to a caller's workspace.  Without one, calls allocate and keep their
+ * hidden allocation to a caller's workspace.  (A workspace with room for all but the
+ * buffers of the one-launch multi-shift form is used with a launch per pass.)  Without one, calls allocate and keep their
  * own workspace (freed by ov_ctx_destroy). */
 ov_status ov_set_workspace(ov_ctx *ctx, void *dev_ptr, size_t bytes);
 
@@ -226,7 +239,9 @@ ov_status ov_apply(ov_ctx *ctx, ov_op op, void *out, const void *in, const void 
  * buffer of the call (multi-shift basis, partial sums, counters, tables) carved from
  * one library-static device array of OV_NOALLOC_SCRATCH_BYTES per device instead of
  * a workspace.  Same arguments, kernels and results as ov_apply (bit for bit at the
- * same launch shape); the caller still owns in, out and phi.  The call allocates
+ * same launch shape; where the array holds the call's buffers but not those of the
+ * one-launch multi-shift form, that of a launch per pass, equal to rounding); the caller
+ * still owns in, out and phi.  The call allocates
  * nothing (no hipMalloc/hipFree, no host staging: that is set up by ov_ctx_create for
  * up to 16 right-hand sides) and ignores any workspace set with ov_set_workspace.
  * Limits and errors: a call whose buffers exceed the array (ov_workspace_bytes of the
@@ -359,10 +374,10 @@ ov_status ov_tune_ms(ov_ctx *ctx, int prec, int nrhs, int block, int sites_per_t
  * the dispatch gap), the number of sampled launches, their summed algorithmic
  * HBM bytes (3 spinor fields per site and pass: two read, one written; two
  * passes per iteration; the resident kernel, which keeps r and t on the chip, the one
- * field per site and iteration that it writes), and the summed kernel-only span max(end) - min(start)
+ * field per site and iteration of each source that it writes), and the summed kernel-only span max(end) - min(start)
  * over the workgroups (ms; what a kernel trace reports) with its launch count.
  * Any output pointer may be NULL.  reset != 0 clears the sums.  The stamp buffer
- * (2 x 8 bytes per workgroup and sampled launch) is allocated with hipMalloc
+ * (3 x 8 bytes per workgroup and sampled launch) is allocated with hipMalloc
  * when sampling first needs it and freed by ov_ctx_destroy. */
 ov_status ov_kernel_sampling(ov_ctx *ctx, int max_per_call);
 ov_status ov_kernel_times(ov_ctx *ctx, int kernel, double *total_ms, long long *count,

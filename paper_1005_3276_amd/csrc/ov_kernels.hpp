@@ -83,7 +83,7 @@ struct SysDev {
   int nshift;
   void* fft_tmp;            // momentum-space scratch field (kernel precision)
   int off_xy, off_z, off_t, off_zt; // first workgroup of this system in each transform pass
-  int xc;                   // x values per workgroup in the t pass (divides X, xc T <= 64)
+  int xc;                   // x values per workgroup in the t pass (divides X, xc T <= 256)
   double* pcs;              // [V] preconditioner scale per momentum (k_pcg_table), or null
   // the caller's fields (complex128, spin innermost) and their planar twins of a call:
   // k_pack io_in -> io_pin, k_unpack io_pout -> io_out
@@ -957,13 +957,14 @@ __global__ void __launch_bounds__(256) k_ms_r(const SysDev* __restrict__ sys,
 //      words that carry the pass's epoch, so one exchange is the reduction and the barrier;
 //   3. with the sum they update t or r, while the service wave advances the recurrences.
 // Nothing else crosses workgroups, so no cache is written back or invalidated, and t_n goes
-// to the basis with streaming stores that nothing waits for.  Bound by latency: an FP64 pass
-// at 16^4 (one source, 128 workgroups of 512 sites) takes 2.9 us, a third of it update and
-// publish, a third the hops out of LDS, the rest waits for faces and the sum (the per-pass
-// kernels: 10 us and the launch gap; with a flag per workgroup for its faces and the
-// partials read one after the other 3.7); 8^4 takes 1.8 us (4.5 us), 4^4, one workgroup and
-// no exchange, 1.4 us (3.3 us).  Two sources of 16^4 at once, 256 workgroups, 3.9 us; 16^3 x
-// 32, all of them in one sum, 4.0 us.
+// to the basis with streaming stores (no workgroup reads them, but they share the wait counter
+// of the face loads behind them, and the next publication waits for both).  Bound by latency:
+// an FP64 pass at 16^4 (one source, 128 workgroups of 512 sites) takes 2.9 us, a third of it
+// update and publish, a third the hops out of LDS, the rest waits for faces and the sum (the
+// per-pass kernels: 10 us and the launch gap; with a flag per workgroup for its faces and the
+// partials read one after the other 3.7); 8^4 takes 1.8 us (4.5 us), 4^4, one workgroup and no
+// exchange, 1.4 us (3.3 us). Two sources of 16^4 at once, 256 workgroups, 3.9 us; 16^3 x 32, all
+// of them in one sum, 4.0 us.
 struct ResRun {          // consecutive entries on one lattice
   int e0, ne;            // table entries
   int wg0;               // first workgroup of the launch
@@ -2380,9 +2381,9 @@ __host__ __device__ inline int fft_xy_plane(int X, int Y) { return Y * (X + 1) +
 // fft_tmp -> the result; either with the time twist of the direction, the inverse with
 // 1/V.  Needs X, Y <= 64, X Y <= 1024, and 2 NS fft_xy_plane + X + Y + 1 values of LDS.  All
 // components, so that the caller's layout is read and written here, in whole lines.  Bound
-// by latency: 8.5 us on 16^3 x 32 in FP64 (512 workgroups), 2 until the field is there,
-// 1.8 for each axis, 2.5 for the store; one component per workgroup and plain sums took 15,
-// and pack, k_yuk and unpack 19 more.
+// by latency: 12.3 us in a kernel trace on 16^3 x 32 in FP64 (512 workgroups), 8.5 of them by
+// the clocks of a workgroup: 2 until the field is there, 1.8 for each axis, 2.5 for the store;
+// one component per workgroup and plain sums took 15, and pack, k_yuk and unpack 19 more.
 template <class R, int NS>
 __global__ void __launch_bounds__(512) k_fft_xy(const SysDev* __restrict__ sys, int nsys, int inv,
                                                 int periodic, const SymIo io) {
@@ -2742,8 +2743,9 @@ __global__ void __launch_bounds__(256) k_fft_t_sym(const SysDev* __restrict__ sy
 // inverse, in place on fft_tmp in the site-line order ((x y) T + t) Z + z with a site's
 // components side by side.  One pass instead of three (k_fft_z twice and k_fft_t_sym): the
 // line stays in LDS, 2 NS fft_xy_plane(Z, T) + Z + T values and 2 (Z + T) doubles.  Bound by
-// the LDS reads of its sums: 16^3 x 32 in FP64 (256 workgroups) 14 us, 3 for each t axis, 2
-// for each z axis, 1.3 for the operator; the three passes took 44.
+// the LDS reads of its sums: 16^3 x 32 in FP64 (256 workgroups) 17.6 us in a kernel trace, 14
+// by the clocks of a workgroup: 3 for each t axis, 2 for each z axis, 1.3 for the operator; the
+// three passes took 44.
 template <class R, int NS>
 __global__ void __launch_bounds__(1024) k_fft_zt(const SysDev* __restrict__ sys, int nsys,
                                                  const SymParams sp) {
