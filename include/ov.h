@@ -258,7 +258,9 @@ ov_status ov_apply_noalloc(ov_ctx *ctx, ov_op op, void *out, const void *in, con
 
 /* Solve MdagM x = b for nrhs right-hand sides (all in one batched launch
  * sequence).  x is the initial guess on entry (zero it for a cold start) and
- * the solution on exit.  st may be NULL or an array of nrhs stats. */
+ * the solution on exit.  st may be NULL or an array of nrhs stats.  x lies apart
+ * from b and phi: in mixed precision a system handed to the FP64 solver
+ * (ov_stats.fp64_fallback) reads them after the first iterate has been written. */
 ov_status ov_solve(ov_ctx *ctx, void *x, const void *b, const void *phi, int nrhs,
                    ov_stats *st);
 
@@ -284,7 +286,9 @@ ov_status ov_force(ov_ctx *ctx, void *grad_phi, double *S_host, const void *xi,
  * every shift (the paper solves one CG per shift); shift i stops when its recursive
  * residual |zeta_i| ||r|| <= outer_tol ||in||.  No preconditioning (M0 does not
  * commute with the shifts).  The D of the context's form is used; the multi-shift
- * form evaluates the sign at inner_tol.  st: nrhs stats (outer_iters = iterations). */
+ * form evaluates the sign at inner_tol.  st: nrhs stats (outer_iters = iterations).
+ * out lies apart from in and phi when shift_pc_cutoff leaves some shifts to solves of
+ * their own: those add to out one after the other. */
 ov_status ov_rational(ov_ctx *ctx, double a0, int n, const double *alpha, const double *beta,
                       void *out, const void *in, const void *phi, int nrhs, ov_stats *st);
 
