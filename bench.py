@@ -318,6 +318,15 @@ def resident_roofline(spans):
             "bytes_per_launch": by / max(cnt, 1), "event_ms_per_solve": ms}
 
 
+def rooflines(spans, families, systems, volume):
+    """The kernel families that a sampled solve launched: pass families by name (kernel names
+    in `families`) and the resident kernel; all of them if none was sampled."""
+    fam = {n: family_roofline(spans, n, k, full_bytes(n, systems, volume))
+           for n, k in families.items()}
+    fam["resident"] = resident_roofline(spans)
+    return {n: r for n, r in fam.items() if r["launches_per_solve"] > 0} or fam
+
+
 def batched_config3(torch, Lattice, inputs):
     """The batched workload (12 sources on 16^3 x 32, mixed): timed solve, then one
     sampled solve giving the pass families' achieved bandwidth at that size."""
@@ -336,12 +345,12 @@ def batched_config3(torch, Lattice, inputs):
     out = {"seconds": e, "rhs_solves_per_s": 12 / e,
            "max_true_rel_res": max(s["true_rel_res"] for s in st),
            "outer_iters": [s["outer_iters"] for s in st],
-           "pass_rooflines": {
-               n: family_roofline(spans, n, k, full_bytes(n, 12, 16 * 16 * 16 * 32)) for n, k in (
-                   ("fp32_inner", "k_ms_t<float, *> + k_ms_r<float, *> (FP32 inner passes, "
-                                  "12 systems x 2 sources per launch)"),
-                   ("fp64_truth", "k_ms_t<double, *> + k_ms_r<double, *> (FP64 true-residual "
-                                  "passes, the systems due for an update x 2 sources per launch)"))}}
+           "pass_rooflines": rooflines(spans, {
+               "fp32_inner": "k_ms_t<float, *> + k_ms_r<float, *> (FP32 inner passes, "
+                             "12 systems x 2 sources per launch)",
+               "fp64_truth": "k_ms_t<double, *> + k_ms_r<double, *> (FP64 true-residual "
+                             "passes, the systems due for an update x 2 sources per launch)"},
+               12, 16 * 16 * 16 * 32)}
     del lat
     return out, b, p
 
@@ -652,9 +661,7 @@ def main():
     else:
         spans = sampled_spans(lat, lambda: lat.solve(dsrc, dphi))
 
-    fam = {n: family_roofline(spans, n, families[n], full_bytes(n, 1, lat.V)) for n in families}
-    fam["resident"] = resident_roofline(spans)
-    fam = {n: r for n, r in fam.items() if r["launches_per_solve"] > 0} or fam
+    fam = rooflines(spans, families, 1, lat.V)
     dom = max(fam, key=lambda n: fam[n]["event_ms_per_solve"])
     roofline = fam[dom]
     roofline_secondary = max((fam[n] for n in fam if n != dom),
