@@ -108,6 +108,7 @@ struct MsParams {
   double coef[MAXP];    // residues a_k
   int zm;               // > 0: z-marching passes over zm planes per workgroup (ZmMarch)
   int share;            // the XCDs share every system (xcd_share), not the launch
+  int nt;               // t_n and r_{n+1} are stored past the caches (launch_ms_tab)
   unsigned long long* tstamp;  // non-null: per workgroup (start, end, sites) stamps
 };
 
@@ -310,6 +311,15 @@ __device__ __forceinline__ void store_sp_nt(c2<R>* __restrict__ f, int V, int i,
     const ev2<R> e = {v[s].x, v[s].y};
     __builtin_nontemporal_store(e, (OV_GLOBAL ev2<R>*)(f + (size_t)s * V + i));
   }
+}
+
+// The multi-shift passes' stores: the next pass reads them, from the caches if they can hold them.
+template <class R>
+__device__ __forceinline__ void store_ms(int nt, c2<R>* __restrict__ f, int V, int i, const c2<R> v[4]) {
+  if (nt)
+    store_sp_nt<R>(f, V, i, v);
+  else
+    store_sp<R>(f, V, i, v);
 }
 
 template <class R, int ZC>
@@ -776,7 +786,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
         for (int k2 = 0; k2 < 4; ++k2)
           o[k2] = c2<R>{o[k2].x + beta * qq[k2].x, o[k2].y + beta * qq[k2].y};
       }
-      store_sp<R>(tn, g.V, ii, o);
+      store_ms<R>(mp->nt, tn, g.V, ii, o);
       return norm2_sp(o);
     });
     i = i1;  // every site done
@@ -788,7 +798,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) o[k2] = c2<R>{o[k2].x + beta * q[k2].x, o[k2].y + beta * q[k2].y};
     }
-    store_sp<R>(tn, g.V, i, o);
+    store_ms<R>(mp->nt, tn, g.V, i, o);
     acc = norm2_sp(o);
   }
   // remaining sites of this block (sites per thread > 1)
@@ -800,7 +810,7 @@ __device__ __forceinline__ int ms_t_block(const SysDev& S, int lb, int n, const 
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) o[k2] = c2<R>{o[k2].x + beta * q[k2].x, o[k2].y + beta * q[k2].y};
     }
-    store_sp<R>(tn, g.V, i, o);
+    store_ms<R>(mp->nt, tn, g.V, i, o);
     acc += norm2_sp(o);
   }
   const double tot = block_sum(acc, lds);
@@ -859,7 +869,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
       for (int k = 0; k < 4; ++k) rr[k] = r0[k];
 #pragma unroll
       for (int k = 0; k < 4; ++k) rr[k] = c2<R>{rr[k].x - alpha * w[k].x, rr[k].y - alpha * w[k].y};
-      store_sp<R>(rout, g.V, ii, rr);
+      store_ms<R>(mp->nt, rout, g.V, ii, rr);
       return norm2_sp(rr);
     });
     i = i1;
@@ -869,7 +879,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
     hw_compute<R>(nb, g, i, (R)mp->diag, w);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r[k] = c2<R>{r[k].x - alpha * w[k].x, r[k].y - alpha * w[k].y};
-    store_sp<R>(rout, g.V, i, r);
+    store_ms<R>(mp->nt, rout, g.V, i, r);
     acc = norm2_sp(r);
   }
   for (i += blockDim.x; !zm && i < i1; i += blockDim.x) {
@@ -878,7 +888,7 @@ __device__ __forceinline__ int ms_r_block(const SysDev& S, int lb, int n, const 
     load_sp<R>(rin, g.V, i, r);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r[k] = c2<R>{r[k].x - alpha * w[k].x, r[k].y - alpha * w[k].y};
-    store_sp<R>(rout, g.V, i, r);
+    store_ms<R>(mp->nt, rout, g.V, i, r);
     acc += norm2_sp(r);
   }
   const double tot = block_sum(acc, lds);
@@ -907,9 +917,8 @@ __device__ __forceinline__ void stamp_block(unsigned long long* ts, unsigned lon
 // history, the nine stencil operands and t_{n-1}) is issued before any of them
 // is consumed, and each wave finishes the reduction and the shift recurrences
 // on its own (identical bits in every wave), so the only barrier is the final
-// block reduction.  The stores of t_n and r_{n+1} go through the caches: the next pass reads
-// both, and the 256 MB last-level cache holds much of them (24^3 x 48: sign 8.4 -> 8.2 ms,
-// mixed solve 166 -> 159 with streaming stores replaced).
+// block reduction.  The stores of t_n and r_{n+1} go through the caches where those can hold
+// them for the next pass, which reads both (MsParams nt; launch_ms_tab).
 template <class R, int ZM, bool CF>
 __global__ void __launch_bounds__(256) k_ms_t(const SysDev* __restrict__ sys,
                                               const int* __restrict__ bmap, int nb_total, int n,

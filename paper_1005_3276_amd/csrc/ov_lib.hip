@@ -1182,6 +1182,12 @@ void launch_ms_tab(const Engine& E, const SysDev* T, const int* bmap_, int nbt_,
   // time slice (X Y == threads per workgroup, sites per thread zc >= 2 dividing Z);
   // OV_MS_ZM=0 switches them off
   MsParams mps = mp;
+  // t_n and r_{n+1} past the caches where the three fields of a pass exceed the 256 MiB
+  // last-level cache (FP64 sign, cached against streaming stores: 24^3 x 48, 127 MB, 6.99
+  // and 7.03 ms, 20^3 x 40, 61 MB, 3.57 and 3.76; 12 fields of 16^3 x 32, 302 MB, 12.7 and
+  // 12.2, 8 of 16^2 x 32^2, 403 MB, 16.9 and 15.2, 8 of 16^3 x 64 17.4 and 16.2, two of 32^4
+  // 23.0 and 21.6; at 201 and 255 MB either by 3 % or less)
+  mps.nt = bytes > 256.0 * (1 << 20);
   size_t shb = 0;
   {
     int zc = 0;
